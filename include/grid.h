@@ -479,16 +479,19 @@ grid_status grid_fd_vjp_adjoint(grid_model m, int32_t N, const float* q, const f
  *
  * The fused kernel exists in eight builds. Build 0 spreads each spatial vector over the
  * four lanes of a quad and gives every derivative column its own quad (few instructions per
- * lane: low latency). Builds 1, 2, 3 give every column one lane that runs the shared
- * sweeps itself (fewest instructions per knot: the highest throughput), allowed 1, 2 or 4
- * resident wavefronts per SIMD. Build 4 is build 0 split over three roles on different
- * wavefronts of a workgroup (RNEA and dtau/du at qdd = 0; M, qdd and the qdd-dependent part
- * of dtau/dq; M^-1), the shortest dependency chain. Build 5
+ * lane: low latency). Build 1 gives each body of a (knot, branch) problem one lane, so that a
+ * wavefront holds several problems (batches); builds 2 and 3 run the same kernel (they were its
+ * predecessor's forms with other register budgets). Build 4 is build 0 split over three roles on
+ * different wavefronts of a workgroup (RNEA and dtau/du at qdd = 0; M, qdd and the qdd-dependent
+ * part of dtau/dq; M^-1), the shortest dependency chain. Build 5
  * gives each (knot, branch) problem
  * one lane (no repeated work: the fewest instructions per knot, the longest latency). Build 6
  * is build 5 with four lanes per problem that share the columns of M^-1 and the derivative
  * columns (each repeats the rest): four times the wavefronts of build 5 for the same batch.
- * Build 7 is the same with two lanes per problem (twice the wavefronts of build 5).
+ * Build 7 is the same with two lanes per problem (twice the wavefronts of build 5). A robot with
+ * a base branch of more than 8 bodies runs build 1's kernel as builds 5, 6 and 7 as well, and as
+ * build 4 for batches of more than 256 knots (its long branch does not fit one lane, and the
+ * three-role kernel gives it a workgroup per knot).
  * Untuned, a batch runs build 4 while its wavefronts fit one per SIMD of the device, build 1
  * beyond, build 6 from 64 knots per compute unit and build 5 from 128, except for a robot
  * with a base branch of more than 8 bodies: build 4 up to 4096 knots, build 6 beyond.

@@ -790,8 +790,11 @@ grid_status grid_tune(grid_model m, const int32_t* Ns, int32_t count, const char
         int best = 0;
         float best_ms = 1e30f;
         for (int v = 0; v < grid_impl::kNumVariants; ++v) {
-            if (!m->fused_variant[v])
-                continue;   // not built for this model
+            bool seen = false;   // a kernel that a smaller index runs too
+            for (int w = 0; w < v; ++w)
+                seen = seen || grid_impl::kernel_of(m, w, N) == grid_impl::kernel_of(m, v, N);
+            if (seen)
+                continue;
             const int reps = 30;
             float times[5];
             for (int trial = 0; trial < 5; ++trial) {
@@ -850,8 +853,7 @@ grid_status grid_tune_apply(grid_model m, const int32_t* Ns, const int32_t* buil
     for (int k = 0; k < count; ++k) {
         if (Ns[k] < 1 || Ns[k] > (1 << 22) || (k > 0 && Ns[k] <= Ns[k - 1]))
             return fail(GRID_EINVAL, "knot counts must ascend within 1..2^22");
-        if (builds[k] < 0 || builds[k] >= grid_impl::kNumVariants ||
-            !m->fused_variant[builds[k]])
+        if (builds[k] < 0 || builds[k] >= grid_impl::kNumVariants)
             return fail(GRID_EUNSUPPORTED, "build " + std::to_string(builds[k]) +
                                                " does not exist for this model");
         table.emplace_back(Ns[k], builds[k]);
@@ -901,7 +903,7 @@ void load_tuning(grid_model m)
             break;
         long Nk = 0, v = 0;
         if (std::sscanf(last.c_str() + p, "[%ld, %ld]", &Nk, &v) != 2 || v < 0 ||
-            v >= kNumVariants || !m->fused_variant[v])
+            v >= kNumVariants)
             break;
         table.emplace_back((int32_t)Nk, (int)v);
         ++p;

@@ -29,6 +29,7 @@ namespace grid_impl {
 #include "grid_fused_src.inc"
 #include "grid_serial_src.inc"
 #include "grid_ops_src.inc"
+#include "grid_team_src.inc"
 
 bool analyse_topology(const int32_t* parent, int32_t n, Topology* out, std::string* err)
 {
@@ -149,6 +150,35 @@ int64_t workgroups_pipe(const Topology& t, int64_t nknots)
 int64_t workgroups_serial(const Topology& t, int64_t nknots, int knots_per_wave)
 {
     return (int64_t)t.insts.size() * ((nknots + knots_per_wave - 1) / knots_per_wave);
+}
+
+// A branch of more than 8 bodies: a lane that holds a whole problem would spill most of it
+bool long_branch(const Topology& t)
+{
+    for (const BranchShape& sh : t.shapes)
+        if (sh.B > 8)
+            return true;
+    return false;
+}
+
+// one lane per body: knots per wavefront of a group of nb branches of one shape, as in
+// grid_team.hip (a robot has at most 32 bodies, so a wavefront holds at least two knots)
+static int team_knots(const Topology& t, int shape)
+{
+    int nb = 0;
+    for (const BranchInst& inst : t.insts)
+        nb += inst.shape == shape ? 1 : 0;
+    return 64 / (nb * t.shapes[shape].B);
+}
+
+int64_t workgroups_team(const Topology& t, int64_t nknots)
+{
+    int64_t total = 0;
+    for (size_t s = 0; s < t.shapes.size(); ++s) {
+        const int K = team_knots(t, (int)s);
+        total += (nknots + K - 1) / K;
+    }
+    return total;
 }
 
 // standalone algorithms (ID, FD, M^-1, dID, VJP): problems per workgroup, as in grid_ops.hip
@@ -337,20 +367,99 @@ static void emit_prelude(std::ostringstream& os, const std::vector<RobotSource>&
     }
 }
 
+// The branches of one robot by shape, for the kernels with one lane per body: Group<g> holds
+// the NB branches of a shape with, per (branch, body), 24 floats (E_T, r, the second moment
+// P = tr(Ibar) / 2 - Ibar, h, m, the mass of the subtree, 1 for a prismatic joint) and 12 ints
+// (robot body, depth, rank among its siblings, children, the local ancestors from the parent
+// up as bytes); the robot row of each local body and the local column of each robot column
+// (-1: another branch's).
+static void emit_groups(std::ostringstream& os, const Topology& t, const std::vector<float>& consts)
+{
+    os << "template <int g> struct Group;\n";
+    for (size_t g = 0; g < t.shapes.size(); ++g) {
+        const BranchShape& sh = t.shapes[g];
+        const int B = sh.B;
+        std::vector<float> tab;
+        std::vector<int> ints, rowmap, colmap;
+        int nb = 0, first = -1;
+        bool prism = false;
+        for (size_t k0 = 0; k0 < t.insts.size(); ++k0) {
+            const BranchInst& in = t.insts[k0];
+            if (in.shape != (int)g)
+                continue;
+            first = first < 0 ? (int)k0 : first;
+            ++nb;
+            prism = prism || in.prism != 0;
+            std::vector<double> sub(B);
+            for (int i = B - 1; i >= 0; --i) {
+                sub[i] += consts[in.coff + (size_t)i * kConstStride + 21];
+                if (sh.parent[i] >= 0)
+                    sub[sh.parent[i]] += sub[i];
+            }
+            std::vector<int> depth(B), children(B), rank(B);
+            for (int i = 0; i < B; ++i) {
+                const int p = sh.parent[i];
+                depth[i] = p < 0 ? 0 : depth[p] + 1;
+                rank[i] = p < 0 ? 0 : children[p]++;
+            }
+            std::vector<int> col(t.n, -1);
+            for (int i = 0; i < B; ++i) {
+                const float* c = consts.data() + in.coff + (size_t)i * kConstStride;
+                tab.insert(tab.end(), c, c + 12);
+                const double tr = 0.5 * ((double)c[12] + c[13] + c[14]);
+                for (int e = 0; e < 6; ++e)
+                    tab.push_back((float)((e < 3 ? tr : 0.0) - c[12 + e]));
+                tab.insert(tab.end(), c + 18, c + 22);
+                tab.push_back((float)sub[i]);
+                tab.push_back((in.prism >> i) & 1ull ? 1.0f : 0.0f);
+                uint32_t words[8] = {};
+                int k = 0;
+                for (int a = sh.parent[i]; a >= 0; a = sh.parent[a], ++k)
+                    words[k / 4] |= (uint32_t)a << (8 * (k % 4));
+                ints.insert(ints.end(), {in.body[i], depth[i], rank[i], children[i]});
+                for (uint32_t w : words)
+                    ints.push_back((int)w);
+                rowmap.push_back(in.body[i]);
+                col[in.body[i]] = i;
+            }
+            colmap.insert(colmap.end(), col.begin(), col.end());
+        }
+        os << "__device__ alignas(16) const float grid_tf_" << g << "[" << tab.size() << "] = ";
+        emit_floats(os, tab.data(), tab.size());
+        os << ";\n";
+        const auto emit_ints = [&](const char* name, const std::vector<int>& v) {
+            os << "__device__ alignas(16) const int " << name << g << "[" << v.size() << "] = ";
+            emit_list(os, v);
+            os << ";\n";
+        };
+        emit_ints("grid_ti_", ints);
+        emit_ints("grid_tr_", rowmap);
+        emit_ints("grid_tc_", colmap);
+        os << "template <> struct Group<" << g << "> {\n    using S = Inst<" << first << ">::S;\n"
+           << "    static constexpr int N = Inst<" << first << ">::N;\n    static constexpr int NB = " << nb
+           << ";\n    static constexpr bool prism = " << (prism ? "true" : "false") << ";\n"
+           << "    __device__ static const float* table() { return grid_tf_" << g << "; }\n"
+           << "    __device__ static const int* ints() { return grid_ti_" << g << "; }\n"
+           << "    __device__ static const int* rowmap() { return grid_tr_" << g << "; }\n"
+           << "    __device__ static const int* colmap() { return grid_tc_" << g << "; }\n"
+           << "    __device__ static const float* a0() { return grid_a0_0; }\n};\n";
+    }
+}
+
 // A dispatcher walks the branches: workgroups [0, nb_0) run branch 0, the next nb_1 run
 // branch 1, and so on. The grid holds exactly sum nb_k workgroups, so the last branch takes
 // the rest without a bound check: with one branch nothing waits for nknots before the other
 // kernel arguments are loaded. (A workgroup past the end would still only recompute the last
 // knot and store nothing: every store checks its knot.) `@` in per_block and call stands for
-// the branch's Inst.
+// the branch's Inst, or for a group of branches (`type` Group).
 // `pool`, when given, is an expression in @ for the LDS floats one branch needs: the dispatch
 // then holds one array of the largest such size, `pool`, that every branch's call shares
-static void emit_dispatch(std::ostringstream& os, const Topology& t, const char* sig,
-                          const std::string& per_block, const std::string& call,
-                          const std::string& pool = "")
+static void emit_dispatch(std::ostringstream& os, const char* type, size_t count,
+                          const char* sig, const std::string& per_block,
+                          const std::string& call, const std::string& pool = "")
 {
-    auto inst = [](size_t k, std::string x) {
-        const std::string K = "Inst<" + std::to_string(k) + ">";
+    auto inst = [type](size_t k, std::string x) {
+        const std::string K = std::string(type) + "<" + std::to_string(k) + ">";
         for (size_t at; (at = x.find("@")) != std::string::npos;)
             x.replace(at, 1, K);
         return x;
@@ -358,13 +467,13 @@ static void emit_dispatch(std::ostringstream& os, const Topology& t, const char*
     os << sig << "\n{\n    int b = block;\n";
     if (!pool.empty()) {
         os << "    __shared__ __align__(16) float pool[grids::cmax(";
-        for (size_t k = 0; k < t.insts.size(); ++k)
+        for (size_t k = 0; k < count; ++k)
             os << (k ? ", " : "") << inst(k, pool);
         os << ")];\n";
     }
-    for (size_t k = 0; k < t.insts.size(); ++k) {
+    for (size_t k = 0; k < count; ++k) {
         auto sub = [&](const std::string& x) { return inst(k, x); };
-        if (k + 1 == t.insts.size()) {
+        if (k + 1 == count) {
             os << "    " << sub(call) << ";\n";
             break;
         }
@@ -388,41 +497,52 @@ std::string generate_source(const Topology& t, const std::vector<float>& consts,
     os << "#line 1 \"grid_device.hip\"\n";
     os << grid_device_src;
     os << "\n// generated: workgroup -> (branch, knot group)\n";
-    emit_dispatch(os, t, "template <int ST>\n__device__ void grid_dispatch(const grid::Args& a, int block)",
+    emit_dispatch(os, "Inst", t.insts.size(), "template <int ST>\n__device__ void grid_dispatch(const grid::Args& a, int block)",
              "64 / @::S::L", "grid::run_branch<@, ST>(a, b)");
     os << "#line 1 \"grid_fused.hip\"\n";
     os << grid_fused_src;
     os << "\n// generated: workgroup -> (branch, problem group), quad layout\n";
-    emit_dispatch(os, t, "__device__ void grid_dispatch_q(const grid::Args& a, int block)",
+    emit_dispatch(os, "Inst", t.insts.size(), "__device__ void grid_dispatch_q(const grid::Args& a, int block)",
              "(GRID_WAVES / @::S::W) * (16 / @::S::Q)", "gridq::run_fused<@>(a, b)");
+    os << "#define GRID_SERIAL_FUSED " << (long_branch(t) ? 0 : 1) << "\n";
     os << "#line 1 \"grid_serial.hip\"\n";
     os << grid_serial_src;
-    os << "\n// generated: workgroup -> (branch, 64 knots), one lane per knot\n";
-    emit_dispatch(os, t, "__device__ void grid_dispatch_s(const grid::Args& a, int block)", "64",
-             "grids::run_serial<@, 1, true>(a, b, pool)",
-             "grids::serial_stage_floats<@, 1, true>()");
-    os << "\n// generated: workgroup -> (branch, 16 or 32 knots), four or two lanes per knot; rows\n"
-          "// staged only when every branch's fit\n";
-    for (int L : {4, 2}) {
-        os << "constexpr bool grid_rows" << L << " = true";
-        for (size_t k = 0; k < t.insts.size(); ++k)
-            os << " && grids::serial_rows_fit<Inst<" << k << ">, " << L << ">()";
-        os << ";\n";
+    if (!long_branch(t)) {
+        os << "\n// generated: workgroup -> (branch, 64 knots), one lane per knot\n";
+        emit_dispatch(os, "Inst", t.insts.size(), "__device__ void grid_dispatch_s(const grid::Args& a, int block)", "64",
+                 "grids::run_serial<@, 1, true>(a, b, pool)",
+                 "grids::serial_stage_floats<@, 1, true>()");
+        os << "\n// generated: workgroup -> (branch, 16 or 32 knots), four or two lanes per knot; rows\n"
+              "// staged only when every branch's fit\n";
+        for (int L : {4, 2}) {
+            os << "constexpr bool grid_rows" << L << " = true";
+            for (size_t k = 0; k < t.insts.size(); ++k)
+                os << " && grids::serial_rows_fit<Inst<" << k << ">, " << L << ">()";
+            os << ";\n";
+        }
+        emit_dispatch(os, "Inst", t.insts.size(), "__device__ void grid_dispatch_s4(const grid::Args& a, int block)", "16",
+                 "grids::run_serial<@, 4, grid_rows4>(a, b, pool)",
+                 "grids::serial_stage_floats<@, 4, grid_rows4>()");
+        emit_dispatch(os, "Inst", t.insts.size(), "__device__ void grid_dispatch_s2(const grid::Args& a, int block)", "32",
+                 "grids::run_serial<@, 2, grid_rows2>(a, b, pool)",
+                 "grids::serial_stage_floats<@, 2, grid_rows2>()");
     }
-    emit_dispatch(os, t, "__device__ void grid_dispatch_s4(const grid::Args& a, int block)", "16",
-             "grids::run_serial<@, 4, grid_rows4>(a, b, pool)",
-             "grids::serial_stage_floats<@, 4, grid_rows4>()");
-    emit_dispatch(os, t, "__device__ void grid_dispatch_s2(const grid::Args& a, int block)", "32",
-             "grids::run_serial<@, 2, grid_rows2>(a, b, pool)",
-             "grids::serial_stage_floats<@, 2, grid_rows2>()");
     os << "\n// generated: workgroup -> (branch, 64 knots), M^-1 alone by either route\n";
-    emit_dispatch(os, t, "template <bool D>\n__device__ void grid_dispatch_minv(const grid::Args& a, int block)",
+    emit_dispatch(os, "Inst", t.insts.size(), "template <bool D>\n__device__ void grid_dispatch_minv(const grid::Args& a, int block)",
              "64", "grids::run_minv<@, D>(a, b)");
     os << "#line 1 \"grid_ops.hip\"\n";
     os << grid_ops_src;
     os << "\n// generated: workgroup -> (branch, problem group), standalone algorithms\n";
-    emit_dispatch(os, t, "template <int OP>\n__device__ void grid_dispatch_op(const gridq::OpArgs& a, int block)",
+    emit_dispatch(os, "Inst", t.insts.size(), "template <int OP>\n__device__ void grid_dispatch_op(const gridq::OpArgs& a, int block)",
              "gridq::op_problems<@::S, OP>()", "gridq::run_op<@, OP>(a, b)");
+    emit_groups(os, t, consts);
+    os << "#line 1 \"grid_team.hip\"\n";
+    os << grid_team_src;
+    os << "\n// generated: workgroup -> (group of branches, knots), one lane per body\n";
+    emit_dispatch(os, "Group", t.shapes.size(),
+                  "template <int OP>\n__device__ void grid_dispatch_t(const gridt::Args& a, int block)",
+                  "gridt::Lay<@>::KPB", "gridt::run_team<@, OP>(a, b, pool)",
+                  "gridt::team_floats<@>()");
     return os.str();
 }
 
@@ -441,7 +561,7 @@ std::string generate_pipe_source(const Topology& t, const std::vector<float>& co
     os << "#line 1 \"grid_fused.hip\"\n";
     os << grid_fused_src;
     os << "\n// generated: workgroup -> (branch, problem group), pipe kernel\n";
-    emit_dispatch(os, t, "__device__ void grid_dispatch_p(const grid::Args& a, int block)",
+    emit_dispatch(os, "Inst", t.insts.size(), "__device__ void grid_dispatch_p(const grid::Args& a, int block)",
                   "@::S::PP", "gridq::run_pipe<@>(a, b)");
     os << "extern \"C\" __global__ void __launch_bounds__(64 * GRID_PIPE_WAVES) "
           "grid_fdgrad_pipe(grid::Args args)\n{\n"

@@ -1,4 +1,5 @@
-// Batched gradient of forward dynamics, CDNA4 (gfx950) device code.
+// The staged pipeline (one lane per derivative column) and what every kernel shares, CDNA4
+// (gfx950) device code.
 //
 // Compiled at model-creation time (hiprtc) behind a generated prelude that writes one
 // robot's topology out as compile-time structures (grid_codegen.cpp):
@@ -180,10 +181,9 @@ __device__ __forceinline__ void ltl_solve(const float (&Lf)[S::B][S::B], const f
     }
 }
 
-// Stages: the fused kernel runs everything; the staged pipeline splits the same steps
-// over five launches with their intermediates in a device workspace (HBM).
+// Stages: the staged pipeline runs the steps as five launches with their intermediates in a
+// device workspace (HBM).
 enum Stage : int {
-    kFused = 0,
     kStageRnea = 1,     // transforms, RNEA(q, qd, 0)             -> c
     kStageMinv = 2,     // transforms, M, M = L^T L               -> L, 1/L_kk, M^-1
     kStageQdd = 3,      // L, c, tau                              -> qdd
@@ -199,7 +199,7 @@ __device__ __forceinline__ void run_branch(const Args& A, int kg)
     constexpr int L = S::L;
     constexpr int K = 64 / L;
     constexpr int N = I::N;
-    constexpr bool kFullSweeps = ST == kFused || ST == kStageRnea || ST == kStageDrnea;
+    constexpr bool kFullSweeps = ST == kStageRnea || ST == kStageDrnea;
     constexpr bool kNeedsX = kFullSweeps || ST == kStageMinv;
     __shared__ float s_M[K][B][B];
 
@@ -321,7 +321,7 @@ __device__ __forceinline__ void run_branch(const Args& A, int kg)
 
     // ------------------------------------------------------------ 3-4. M = L^T L
     float Lf[B][B], dinv[B];
-    if constexpr (ST == kFused || ST == kStageMinv) {
+    if constexpr (ST == kStageMinv) {
         // column jm of M as ID(q, 0, e_jm) without gravity, exchanged through LDS
         {
             float am[B][6], fm[B][6];
@@ -393,7 +393,7 @@ __device__ __forceinline__ void run_branch(const Args& A, int kg)
     }
 
     // ------------------------------------------------------------ M^-1 and the factor
-    if constexpr (ST == kFused || ST == kStageMinv) {
+    if constexpr (ST == kStageMinv) {
         float mc[B];                              // column jm of M^-1
 #pragma unroll
         for (int i = 0; i < B; ++i)
@@ -436,7 +436,7 @@ __device__ __forceinline__ void run_branch(const Args& A, int kg)
     }
 
     // ------------------------------------------------------------ 5. qdd
-    if constexpr (ST == kFused || ST == kStageQdd) {
+    if constexpr (ST == kStageQdd) {
         if constexpr (ST == kStageQdd) {
 #pragma unroll
             for (int i = 0; i < B; ++i)
@@ -614,7 +614,7 @@ __device__ __forceinline__ void run_branch(const Args& A, int kg)
     }
 
     // ------------------------------------------------------------ 8. -M^-1 dtau/du_j
-    if constexpr (ST == kFused || ST == kStageFdgrad) {
+    if constexpr (ST == kStageFdgrad) {
         ltl_solve<S>(Lf, dinv, dx);
         if (!valid)
             return;
@@ -650,26 +650,6 @@ using namespace grid;
 // defined by the generated epilogue: workgroup -> (branch, knot group)
 template <int ST>
 __device__ void grid_dispatch(const Args& args, int block);
-
-// Three builds of the fused kernel differ only in the register budget the compiler may
-// use: 1, 2 or 4 resident wavefronts per SIMD (more registers and no spills, or more
-// wavefronts to hide latency at large N). The autotuner picks one per batch size.
-extern "C" __global__ void __launch_bounds__(64) grid_fdgrad_fused(Args args)
-{
-    grid_dispatch<kFused>(args, (int)blockIdx.x);
-}
-
-extern "C" __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2)))
-grid_fdgrad_fused_w2(Args args)
-{
-    grid_dispatch<kFused>(args, (int)blockIdx.x);
-}
-
-extern "C" __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4)))
-grid_fdgrad_fused_w4(Args args)
-{
-    grid_dispatch<kFused>(args, (int)blockIdx.x);
-}
 
 extern "C" __global__ void __launch_bounds__(64) grid_stage_rnea(Args args)
 {

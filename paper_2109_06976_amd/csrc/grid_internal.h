@@ -15,10 +15,12 @@ namespace grid_impl {
 constexpr int kMaxBodies = 32;      // the 2B derivative columns of a branch fit one wavefront
 constexpr int kConstStride = 24;    // floats of device constants per body
 
-// builds of the fused kernel: quad layout, lane layout at 1, 2, 4 wavefronts per SIMD,
-// quad layout in three roles, one lane per knot, four lanes per knot, two lanes per knot
+// builds of the fused kernel (grid.h): quad layout, one lane per body, quad layout in three
+// roles, one lane per knot, four and two lanes per knot. Builds 2 and 3 run build 1's kernel,
+// and a robot with a long base branch runs it in place of the one-lane-per-knot forms too
+// (kernel_of)
 constexpr int kVariantQuad = 0;
-constexpr int kVariantLane1 = 1;
+constexpr int kVariantTeam = 1;
 constexpr int kVariantPipe = 4;
 constexpr int kVariantSerial = 5;
 constexpr int kVariantSerial4 = 6;
@@ -132,6 +134,7 @@ int64_t workgroups_for(const Topology& t, int64_t nknots);
 int64_t workgroups_quad(const Topology& t, int64_t nknots);
 int64_t workgroups_pipe(const Topology& t, int64_t nknots);
 int64_t workgroups_serial(const Topology& t, int64_t nknots, int knots_per_wave = 64);
+int64_t workgroups_team(const Topology& t, int64_t nknots);
 int64_t workgroups_op(const Topology& t, int64_t nknots, int op);
 int pipe_problems(int B);
 int pipe_waves(const Topology& t);
@@ -149,6 +152,8 @@ grid_status launch_fused_variant(grid_model m, int variant, int32_t N, const flo
                                  const float* qd, const float* tau, float* qdd, float* Minv,
                                  float* dq, float* dqd, hipStream_t stream);
 int fused_variant_for(grid_model m, int32_t N);
+int kernel_of(grid_model m, int variant, int32_t N);
+bool long_branch(const Topology& t);
 void load_tuning(grid_model m);
 std::string cache_dir();
 
@@ -176,7 +181,8 @@ struct grid_model_s {
     uint64_t code_hash = 0;             // of the two loaded code objects, in that order:
                                         // keys tuning tables
     int compute_units = 256;
-    hipFunction_t fused_variant[grid_impl::kNumVariants] = {};   // see kVariantQuad
+    // kernels of the builds that have one of their own (see kVariantQuad, kernel_of)
+    hipFunction_t fused_variant[grid_impl::kNumVariants] = {};
     hipFunction_t op[grid_impl::kNumOps] = {};                    // see kOpId
     hipFunction_t minv_route[2] = {};   // M^-1 one lane per knot: L^T L, direct
     std::vector<std::pair<int32_t, int>> tuned;   // (largest N, variant), ascending N

@@ -232,6 +232,10 @@ grid_status launch(hipFunction_t fn, unsigned blocks, unsigned threads, int32_t 
 
 namespace grid_impl {
 
+// The largest batch of a robot with a long branch that the three-role kernel runs faster than
+// one lane per body (humanoid30, see kernel_of)
+constexpr int kPipeLongKnots = 256;
+
 int fused_variant_for(grid_model m, int32_t N)
 {
     for (const auto& e : m->tuned)
@@ -240,48 +244,63 @@ int fused_variant_for(grid_model m, int32_t N)
     if (!m->tuned.empty())
         return m->tuned.back().second;
     // untuned: the three-role kernel while its wavefronts fit one per SIMD of the device (the
-    // lowest-latency form), the lane layout beyond (fewer instructions per knot), and from 64
-    // knots per compute unit the forms with one problem per lane or four lanes (no repeated
-    // sweeps; build 5 once it has 128 knots per compute unit, half a wavefront per SIMD at
-    // least). A branch of more than 8 bodies makes the lane layout's repeated sweeps expensive,
-    // and the tuner keeps the three-role kernel far beyond one wavefront per SIMD there
-    // (humanoid30: up to 4096 knots, then build 6)
+    // lowest-latency form), one lane per body beyond, and from 64 knots per compute unit the
+    // forms with one problem per lane or four lanes (build 5 once it has 128 knots per compute
+    // unit, half a wavefront per SIMD at least). A robot with a long branch keeps the index of
+    // the three-role build up to 4096 knots; kernel_of says what it runs there
     const int64_t waves = workgroups_pipe(m->topo, N) * pipe_waves(m->topo);
     if (waves <= 4 * (int64_t)m->compute_units)
         return kVariantPipe;
-    int largest = 0;
-    for (const BranchShape& sh : m->topo.shapes)
-        largest = std::max(largest, sh.B);
-    if (largest > 8)
+    if (long_branch(m->topo))
         return N <= 4096 ? kVariantPipe : kVariantSerial4;
     if (N >= 128 * (int64_t)m->compute_units)
         return kVariantSerial;
     if (N >= 64 * (int64_t)m->compute_units)
         return kVariantSerial4;
-    return kVariantLane1;
+    return kVariantTeam;
+}
+
+// The build whose kernel runs a batch of N knots under the index `variant`
+int kernel_of(grid_model m, int variant, int32_t N)
+{
+    if (variant > kVariantTeam && variant < kVariantPipe)
+        return kVariantTeam;
+    if (!long_branch(m->topo))
+        return variant;
+    // a long branch: one lane per knot does not fit the registers, and the three-role kernel
+    // holds one such problem per workgroup
+    if (variant == kVariantPipe)
+        return N <= kPipeLongKnots ? kVariantPipe : kVariantTeam;
+    return variant == kVariantQuad ? kVariantQuad : kVariantTeam;
 }
 
 grid_status launch_fused_variant(grid_model m, int variant, int32_t N, const float* q,
                                  const float* qd, const float* tau, float* qdd, float* Minv,
                                  float* dq, float* dqd, hipStream_t stream)
 {
-    if (variant < 0 || variant >= kNumVariants || !m->fused_variant[variant])
+    if (variant < 0 || variant >= kNumVariants)
         return fail(GRID_EUNSUPPORTED, "the requested build of the fused kernel does not exist for the model");
-    if (variant == kVariantQuad)
-        return launch(m->fused_variant[variant], (unsigned)workgroups_quad(m->topo, N),
-                      64u * (unsigned)m->topo.waves, N, nullptr, q, qd, tau, qdd, Minv, dq, dqd,
-                      stream);
-    if (variant == kVariantPipe)
-        return launch(m->fused_variant[variant], (unsigned)workgroups_pipe(m->topo, N),
-                      64u * (unsigned)pipe_waves(m->topo), N, nullptr, q, qd, tau, qdd, Minv, dq,
-                      dqd, stream);
-    if (variant == kVariantSerial || variant == kVariantSerial4 || variant == kVariantSerial2)
-        return launch(m->fused_variant[variant],
-                      (unsigned)workgroups_serial(m->topo, N, variant == kVariantSerial ? 64
-                                                          : variant == kVariantSerial2 ? 32 : 16),
-                      64u, N, nullptr, q, qd, tau, qdd, Minv, dq, dqd, stream);
-    return launch(m->fused_variant[variant], (unsigned)workgroups_for(m->topo, N), 64u, N,
-                  nullptr, q, qd, tau, qdd, Minv, dq, dqd, stream);
+    variant = kernel_of(m, variant, N);
+    int64_t blocks = 0;
+    unsigned threads = 64;
+    switch (variant) {
+    case kVariantQuad:
+        blocks = workgroups_quad(m->topo, N);
+        threads = 64u * (unsigned)m->topo.waves;
+        break;
+    case kVariantPipe:
+        blocks = workgroups_pipe(m->topo, N);
+        threads = 64u * (unsigned)pipe_waves(m->topo);
+        break;
+    case kVariantTeam:
+        blocks = workgroups_team(m->topo, N);
+        break;
+    default:
+        blocks = workgroups_serial(m->topo, N, variant == kVariantSerial ? 64
+                                               : variant == kVariantSerial2 ? 32 : 16);
+    }
+    return launch(m->fused_variant[variant], (unsigned)blocks, threads, N, nullptr, q, qd, tau,
+                  qdd, Minv, dq, dqd, stream);
 }
 
 grid_status launch_fused(grid_model m, int32_t N, const float* q, const float* qd,
@@ -566,12 +585,13 @@ grid_status grid_model_create(const grid_model_desc* desc, int32_t device, uint3
     static const char* const kStages[5] = {"grid_stage_rnea", "grid_stage_minv", "grid_stage_qdd",
                                            "grid_stage_drnea", "grid_stage_fdgrad"};
     static const char* const kVariants[kNumVariants] = {
-        "grid_fdgrad_quad", "grid_fdgrad_fused", "grid_fdgrad_fused_w2", "grid_fdgrad_fused_w4",
+        "grid_fdgrad_quad", "grid_fdgrad_team", nullptr, nullptr,
         "grid_fdgrad_pipe", "grid_fdgrad_serial", "grid_fdgrad_serial4", "grid_fdgrad_serial2"};
     m->compute_units = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
     hipError_t e = hipModuleLoadData(&m->module, code.data());
     for (int k = 0; k < kNumVariants && e == hipSuccess; ++k)
-        if (k != kVariantPipe)   // build 4 lives in the pipe module alone
+        // build 4 lives in the pipe module alone; only the kernels that kernel_of names exist
+        if (k != kVariantPipe && kernel_of(m, k, 1) == k)
             e = hipModuleGetFunction(&m->fused_variant[k], m->module, kVariants[k]);
     static const char* const kOps[kNumOps] = {"grid_op_id", "grid_op_fd", "grid_op_minv",
                                               "grid_op_idgrad", "grid_op_vjp"};
