@@ -443,7 +443,8 @@ grid_status grid_minv(grid_model m, int32_t N, const float* q, float* Minv, void
 
 /* M(q)^-1 by a chosen route, to compare the paper's direct inverse with the factorisation
  * the fused kernels use (Sec. IV-B lists the direct inverse of Carpentier and Mansard):
- *   GRID_MINV_QUAD         grid_minv itself (quad layout: columns of M, L^T L, solves);
+ *   GRID_MINV_QUAD         grid_minv itself (columns of M, L^T L, solves: quad layout, or one
+ *                          lane per body for large batches and long branches);
  *   GRID_MINV_LANE_LTL     one lane per knot and branch: M by composite rigid bodies,
  *                          M = L^T L along ancestor paths, B triangular solve pairs;
  *   GRID_MINV_LANE_DIRECT  one lane per knot and branch: the direct articulated-body
@@ -489,8 +490,8 @@ grid_status grid_fd_vjp_adjoint(grid_model m, int32_t N, const float* q, const f
  * is build 5 with four lanes per problem that share the columns of M^-1 and the derivative
  * columns (each repeats the rest): four times the wavefronts of build 5 for the same batch.
  * Build 7 is the same with two lanes per problem (twice the wavefronts of build 5). A robot with
- * a base branch of more than 8 bodies runs build 1's kernel as builds 5, 6 and 7 as well, and as
- * build 4 for batches of more than 256 knots (its long branch does not fit one lane, and the
+ * a base branch of more than 8 bodies runs build 1's kernel as builds 0, 5, 6 and 7 as well, and
+ * as build 4 for batches of more than 256 knots (its long branch does not fit one lane, and the
  * three-role kernel gives it a workgroup per knot).
  * Untuned, a batch runs build 4 while its wavefronts fit one per SIMD of the device, build 1
  * beyond, build 6 from 64 knots per compute unit and build 5 from 128, except for a robot

@@ -499,12 +499,14 @@ std::string generate_source(const Topology& t, const std::vector<float>& consts,
     os << "\n// generated: workgroup -> (branch, knot group)\n";
     emit_dispatch(os, "Inst", t.insts.size(), "template <int ST>\n__device__ void grid_dispatch(const grid::Args& a, int block)",
              "64 / @::S::L", "grid::run_branch<@, ST>(a, b)");
+    os << "#define GRID_LONG_BRANCH " << (long_branch(t) ? 1 : 0) << "\n";
     os << "#line 1 \"grid_fused.hip\"\n";
     os << grid_fused_src;
-    os << "\n// generated: workgroup -> (branch, problem group), quad layout\n";
-    emit_dispatch(os, "Inst", t.insts.size(), "__device__ void grid_dispatch_q(const grid::Args& a, int block)",
-             "(GRID_WAVES / @::S::W) * (16 / @::S::Q)", "gridq::run_fused<@>(a, b)");
-    os << "#define GRID_SERIAL_FUSED " << (long_branch(t) ? 0 : 1) << "\n";
+    if (!long_branch(t)) {
+        os << "\n// generated: workgroup -> (branch, problem group), quad layout\n";
+        emit_dispatch(os, "Inst", t.insts.size(), "__device__ void grid_dispatch_q(const grid::Args& a, int block)",
+                 "(GRID_WAVES / @::S::W) * (16 / @::S::Q)", "gridq::run_fused<@>(a, b)");
+    }
     os << "#line 1 \"grid_serial.hip\"\n";
     os << grid_serial_src;
     if (!long_branch(t)) {

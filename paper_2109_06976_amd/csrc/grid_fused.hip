@@ -1243,6 +1243,10 @@ __device__ __forceinline__ void run_pipe(const grid::Args& A, int block)
 // own entry point, grid_fdgrad_pipe_mixed)
 #ifndef GRID_PIPE_ONLY
 
+// (a robot with a branch of more than 8 bodies has no build 0: humanoid30 at 128 knots took 26 us,
+// the three-role kernel 12 and one lane per body 17)
+#if !GRID_LONG_BRANCH
+
 // defined by the generated epilogue: workgroup -> (branch, problem group)
 __device__ void grid_dispatch_q(const grid::Args& args, int block);
 
@@ -1251,6 +1255,8 @@ extern "C" __global__ void __launch_bounds__(64 * GRID_WAVES) grid_fdgrad_quad(g
 {
     grid_dispatch_q(args, (int)blockIdx.x);
 }
+
+#endif  // GRID_LONG_BRANCH
 
 // The three-role kernel (grid_fdgrad_pipe) has an entry point only in the module generated
 // for it alone, which is compiled with its own schedule.

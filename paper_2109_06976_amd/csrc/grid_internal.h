@@ -17,7 +17,7 @@ constexpr int kConstStride = 24;    // floats of device constants per body
 
 // builds of the fused kernel (grid.h): quad layout, one lane per body, quad layout in three
 // roles, one lane per knot, four and two lanes per knot. Builds 2 and 3 run build 1's kernel,
-// and a robot with a long base branch runs it in place of the one-lane-per-knot forms too
+// and a robot with a long base branch runs it in place of the others but the three-role one
 // (kernel_of)
 constexpr int kVariantQuad = 0;
 constexpr int kVariantTeam = 1;
@@ -184,6 +184,7 @@ struct grid_model_s {
     // kernels of the builds that have one of their own (see kVariantQuad, kernel_of)
     hipFunction_t fused_variant[grid_impl::kNumVariants] = {};
     hipFunction_t op[grid_impl::kNumOps] = {};                    // see kOpId
+    hipFunction_t team_op[grid_impl::kNumOps] = {};   // their forms with one lane per body
     hipFunction_t minv_route[2] = {};   // M^-1 one lane per knot: L^T L, direct
     std::vector<std::pair<int32_t, int>> tuned;   // (largest N, variant), ascending N
     hipModule_t module = nullptr;

@@ -279,6 +279,10 @@ extern "C" __global__ void __launch_bounds__(64) grid_op_id(gridq::OpArgs args)
     grid_dispatch_op<gridq::kOpId>(args, (int)blockIdx.x);
 }
 
+// a robot with a branch of more than 8 bodies runs the forms with one lane per body instead (its
+// columns of M would take several passes here)
+#if !GRID_LONG_BRANCH
+
 extern "C" __global__ void __launch_bounds__(64) grid_op_fd(gridq::OpArgs args)
 {
     grid_dispatch_op<gridq::kOpFd>(args, (int)blockIdx.x);
@@ -298,5 +302,7 @@ extern "C" __global__ void __launch_bounds__(64) grid_op_vjp(gridq::OpArgs args)
 {
     grid_dispatch_op<gridq::kOpVjp>(args, (int)blockIdx.x);
 }
+
+#endif  // GRID_LONG_BRANCH
 
 #endif  // GRID_PIPE_ONLY

@@ -271,7 +271,7 @@ int kernel_of(grid_model m, int variant, int32_t N)
     // holds one such problem per workgroup
     if (variant == kVariantPipe)
         return N <= kPipeLongKnots ? kVariantPipe : kVariantTeam;
-    return variant == kVariantQuad ? kVariantQuad : kVariantTeam;
+    return kVariantTeam;
 }
 
 grid_status launch_fused_variant(grid_model m, int variant, int32_t N, const float* q,
@@ -596,7 +596,13 @@ grid_status grid_model_create(const grid_model_desc* desc, int32_t device, uint3
     static const char* const kOps[kNumOps] = {"grid_op_id", "grid_op_fd", "grid_op_minv",
                                               "grid_op_idgrad", "grid_op_vjp"};
     for (int k = 0; k < kNumOps && e == hipSuccess; ++k)
-        e = hipModuleGetFunction(&m->op[k], m->module, kOps[k]);
+        if (k == kOpId || !long_branch(m->topo))   // the others run one lane per body there
+            e = hipModuleGetFunction(&m->op[k], m->module, kOps[k]);
+    static const char* const kTeamOps[kNumOps] = {nullptr, "grid_team_fd", "grid_team_minv",
+                                                  "grid_team_idgrad", "grid_team_vjp"};
+    for (int k = 0; k < kNumOps && e == hipSuccess; ++k)
+        if (kTeamOps[k])
+            e = hipModuleGetFunction(&m->team_op[k], m->module, kTeamOps[k]);
     for (int k = 0; k < 5 && e == hipSuccess; ++k)
         e = hipModuleGetFunction(&m->stage[k], m->module, kStages[k]);
     static const char* const kMinvRoutes[2] = {"grid_minv_serial", "grid_minv_direct"};
@@ -697,11 +703,21 @@ static grid_status launch_op(grid_model m, int op, int32_t N, const float* q, co
     a.out0 = out0;
     a.out1 = needs_out1 ? out1 : nullptr;
     a.out2 = vjp ? out2 : nullptr;
-    const unsigned blocks = (unsigned)workgroups_op(m->topo, N, op);
-    const unsigned threads = op == kOpIdGrad ? 64u * (unsigned)m->topo.waves : 64u;
     void* params[] = {&a};
-    HIP_TRY(hipModuleLaunchKernel(m->op[op], blocks, 1, 1, threads, 1, 1, 0, (hipStream_t)stream,
-                                  params, nullptr));
+    const int64_t blocks = workgroups_op(m->topo, N, op);
+    const int waves = op == kOpIdGrad ? m->topo.waves : 1;
+    // One lane per body beyond two wavefronts per SIMD of the quad layout, whose quads repeat the
+    // shared sweeps: at two the forms are level (chain7 FD at 4096 knots 6.1 us both, dID at 2048
+    // 6.9 and 7.3), at four the quad layout takes 1.5 times as long (FD at 8192 9.5 and 6.4, dID
+    // at 4096 11.9 and 7.9; quad12 FD at 4096 4.5 and 3.7). A long branch takes it at every size.
+    if (m->team_op[op] &&
+        (long_branch(m->topo) || blocks * waves > 8 * (int64_t)m->compute_units)) {
+        HIP_TRY(hipModuleLaunchKernel(m->team_op[op], (unsigned)workgroups_team(m->topo, N), 1, 1,
+                                      64u, 1, 1, 0, (hipStream_t)stream, params, nullptr));
+        return GRID_OK;
+    }
+    HIP_TRY(hipModuleLaunchKernel(m->op[op], (unsigned)blocks, 1, 1, 64u * (unsigned)waves, 1, 1, 0,
+                                  (hipStream_t)stream, params, nullptr));
     return GRID_OK;
 }
 

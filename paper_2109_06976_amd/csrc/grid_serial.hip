@@ -869,7 +869,7 @@ __device__ __forceinline__ void run_minv(const grid::Args& A, int block)
 
 // (a robot with a branch of more than 8 bodies has none of the three: they would hold most of
 // a problem in scratch memory)
-#if GRID_SERIAL_FUSED
+#if !GRID_LONG_BRANCH
 
 // defined by the generated epilogue: workgroup -> (branch, 64 knots)
 __device__ void grid_dispatch_s(const grid::Args& args, int block);
@@ -895,7 +895,7 @@ extern "C" __global__ void __launch_bounds__(64) grid_fdgrad_serial2(grid::Args 
     grid_dispatch_s2(args, (int)blockIdx.x);
 }
 
-#endif  // GRID_SERIAL_FUSED
+#endif  // GRID_LONG_BRANCH
 
 // defined by the generated epilogue: workgroup -> (branch, 64 knots), M^-1 by either route
 template <bool kDirect>

@@ -39,6 +39,9 @@
 // Bound by the latency of its chain of LDS exchanges up to a few wavefronts per SIMD, by VALU
 // issue beyond. humanoid30: 236 us per launch at 4096 knots and 648 at 16384 on the kernels it
 // took the place of, 28 and 82 here; chain7 at 4096 knots 11.4 and 10.7, quad12 7.8 and 6.8.
+// FD / M^-1 / dID / VJP against the quad layout's (grid_ops.hip): humanoid30 at 4096 knots 46 /
+// 31 / 192 / 68 and 12 / 12 / 18 / 18 us, at 128 9.8 / 9.7 / 11.3 / 14.1 and 8.7 / 8.0 / 11.1 /
+// 12.0; chain7 at 32768 29 / 16 / 77 / 53 and 13 / 11 / 19 / 19.
 
 namespace gridt {
 
@@ -823,6 +826,30 @@ extern "C" __global__ void __launch_bounds__(64) grid_fdgrad_team(grid::Args arg
     const gridt::Args a{args.nknots, args.q, args.qd, args.tau, nullptr,
                         args.qdd, args.Minv, args.dqdd_dq, args.dqdd_dqd};
     grid_dispatch_t<gridt::kFdGrad>(a, (int)blockIdx.x);
+}
+
+extern "C" __global__ void __launch_bounds__(64) grid_team_fd(gridq::OpArgs x)
+{
+    const gridt::Args a{x.nknots, x.q, x.qd, x.u, nullptr, x.out0, nullptr, nullptr, nullptr};
+    grid_dispatch_t<gridt::kFd>(a, (int)blockIdx.x);
+}
+
+extern "C" __global__ void __launch_bounds__(64) grid_team_minv(gridq::OpArgs x)
+{
+    const gridt::Args a{x.nknots, x.q, nullptr, nullptr, nullptr, x.out0, nullptr, nullptr, nullptr};
+    grid_dispatch_t<gridt::kMinv>(a, (int)blockIdx.x);
+}
+
+extern "C" __global__ void __launch_bounds__(64) grid_team_idgrad(gridq::OpArgs x)
+{
+    const gridt::Args a{x.nknots, x.q, x.qd, x.u, nullptr, x.out0, x.out1, nullptr, nullptr};
+    grid_dispatch_t<gridt::kIdGrad>(a, (int)blockIdx.x);
+}
+
+extern "C" __global__ void __launch_bounds__(64) grid_team_vjp(gridq::OpArgs x)
+{
+    const gridt::Args a{x.nknots, x.q, x.qd, x.u, x.u2, x.out0, x.out1, x.out2, nullptr};
+    grid_dispatch_t<gridt::kVjp>(a, (int)blockIdx.x);
 }
 
 #endif  // GRID_PIPE_ONLY

@@ -761,7 +761,7 @@ MIXED_ONE_LAUNCH, MIXED_PERSISTENT, MIXED_PER_ROBOT = range(3)
 MIXED_MODES = ("one_launch", "persistent", "per_robot")
 JOINT_REVOLUTE, JOINT_PRISMATIC, JOINT_FIXED = 0, 1, 2
 # each build's kernel; a robot with a base branch of more than 8 bodies runs grid_fdgrad_team as
-# builds 5 to 7 too, and as build 4 beyond 256 knots
+# builds 0 and 5 to 7 too, and as build 4 beyond 256 knots
 BUILD_KERNELS = ("grid_fdgrad_quad", "grid_fdgrad_team", "grid_fdgrad_team", "grid_fdgrad_team",
                  "grid_fdgrad_pipe", "grid_fdgrad_serial", "grid_fdgrad_serial4",
                  "grid_fdgrad_serial2")

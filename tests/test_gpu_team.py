@@ -72,3 +72,52 @@ def test_team_gradient_at_wavefront_edges(orc, name):
             np.testing.assert_array_equal(Mi, np.swapaxes(Mi, 1, 2))
     finally:
         m.close()
+
+
+@pytest.mark.parametrize("name", list(ROBOTS))
+def test_team_algorithms_on_large_batches(orc, name):
+    """FD, M^-1, dID and the adjoint VJP at a batch that takes them to one lane per body on any
+    robot (more than two wavefronts per SIMD of the quad layout: 64 sampled knots, the first and
+    the last included, against the oracle), the other knots finite."""
+    import torch
+    make, _ = ROBOTS[name]
+    robot = make()
+    n = robot.n
+    N = 256 * torch.cuda.get_device_properties(0).multi_processor_count + 3
+    m = grid.Model(robot)
+    try:
+        say(f"[gpu] team algorithms {name} N={N}")
+        kn = synth.random_knots(n, N, 1500)
+        g = synth.random_knots(n, N, 1501).qd
+        q, qd, tau, gb = (torch.from_numpy(a).cuda() for a in (kn.q, kn.qd, kn.tau, g))
+        vec = [torch.full((N, n), float("nan"), device="cuda") for _ in range(4)]
+        mat = [torch.full((N, n, n), float("nan"), device="cuda") for _ in range(3)]
+        m.fd(q, qd, tau, vec[0])
+        m.minv(q, mat[0])
+        m.id_grad(q, qd, tau, mat[1], mat[2])
+        grid.fd_vjp_adjoint(m, q, qd, tau, gb, vec[1], vec[2], vec[3])
+        torch.cuda.synchronize()
+        for t in vec + mat:
+            assert bool(torch.isfinite(t).all())
+        idx = np.unique(np.concatenate([[0, N - 1], np.random.default_rng(7).integers(0, N, 62)]))
+        it = torch.from_numpy(idx).cuda()
+        fd, qb, qdb, tb = (t[it].cpu().numpy() for t in vec)
+        mi, dq, dqd = (t[it].cpu().numpy() for t in mat)
+        r_fd, r_mi, r_dq, r_dqd, r_v = [], [], [], [], []
+        for k in idx:
+            r_fd.append(orc.fd(robot, kn.q[k], kn.qd[k], kn.tau[k]))
+            r_mi.append(orc.minv_cholesky(robot, kn.q[k]))
+            a, b = orc.rnea_grad(robot, kn.q[k], kn.qd[k], kn.tau[k])
+            r_dq.append(a)
+            r_dqd.append(b)
+            t = r_mi[-1] @ g[k].astype(np.float64)
+            r_v.append((-(a.T @ t), -(b.T @ t), t))
+        check((name, "FD"), fd, np.stack(r_fd), 1e-4)
+        check((name, "Minv"), mi, np.stack(r_mi), 1e-3)
+        check((name, "dID dq"), dq, np.stack(r_dq), 1e-3)
+        check((name, "dID dqd"), dqd, np.stack(r_dqd), 1e-3)
+        for got, ref, what in zip((qb, qdb, tb), zip(*r_v), ("qbar", "qdbar", "taubar")):
+            check((name, what), got, np.stack(ref), 1e-3)
+        np.testing.assert_array_equal(mi, np.swapaxes(mi, 1, 2))
+    finally:
+        m.close()
