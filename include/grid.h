@@ -443,8 +443,8 @@ grid_status grid_minv(grid_model m, int32_t N, const float* q, float* Minv, void
 
 /* M(q)^-1 by a chosen route, to compare the paper's direct inverse with the factorisation
  * the fused kernels use (Sec. IV-B lists the direct inverse of Carpentier and Mansard):
- *   GRID_MINV_QUAD         grid_minv itself (columns of M, L^T L, solves: quad layout, or one
- *                          lane per body for large batches and long branches);
+ *   GRID_MINV_QUAD         grid_minv itself (columns of M, L^T L, solves: quad layout; one lane
+ *                          per problem for large batches, per body for long branches);
  *   GRID_MINV_LANE_LTL     one lane per knot and branch: M by composite rigid bodies,
  *                          M = L^T L along ancestor paths, B triangular solve pairs;
  *   GRID_MINV_LANE_DIRECT  one lane per knot and branch: the direct articulated-body
@@ -478,24 +478,22 @@ grid_status grid_fd_vjp_adjoint(grid_model m, int32_t N, const float* q, const f
 
 /* ------------------------------------------------------------------ autotuning
  *
- * The fused kernel exists in eight builds. Build 0 spreads each spatial vector over the
- * four lanes of a quad and gives every derivative column its own quad (few instructions per
- * lane: low latency). Build 1 gives each body of a (knot, branch) problem one lane, so that a
- * wavefront holds several problems (batches); builds 2 and 3 run the same kernel (they were its
- * predecessor's forms with other register budgets). Build 4 is build 0 split over three roles on
- * different wavefronts of a workgroup (RNEA and dtau/du at qdd = 0; M, qdd and the qdd-dependent
- * part of dtau/dq; M^-1), the shortest dependency chain. Build 5
- * gives each (knot, branch) problem
- * one lane (no repeated work: the fewest instructions per knot, the longest latency). Build 6
- * is build 5 with four lanes per problem that share the columns of M^-1 and the derivative
- * columns (each repeats the rest): four times the wavefronts of build 5 for the same batch.
- * Build 7 is the same with two lanes per problem (twice the wavefronts of build 5). A robot with
- * a base branch of more than 8 bodies runs build 1's kernel as builds 0, 5, 6 and 7 as well, and
- * as build 4 for batches of more than 256 knots (its long branch does not fit one lane, and the
- * three-role kernel gives it a workgroup per knot).
- * Untuned, a batch runs build 4 while its wavefronts fit one per SIMD of the device, build 1
- * beyond, build 6 from 64 knots per compute unit and build 5 from 128, except for a robot
- * with a base branch of more than 8 bodies: build 4 up to 4096 knots, build 6 beyond.
+ * The fused kernel exists in eight builds, which share four kernels. Build 0 spreads each spatial
+ * vector over the four lanes of a quad and gives every derivative column its own quad (few
+ * instructions per lane: low latency). Build 4 is build 0 split over three roles on different
+ * wavefronts of a workgroup (RNEA and dtau/du at qdd = 0; M, qdd and the qdd-dependent part of
+ * dtau/dq; M^-1), the shortest dependency chain. Build 5 gives each (knot, branch) problem one
+ * lane (no repeated work: the fewest instructions per knot, the longest latency). Build 1 gives
+ * each body of a problem one lane, so that a wavefront holds several problems, while that takes
+ * at most two wavefronts per SIMD, and runs build 5's kernel beyond. Builds 2, 3 and 6 are the
+ * same as build 1 and build 7 the same as build 5 (indices that tables may hold).
+ * A robot with a base branch of more than 8 bodies runs one lane per body as every build but 4,
+ * and as build 4 for batches of more than 256 knots (its long branch does not fit one lane, and
+ * the three-role kernel gives it a workgroup per knot).
+ * Untuned, a batch runs build 4 while its wavefronts fit one per SIMD of the device, build 0
+ * while its fit, build 1 beyond, build 6 from 64 knots per compute unit and build 5 from 128,
+ * except for a robot with a base branch of more than 8 bodies: build 4 up to 4096 knots, build 6
+ * beyond.
  * grid_tune times each build on the model's
  * device for every knot count in Ns (synthetic inputs, HIP events, median of repeats),
  * keeps the fastest per count, and from then on grid_fd_grad uses, for a batch of N

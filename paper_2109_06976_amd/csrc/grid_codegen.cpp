@@ -30,6 +30,7 @@ namespace grid_impl {
 #include "grid_serial_src.inc"
 #include "grid_ops_src.inc"
 #include "grid_team_src.inc"
+#include "grid_axes_src.inc"
 
 bool analyse_topology(const int32_t* parent, int32_t n, Topology* out, std::string* err)
 {
@@ -147,9 +148,9 @@ int64_t workgroups_pipe(const Topology& t, int64_t nknots)
     return total;
 }
 
-int64_t workgroups_serial(const Topology& t, int64_t nknots, int knots_per_wave)
+int64_t workgroups_serial(const Topology& t, int64_t nknots)
 {
-    return (int64_t)t.insts.size() * ((nknots + knots_per_wave - 1) / knots_per_wave);
+    return (int64_t)t.insts.size() * ((nknots + 63) / 64);
 }
 
 // A branch of more than 8 bodies: a lane that holds a whole problem would spill most of it
@@ -507,27 +508,15 @@ std::string generate_source(const Topology& t, const std::vector<float>& consts,
         emit_dispatch(os, "Inst", t.insts.size(), "__device__ void grid_dispatch_q(const grid::Args& a, int block)",
                  "(GRID_WAVES / @::S::W) * (16 / @::S::Q)", "gridq::run_fused<@>(a, b)");
     }
+    os << "#line 1 \"grid_axes.hip\"\n";
+    os << grid_axes_src;
     os << "#line 1 \"grid_serial.hip\"\n";
     os << grid_serial_src;
     if (!long_branch(t)) {
         os << "\n// generated: workgroup -> (branch, 64 knots), one lane per knot\n";
-        emit_dispatch(os, "Inst", t.insts.size(), "__device__ void grid_dispatch_s(const grid::Args& a, int block)", "64",
-                 "grids::run_serial<@, 1, true>(a, b, pool)",
-                 "grids::serial_stage_floats<@, 1, true>()");
-        os << "\n// generated: workgroup -> (branch, 16 or 32 knots), four or two lanes per knot; rows\n"
-              "// staged only when every branch's fit\n";
-        for (int L : {4, 2}) {
-            os << "constexpr bool grid_rows" << L << " = true";
-            for (size_t k = 0; k < t.insts.size(); ++k)
-                os << " && grids::serial_rows_fit<Inst<" << k << ">, " << L << ">()";
-            os << ";\n";
-        }
-        emit_dispatch(os, "Inst", t.insts.size(), "__device__ void grid_dispatch_s4(const grid::Args& a, int block)", "16",
-                 "grids::run_serial<@, 4, grid_rows4>(a, b, pool)",
-                 "grids::serial_stage_floats<@, 4, grid_rows4>()");
-        emit_dispatch(os, "Inst", t.insts.size(), "__device__ void grid_dispatch_s2(const grid::Args& a, int block)", "32",
-                 "grids::run_serial<@, 2, grid_rows2>(a, b, pool)",
-                 "grids::serial_stage_floats<@, 2, grid_rows2>()");
+        emit_dispatch(os, "Inst", t.insts.size(),
+                      "template <int OP>\n__device__ void grid_dispatch_s(const gridv::BatchArgs& a, int block)",
+                      "64", "grids::run_serial<@, OP>(a, b, pool)", "grids::serial_floats<@, OP>()");
     }
     os << "\n// generated: workgroup -> (branch, 64 knots), M^-1 alone by either route\n";
     emit_dispatch(os, "Inst", t.insts.size(), "template <bool D>\n__device__ void grid_dispatch_minv(const grid::Args& a, int block)",
@@ -542,7 +531,7 @@ std::string generate_source(const Topology& t, const std::vector<float>& consts,
     os << grid_team_src;
     os << "\n// generated: workgroup -> (group of branches, knots), one lane per body\n";
     emit_dispatch(os, "Group", t.shapes.size(),
-                  "template <int OP>\n__device__ void grid_dispatch_t(const gridt::Args& a, int block)",
+                  "template <int OP>\n__device__ void grid_dispatch_t(const gridv::BatchArgs& a, int block)",
                   "gridt::Lay<@>::KPB", "gridt::run_team<@, OP>(a, b, pool)",
                   "gridt::team_floats<@>()");
     return os.str();

@@ -15,10 +15,8 @@ namespace grid_impl {
 constexpr int kMaxBodies = 32;      // the 2B derivative columns of a branch fit one wavefront
 constexpr int kConstStride = 24;    // floats of device constants per body
 
-// builds of the fused kernel (grid.h): quad layout, one lane per body, quad layout in three
-// roles, one lane per knot, four and two lanes per knot. Builds 2 and 3 run build 1's kernel,
-// and a robot with a long base branch runs it in place of the others but the three-role one
-// (kernel_of)
+// builds of the fused kernel (grid.h). Four kernels: quad layout, one lane per body, quad layout
+// in three roles, one lane per (knot, branch) problem; kernel_of says which of them an index runs
 constexpr int kVariantQuad = 0;
 constexpr int kVariantTeam = 1;
 constexpr int kVariantPipe = 4;
@@ -133,7 +131,7 @@ grid_status validate_desc(const grid_model_desc* d, std::string* err);
 int64_t workgroups_for(const Topology& t, int64_t nknots);
 int64_t workgroups_quad(const Topology& t, int64_t nknots);
 int64_t workgroups_pipe(const Topology& t, int64_t nknots);
-int64_t workgroups_serial(const Topology& t, int64_t nknots, int knots_per_wave = 64);
+int64_t workgroups_serial(const Topology& t, int64_t nknots);
 int64_t workgroups_team(const Topology& t, int64_t nknots);
 int64_t workgroups_op(const Topology& t, int64_t nknots, int op);
 int pipe_problems(int B);
@@ -184,7 +182,8 @@ struct grid_model_s {
     // kernels of the builds that have one of their own (see kVariantQuad, kernel_of)
     hipFunction_t fused_variant[grid_impl::kNumVariants] = {};
     hipFunction_t op[grid_impl::kNumOps] = {};                    // see kOpId
-    hipFunction_t team_op[grid_impl::kNumOps] = {};   // their forms with one lane per body
+    hipFunction_t team_op[grid_impl::kNumOps] = {};   // their forms with one lane per body,
+    hipFunction_t serial_op[grid_impl::kNumOps] = {}; // and with one lane per problem
     hipFunction_t minv_route[2] = {};   // M^-1 one lane per knot: L^T L, direct
     std::vector<std::pair<int32_t, int>> tuned;   // (largest N, variant), ascending N
     hipModule_t module = nullptr;

@@ -244,15 +244,17 @@ int fused_variant_for(grid_model m, int32_t N)
     if (!m->tuned.empty())
         return m->tuned.back().second;
     // untuned: the three-role kernel while its wavefronts fit one per SIMD of the device (the
-    // lowest-latency form), one lane per body beyond, and from 64 knots per compute unit the
-    // forms with one problem per lane or four lanes (build 5 once it has 128 knots per compute
-    // unit, half a wavefront per SIMD at least). A robot with a long branch keeps the index of
-    // the three-role build up to 4096 knots; kernel_of says what it runs there
-    const int64_t waves = workgroups_pipe(m->topo, N) * pipe_waves(m->topo);
-    if (waves <= 4 * (int64_t)m->compute_units)
+    // lowest-latency form), then build 0 while its fit (it has fewer: chain7 at 1024 knots 6.6 us,
+    // build 4 7.0, build 1 9.6; quad12 at 512 4.3 / 4.5 / 5.9), the batch kernels beyond (indices
+    // 1, 6 and 5: kernel_of says which). A robot with a long branch keeps the index of the
+    // three-role build up to 4096 knots
+    const int64_t simds = 4 * (int64_t)m->compute_units;
+    if (workgroups_pipe(m->topo, N) * pipe_waves(m->topo) <= simds)
         return kVariantPipe;
     if (long_branch(m->topo))
         return N <= 4096 ? kVariantPipe : kVariantSerial4;
+    if (workgroups_quad(m->topo, N) * m->topo.waves <= simds)
+        return kVariantQuad;
     if (N >= 128 * (int64_t)m->compute_units)
         return kVariantSerial;
     if (N >= 64 * (int64_t)m->compute_units)
@@ -263,15 +265,25 @@ int fused_variant_for(grid_model m, int32_t N)
 // The build whose kernel runs a batch of N knots under the index `variant`
 int kernel_of(grid_model m, int variant, int32_t N)
 {
-    if (variant > kVariantTeam && variant < kVariantPipe)
-        return kVariantTeam;
-    if (!long_branch(m->topo))
+    if (long_branch(m->topo)) {
+        // a long branch: a lane does not hold it, and the three-role kernel gives it a workgroup
+        return variant == kVariantPipe && N <= kPipeLongKnots ? kVariantPipe : kVariantTeam;
+    }
+    switch (variant) {
+    case kVariantQuad:
+    case kVariantPipe:
         return variant;
-    // a long branch: one lane per knot does not fit the registers, and the three-role kernel
-    // holds one such problem per workgroup
-    if (variant == kVariantPipe)
-        return N <= kPipeLongKnots ? kVariantPipe : kVariantTeam;
-    return kVariantTeam;
+    case kVariantSerial:
+    case kVariantSerial2:
+        return kVariantSerial;
+    default:
+        // One lane per body while its wavefronts are at most two per SIMD; beyond, one lane per
+        // problem, which issues a third of the instructions but takes as long for 64 knots as for
+        // 65536 (chain7 at 16384 knots, 1.8 wavefronts per SIMD: 14.7 and 17.3 us, at 32768 25.4
+        // and 18.7; quad12 at 8192, 1.6 per SIMD: 8.9 both, at 16384 14.5 and 10.2)
+        return workgroups_team(m->topo, N) <= 8 * (int64_t)m->compute_units ? kVariantTeam
+                                                                            : kVariantSerial;
+    }
 }
 
 grid_status launch_fused_variant(grid_model m, int variant, int32_t N, const float* q,
@@ -296,8 +308,7 @@ grid_status launch_fused_variant(grid_model m, int variant, int32_t N, const flo
         blocks = workgroups_team(m->topo, N);
         break;
     default:
-        blocks = workgroups_serial(m->topo, N, variant == kVariantSerial ? 64
-                                               : variant == kVariantSerial2 ? 32 : 16);
+        blocks = workgroups_serial(m->topo, N);
     }
     return launch(m->fused_variant[variant], (unsigned)blocks, threads, N, nullptr, q, qd, tau,
                   qdd, Minv, dq, dqd, stream);
@@ -586,7 +597,7 @@ grid_status grid_model_create(const grid_model_desc* desc, int32_t device, uint3
                                            "grid_stage_drnea", "grid_stage_fdgrad"};
     static const char* const kVariants[kNumVariants] = {
         "grid_fdgrad_quad", "grid_fdgrad_team", nullptr, nullptr,
-        "grid_fdgrad_pipe", "grid_fdgrad_serial", "grid_fdgrad_serial4", "grid_fdgrad_serial2"};
+        "grid_fdgrad_pipe", "grid_fdgrad_serial", nullptr, nullptr};
     m->compute_units = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
     hipError_t e = hipModuleLoadData(&m->module, code.data());
     for (int k = 0; k < kNumVariants && e == hipSuccess; ++k)
@@ -603,6 +614,11 @@ grid_status grid_model_create(const grid_model_desc* desc, int32_t device, uint3
     for (int k = 0; k < kNumOps && e == hipSuccess; ++k)
         if (kTeamOps[k])
             e = hipModuleGetFunction(&m->team_op[k], m->module, kTeamOps[k]);
+    static const char* const kSerialOps[kNumOps] = {nullptr, "grid_serial_fd", "grid_serial_minv",
+                                                    "grid_serial_idgrad", "grid_serial_vjp"};
+    for (int k = 0; k < kNumOps && e == hipSuccess; ++k)
+        if (kSerialOps[k] && !long_branch(m->topo))
+            e = hipModuleGetFunction(&m->serial_op[k], m->module, kSerialOps[k]);
     for (int k = 0; k < 5 && e == hipSuccess; ++k)
         e = hipModuleGetFunction(&m->stage[k], m->module, kStages[k]);
     static const char* const kMinvRoutes[2] = {"grid_minv_serial", "grid_minv_direct"};
@@ -706,14 +722,21 @@ static grid_status launch_op(grid_model m, int op, int32_t N, const float* q, co
     void* params[] = {&a};
     const int64_t blocks = workgroups_op(m->topo, N, op);
     const int waves = op == kOpIdGrad ? m->topo.waves : 1;
-    // One lane per body beyond two wavefronts per SIMD of the quad layout, whose quads repeat the
-    // shared sweeps: at two the forms are level (chain7 FD at 4096 knots 6.1 us both, dID at 2048
-    // 6.9 and 7.3), at four the quad layout takes 1.5 times as long (FD at 8192 9.5 and 6.4, dID
-    // at 4096 11.9 and 7.9; quad12 FD at 4096 4.5 and 3.7). A long branch takes it at every size.
-    if (m->team_op[op] &&
-        (long_branch(m->topo) || blocks * waves > 8 * (int64_t)m->compute_units)) {
-        HIP_TRY(hipModuleLaunchKernel(m->team_op[op], (unsigned)workgroups_team(m->topo, N), 1, 1,
-                                      64u, 1, 1, 0, (hipStream_t)stream, params, nullptr));
+    // The quad layout's quads repeat the shared sweeps: beyond two wavefronts of it per SIMD the
+    // batch forms take over. FD and M^-1 then run one lane per problem (chain7 FD at 4096 knots, two
+    // per SIMD: 6.1 us, 5.4 in that form, M^-1 4.2 and 4.7, at 8192 6.0 and 4.8). dID and the VJP
+    // first run one lane per body (chain7 dID at 4096 knots, four per SIMD: 11.9 and 7.9; 10.5 with
+    // one lane per problem), up to one and a half wavefronts of that per SIMD (at 32768 18.8 and
+    // 12.0; quad12 at 8192, 1.6 per SIMD: dID 6.6 both, VJP 5.6 and 4.6). A long branch runs one
+    // lane per body at every size (humanoid30 at 16 knots: FD 9.6 us in the quad layout, 8.6).
+    const int64_t cu = m->compute_units;
+    if (m->team_op[op] && (long_branch(m->topo) || blocks * waves > 8 * cu)) {
+        const int64_t team = workgroups_team(m->topo, N);
+        const bool one_lane = m->serial_op[op] && (op == kOpFd || op == kOpMinv || team > 6 * cu);
+        HIP_TRY(hipModuleLaunchKernel(
+            one_lane ? m->serial_op[op] : m->team_op[op],
+            (unsigned)(one_lane ? workgroups_serial(m->topo, N) : team), 1, 1, 64u, 1, 1, 0,
+            (hipStream_t)stream, params, nullptr));
         return GRID_OK;
     }
     HIP_TRY(hipModuleLaunchKernel(m->op[op], (unsigned)blocks, 1, 1, 64u * (unsigned)waves, 1, 1, 0,
@@ -757,7 +780,7 @@ grid_status grid_minv_route(grid_model m, int32_t N, const float* q, float* Minv
         return fail(GRID_EINVAL, "a data pointer is NULL");
     HIP_TRY(hipSetDevice(m->device));
     return launch(m->minv_route[route == GRID_MINV_LANE_DIRECT ? 1 : 0],
-                  (unsigned)workgroups_serial(m->topo, N, 64), 64u, N, nullptr, q, nullptr,
+                  (unsigned)workgroups_serial(m->topo, N), 64u, N, nullptr, q, nullptr,
                   nullptr, nullptr, Minv, nullptr, nullptr, (hipStream_t)stream);
 }
 

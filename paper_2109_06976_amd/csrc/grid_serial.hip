@@ -1,25 +1,24 @@
-// Fused kernel with one lane per (knot, branch) problem (gfx950): grid_fdgrad_serial.
+// One lane per (knot, branch) problem (gfx950): grid_fdgrad_serial, the batch forms of FD, M^-1,
+// dID and the adjoint VJP, and M^-1 alone by two routes.
 //
 // Every lane of a wavefront works on the same branch of the same robot for a different knot,
 // so all model constants are instruction literals, nothing crosses lanes, and no work is
 // repeated: the fewest instructions per knot of all the builds (the throughput form; its
-// latency is one lane's whole chain). Per problem, float32 (Sec. IV-B):
-//   1. X_i = (E_i, r_i), E_i = E_z(q_i) E_T,i (revolute), or E_i = E_T,i and
-//      r_i = r_T,i + q_i E_T,i^T e_z (prismatic)
-//   2. RNEA(q, qd, 0): v_i, a_i, gamma_i = I_i v_i, f_i, accumulated inward; c_i = S^T f_i
-//   3. M by composite rigid bodies: I^c_i = I_i + sum over children of X^T I^c X, kept as
-//      (mass, first moment, rotational inertia about the origin); M_ii = S^T I^c_i S and
-//      M_ki = S^T (X^T ... X^T I^c_i S) for the ancestors k of i
-//   4. M = L^T L along ancestor paths, M^-1 by B solves, qdd = M^-1 (tau - c)
-//   5. RNEA at qdd as the increment over step 2 (Da_i, Df_i)
-//   6. for each joint j the columns d/dq_j and d/dqd_j together: Algorithm 1 forward over
-//      the subtree of j, the backward pass over the subtree and the ancestors of j, and
-//      dqdd/du_j = -M^-1 dtau/du_j by the two triangular solves
+// latency is one lane's whole chain). Per problem, float32 (Sec. IV-B), in the formulation of
+// grid_axes.hip:
+//   1. outward: axes, velocities, accelerations at qdd = 0, forces, inertias
+//   2. inward: M by the subtrees' inertias and the bias forces; M = L^T L along ancestor paths,
+//      qdd = M^-1 (tau - c), M^-1 by B solves
+//   3. outward: accelerations at qdd
+//   4. inward: the derivatives from the subtrees' inertias, momenta and forces, each column moved
+//      up its ancestor path; dqdd/du_j = -M^-1 dtau/du_j by the two triangular solves
 //
-// Transform of a rigid-body inertia (m, h, Ibar) of frame i into its parent frame, X = (E, r):
-//   m' = m, h' = E^T h + m r,
-//   Ibar' = E^T Ibar E + 2 (r . h~) 1 - r h~^T - h~ r^T + m (|r|^2 1 - r r^T),  h~ = E^T h
-// (from X^T I X written out with a x b x = b a^T - (a . b) 1).
+// 65536 knots of chain7 are one wavefront per SIMD: bound by issue (7,150 VALU instructions, 11.9
+// us) and by its stores, which do not overlap with it, since all wavefronts run in step (9 us at
+// the rate of a copy). 37.1 us per launch with a derivative sweep per column (15,452
+// instructions), 20.0 here; quad12 44.7 and 29.7 (writes at 4.3 TB/s), at 16384 knots 19.7 and
+// 10.2. FD / M^-1 / dID / VJP of chain7 at 32768 knots 13 / 11 / 19 / 19 us with one lane per body,
+// 5.6 / 5.5 / 12.0 / 14.3 here.
 
 namespace grids {
 
@@ -34,7 +33,7 @@ using grid::x_mv;
 using grid::xt_fv;
 
 template <class S>
-__device__ __forceinline__ bool in_subtree(int i, int j)   // i == j or j a strict ancestor of i
+__device__ __forceinline__ constexpr bool in_subtree(int i, int j)   // i == j or j an ancestor
 {
     return i == j || ((S::anc[i] >> j) & 1ull);
 }
@@ -172,78 +171,9 @@ __device__ __forceinline__ void serial_mass_factor(const float (&E)[I::S::B][9],
     gridq::ltl_factor<S>(Lf, dinv);
 }
 
-template <int B>
-__device__ __forceinline__ void pick6(const float (&arr)[B][6], int j, float (&out)[6])
-{
-#pragma unroll
-    for (int k = 0; k < 6; ++k)
-        out[k] = arr[0][k];
-#pragma unroll
-    for (int i = 1; i < B; ++i)
-#pragma unroll
-        for (int k = 0; k < 6; ++k)
-            out[k] = (i == j) ? arr[i][k] : out[k];
-}
-
-// The K knots of a wavefront own one contiguous block of each output array when their branch
-// is the whole robot (N == B). Lane-per-knot stores of one element each hit 64 addresses
-// N^2 floats apart, so for small robots the outputs are staged in LDS (two [K][N][N] arrays)
-// and written out by the wavefront as contiguous 16-byte stores.
-template <int B, int N, int K>
-struct SerialStage {
-    static constexpr bool on = N == B && 2 * K * N * N * 4 <= 32 * 1024;
-    static constexpr int floats = on ? K * N * N : 4;
-};
-
-// A branch that is not the whole robot (N > B) owns B rows of each knot's blocks, scattered
-// over the robot's numbering: lane-per-knot stores of one element each would again hit 64
-// addresses N^2 floats apart. Its rows are staged instead ([K][B][N], local row i, robot
-// column) while two such tiles fit 32 KB, and the wavefront writes each row's N floats with
-// consecutive lanes on consecutive elements, zeros in the other branches' columns included.
-// With four lanes per knot (whose stores already put four columns side by side) the dispatch
-// stages only when every branch of the robot fits: on a robot whose long branch does not,
-// staging its short ones made the launch slower.
-template <int B, int N, int K, bool kAllowed = true>
-struct SerialRows {
-    static constexpr bool fits = N > B && 2 * K * B * N * 4 <= 32 * 1024;
-    static constexpr bool on = kAllowed && fits;
-    static constexpr int floats = on ? K * B * N : 4;
-};
-
-template <class I, int L>
-constexpr bool serial_rows_fit()
-{
-    return SerialRows<I::S::B, I::N, 64 / L>::fits;
-}
-
-// floats of LDS one branch's staging takes (its two tiles); the dispatch of a robot allocates
-// the largest over its branches once, so that the branches of one kernel share it
-template <class I, int L, bool kRows>
-constexpr int serial_stage_floats()
-{
-    using ST = SerialStage<I::S::B, I::N, 64 / L>;
-    using SR = SerialRows<I::S::B, I::N, 64 / L, kRows>;
-    return 2 * (ST::on ? ST::floats : SR::floats);
-}
-
 constexpr int cmax(int a) { return a; }
 template <class... T>
 constexpr int cmax(int a, int b, T... rest) { return cmax(a > b ? a : b, rest...); }
-
-// write the staged rows of the wavefront's nv valid knots: element (knot, local row i, column c)
-// goes to row body(i) of that knot's block; `dst` is the block of the wavefront's first knot
-template <class I>
-__device__ __forceinline__ void flush_rows(float* dst, const float* tile, int nv, int lane)
-{
-    constexpr int B = I::S::B;
-    constexpr int N = I::N;
-    for (int e = lane; e < nv * B * N; e += 64) {
-        const int kl = e / (B * N), rem = e - kl * (B * N);
-        const int i = rem / N, c2 = rem - i * N;
-        const float v = I::contains(c2) ? tile[e] : 0.0f;
-        dst[(long)kl * N * N + (long)I::body_of(i) * N + c2] = v;
-    }
-}
 
 // the workgroup is one wavefront: ordering its own LDS traffic needs no workgroup barrier
 __device__ __forceinline__ void wave_lds_sync()
@@ -253,368 +183,534 @@ __device__ __forceinline__ void wave_lds_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// copy `cnt` floats from LDS to global memory: 16 bytes per lane and step when the destination
-// is 16-byte aligned (the staging array is; a wavefront's block starts at a multiple of 64 N
-// floats, so only the caller's base address decides), else one float per lane and step
-__device__ __forceinline__ void flush_stage(float* dst, const float* src, int cnt, int lane)
+template <int K>
+struct Int {
+    static constexpr int v = K;
+};
+
+// f(Int<0>), f(Int<1>), .. f(Int<N - 1>)
+template <int N, int K = 0, class F>
+__device__ __forceinline__ void static_for(const F& f)
 {
-    int done = 0;
-    if ((reinterpret_cast<unsigned long>(dst) & 15ul) == 0) {
-        const int n4 = cnt / 4;
-        for (int e = lane; e < n4; e += 64)
-            reinterpret_cast<float4*>(dst)[e] = reinterpret_cast<const float4*>(src)[e];
-        done = 4 * n4;
+    if constexpr (K < N) {
+        f(Int<K>{});
+        static_for<N, K + 1>(f);
     }
-    for (int e = done + lane; e < cnt; e += 64)
-        dst[e] = src[e];
 }
 
-// L lanes per knot (1: build 5; 4: build 6; 2: build 7). Every lane of a knot runs steps 1-5; the columns
-// of M^-1 and the joints j of step 6 are dealt out among them (lane h takes h, h + L, ...), so
-// a wavefront holds 64 / L knots: L times the wavefronts of build 5 for the same batch, at the
-// cost of repeating steps 1-5 L times. The lanes of a knot are adjacent.
-// `pool` is the dispatch's LDS array of at least serial_stage_floats<I, L, kRows>() floats;
-// kRows allows the row staging of a branch smaller than the robot.
-template <class I, int L, bool kRows>
-__device__ __forceinline__ void run_serial(const grid::Args& A, int block, float* pool)
+// Outputs. A lane that wrote the entries of its own knot would put 64 addresses N^2 floats apart
+// into each store, so the B x B block of a matrix is staged in LDS ([knot][B][B]: the lane stride
+// B^2 is odd for odd B, no bank conflicts) and the wavefront writes its knots' contiguous blocks
+// with 16-byte stores when the branch is the whole robot, else its B rows of N floats per knot,
+// zeros in the other branches' columns included.
+
+// copy the [nv][N][N] floats of the wavefront's valid knots: 16 bytes per lane and step (global
+// memory takes them at any 4-byte aligned address); several steps in flight, since one at a time
+// waits for LDS and for memory in turn
+template <int N>
+__device__ __forceinline__ void flush_whole(float* dst, const float* src, int nv, int lane)
 {
+    constexpr int STEPS = (64 * N * N / 4 + 63) / 64;
+    const int cnt = nv * N * N, n4 = cnt / 4;
+#pragma unroll
+    for (int s = 0; s < STEPS; ++s) {
+        const int e = s * 64 + lane;
+        if (e < n4) {
+            const float4 v = reinterpret_cast<const float4*>(src)[e];
+            reinterpret_cast<gridv::F4*>(dst)[e] = gridv::F4{v.x, v.y, v.z, v.w};
+        }
+    }
+    if (4 * n4 + lane < cnt)                             // up to three floats left
+        dst[4 * n4 + lane] = src[4 * n4 + lane];
+}
+
+// the branch's rows of a knot as V-float pieces, LPK of them; a lane keeps its place in the knot
+// and strides over the knots, KPI at a time (one address computation per lane)
+template <class I>
+struct RowPieces {
+    static constexpr int B = I::S::B, N = I::N;
+    static constexpr int V = N % 4 == 0 ? 4 : (N % 2 == 0 ? 2 : 1);
+    static constexpr int PPR = N / V;                    // pieces per row
+    static constexpr int LPK = B * PPR;
+    static constexpr int KPI = LPK <= 64 ? 64 / LPK : 0; // 0: a knot takes several steps
+};
+
+// write the blocks of the wavefront's nv valid knots, NM matrices; `d0`, `d1` are the blocks of
+// its first knot
+template <class I, int NM>
+__device__ __forceinline__ void flush_blocks(float* d0, float* d1, const float* t0,
+                                             const float* t1, int nv, int lane)
+{
+    using RP = RowPieces<I>;
+    constexpr int B = RP::B, N = RP::N, V = RP::V;
+    if constexpr (B == N) {
+        flush_whole<N>(d0, t0, nv, lane);
+        if constexpr (NM > 1)
+            flush_whole<N>(d1, t1, nv, lane);
+    } else {
+        constexpr int KPI = RP::KPI > 0 ? RP::KPI : 1;
+        constexpr int TURNS = RP::KPI > 0 ? 1 : (RP::LPK + 63) / 64;
+#pragma unroll
+        for (int turn = 0; turn < TURNS; ++turn) {
+            const int e = turn * 64 + lane;
+            const int kk = RP::KPI > 0 ? lane / RP::LPK : 0, rem = e - kk * RP::LPK;
+            if (RP::KPI > 0 ? kk >= KPI : rem >= RP::LPK)
+                continue;
+            const int i = rem / RP::PPR, c = (rem - i * RP::PPR) * V;
+            bool in[V];
+            int at[V];
+#pragma unroll
+            for (int w = 0; w < V; ++w) {
+                // the local column: the branch's bodies below c (local order follows the robot's)
+                in[w] = I::contains(c + w);
+                at[w] = i * B + (in[w] ? __popcll(I::mask & ((1ull << (c + w)) - 1)) : 0);
+            }
+            const int off = I::body_of(i) * N + c;
+#pragma unroll 5
+            for (int k = kk; k < nv; k += KPI) {
+                float x[V], y[V];
+#pragma unroll
+                for (int w = 0; w < V; ++w) {
+                    x[w] = in[w] ? t0[k * B * B + at[w]] : 0.0f;
+                    y[w] = NM > 1 && in[w] ? t1[k * B * B + at[w]] : 0.0f;
+                }
+                gridv::store<V>(d0 + k * N * N + off, x);
+                if constexpr (NM > 1)
+                    gridv::store<V>(d1 + k * N * N + off, y);
+            }
+        }
+    }
+}
+
+// LDS: the tiles of one matrix, or of two at a time where they are small (the addresses are then
+// computed once), and what a lane parks while it factors M and writes M^-1: 16 floats for every
+// body but the first. Without parking a branch of 7 bodies holds 330 floats there, which move
+// through the accumulation registers and scratch memory (65536 knots 21.4 us, 20.2 with it); one
+// of 3 bodies has room (7.0 us at 128 knots, 7.7 with it)
+template <class I, int OP>
+struct SerialLds {
+    static constexpr int B = I::S::B;
+    static constexpr bool kPark = B > 4 && (OP == gridv::kFdGrad || OP == gridv::kVjp);
+    static constexpr bool kTiles = OP != gridv::kFd && OP != gridv::kVjp;
+    static constexpr int NT = !kTiles ? 0 : (B > 4 || OP == gridv::kMinv ? 1 : 2);
+    static constexpr int tile = 64 * B * B;
+    static constexpr int floats = NT * tile + (kPark ? 16 * 64 * (B - 1) : 0) + 4;
+};
+template <class I, int OP>
+constexpr int serial_floats()
+{
+    return SerialLds<I, OP>::floats;
+}
+
+// x <- (L^T L)^-1 x, entry k of x zero unless bit k of MASK is set (MASK holds the ancestors of
+// its bodies); entries up to LAST only
+template <class S, unsigned long long MASK, int LAST>
+__device__ __forceinline__ void solve_masked(const float (&L)[S::B][S::B],
+                                             const float (&dinv)[S::B], float (&x)[S::B])
+{
+    constexpr int B = S::B;
+    static_for<B>([&](auto kk) {
+        constexpr int k = B - 1 - decltype(kk)::v;
+        if constexpr ((MASK >> k) & 1ull) {
+            x[k] *= dinv[k];
+#pragma unroll
+            for (int a = 0; a < k; ++a)
+                if ((S::anc[k] >> a) & 1ull)
+                    x[a] -= L[k][a] * x[k];
+        }
+    });
+    static_for<LAST + 1>([&](auto kk) {
+        constexpr int k = decltype(kk)::v;
+        float t = ((MASK >> k) & 1ull) ? x[k] : 0.0f;
+#pragma unroll
+        for (int a = 0; a < k; ++a)
+            if ((S::anc[k] >> a) & 1ull)
+                t -= L[k][a] * x[a];
+        x[k] = t * dinv[k];
+    });
+}
+
+// j, its ancestors and its subtree
+template <class S>
+constexpr unsigned long long relatives(int j)
+{
+    unsigned long long m = S::anc[j] | (1ull << j);
+    for (int i = 0; i < S::B; ++i)
+        if ((S::anc[i] >> j) & 1ull)
+            m |= 1ull << i;
+    return m;
+}
+
+// One lane per (knot, branch) problem. Along the first body's axes (grid_axes.hip) its rotation is
+// the identity and its joint axis e_z, so that what concerns it folds.
+template <class I, int OP>
+__device__ __forceinline__ void run_serial(const gridv::BatchArgs& A, int block, float* pool)
+{
+    using namespace gridv;
     using S = typename I::S;
     constexpr int B = S::B;
     constexpr int N = I::N;
-    constexpr int K = 64 / L;                        // knots per wavefront
-    using ST = SerialStage<B, N, K>;
-    using SR = SerialRows<B, N, K, kRows>;
-    float* const s_stage[2] = {pool, pool + serial_stage_floats<I, L, kRows>() / 2};
+    using Y = SerialLds<I, OP>;
+    constexpr bool kVel = OP != kMinv;
+    constexpr bool kMass = OP != kIdGrad;
+    constexpr bool kBias = OP == kFdGrad || OP == kFd;
+    constexpr bool kDer = OP != kFd && OP != kMinv;
+    constexpr bool kPark = Y::kPark;
     const int lane = (int)threadIdx.x;
-    const int h = lane % L;                          // this lane's share of the columns
-    const int kl = lane / L;                         // the knot within the wavefront
-    const int kraw = block * K + kl;
+    const int kraw = block * 64 + lane;
     const bool valid = kraw < A.nknots;
-    const int knot = valid ? kraw : A.nknots - 1;   // tail lanes recompute the last knot
-    const float* C = I::consts();                   // literals: folded into the code
+    const int knot = valid ? kraw : A.nknots - 1;       // tail lanes recompute the last knot
+    const int nv = min(64, A.nknots - block * 64);
+    const float* C = I::consts();                       // literals: folded into the code
     const long vbase = (long)knot * N;
-    const long mbase = (long)knot * N * N;
+    const long mb = (long)block * 64 * N * N;           // the wavefront's first output block
+    float* const mine = pool + lane * B * B;
+    float4* const park = reinterpret_cast<float4*>(pool + Y::NT * Y::tile) + lane;
+    const auto zero3 = V3{0.0f, 0.0f, 0.0f};
 
-    // ------------------------------------------------------------ 1. transforms
-    float qd[B], E[B][9], R[B][3];
-#pragma unroll
-    for (int i = 0; i < B; ++i) {
-        const long o = vbase + I::body[i];
-        qd[i] = A.qd[o];
-        serial_transform<I>(i, A.q[o], E[i], R[i]);
-    }
-    const float a0[6] = {0.0f, 0.0f, 0.0f, I::a0()[0], I::a0()[1], I::a0()[2]};   // -g
-    const float zero6[6] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+    float qd[B], uu[B];
+    V3 z[B], r[B], h[B];
+    Sym P[B];
+    Six vl[B], psd[B], al[B];                           // vl, al: the parent's, at this origin
+    const auto pri = [](int i) { return prismatic<I>(i); };
+    const auto add_S = [&](int i, Six y, float s) {
+        if (pri(i))
+            return Six{y.a, y.l + z[i] * s};
+        return Six{y.a + z[i] * s, y.l};
+    };
+    const auto cross_S = [&](int i, Six x) {
+        if (pri(i))
+            return Six{zero3, cross(x.a, z[i])};
+        return Six{cross(x.a, z[i]), cross(x.l, z[i])};
+    };
+    const auto dot_S = [&](int i, Six f) { return pri(i) ? dot(z[i], f.l) : dot(z[i], f.a); };
+    const auto mass_of = [&](int i) { return C[i * kConstStride + 21]; };
 
-    // ------------------------------------------------------------ 2. RNEA(q, qd, 0)
-    float v[B][6], gam[B][6], F[B][6], xa[B][6];   // xa_i = X_i a_lambda(i)
+    // ------------------------------------------------------------ outward: axes, velocities,
+    // the parents' accelerations (at qdd = 0 for dFD and FD, else at the given qdd), inertias
+    Six F[B];
     {
-        float a[B][6];
-#pragma unroll
-        for (int i = 0; i < B; ++i) {
-            const int p = S::parent[i];
+        Mat R[B];
+        Six a[B], v[B];
+        static_for<B>([&](auto ii) {
+            constexpr int i = decltype(ii)::v;
+            constexpr int p = S::parent[i];
             const float* c = C + i * kConstStride;
-            x_mv(E[i], R[i], p < 0 ? zero6 : v[p < 0 ? 0 : p], v[i]);
-            x_mv(E[i], R[i], p < 0 ? a0 : a[p < 0 ? 0 : p], xa[i]);
-            v[i][s_index(prismatic<I>(i))] += qd[i];
-            float vxs[6], Ia[6], w[6];
-            cross_S(prismatic<I>(i), v[i], vxs);
-#pragma unroll
-            for (int k = 0; k < 6; ++k)
-                a[i][k] = xa[i][k] + vxs[k] * qd[i];
-            inertia_mv(c, v[i], gam[i]);
-            inertia_mv(c, a[i], Ia);
-            crf_mv(v[i], gam[i], w);
-#pragma unroll
-            for (int k = 0; k < 6; ++k)
-                F[i][k] = Ia[k] + w[k];
-        }
-#pragma unroll
-        for (int i = B - 1; i >= 0; --i) {
-            const int p = S::parent[i];
-            if (p >= 0) {
-                float y[6];
-                xt_fv(E[i], R[i], F[i], y);
-#pragma unroll
-                for (int k = 0; k < 6; ++k)
-                    F[p][k] += y[k];
+            const long o = vbase + I::body[i];
+            const float qi = A.q[o];
+            qd[i] = kVel ? A.qd[o] : 0.0f;
+            uu[i] = kVel ? A.u[o] : 0.0f;
+            const V3 e0{c[0], c[1], c[2]}, e1{c[3], c[4], c[5]}, e2{c[6], c[7], c[8]};
+            float sn = 0.0f, co = 1.0f;
+            if (!pri(i)) {
+                const float rev = __builtin_amdgcn_fractf(qi * 0.159154943091895336f);
+                sn = __builtin_amdgcn_sinf(rev);
+                co = __builtin_amdgcn_cosf(rev);
             }
-        }
-    }
-
-    // ------------------------------------------------------------ 3. M by composite bodies
-    float Lf[B][B], dinv[B];
-    serial_mass_factor<I>(E, R, Lf, dinv);
-
-    // ------------------------------------------------------------ 4. M^-1 and qdd
-    if (valid && L == 1) {
-#pragma unroll
-        for (int jm = 0; jm < B; ++jm) {
-            float mc[B];
-#pragma unroll
-            for (int i = 0; i < B; ++i)
-                mc[i] = (i == jm) ? 1.0f : 0.0f;
-            gridq::ltl_solve<S>(Lf, dinv, mc);
-            // entries (i, jm), i <= jm, written to both mirrored positions: exactly symmetric
-#pragma unroll
-            for (int i = 0; i <= jm; ++i) {
-                if constexpr (ST::on) {
-                    s_stage[0][kl * N * N + I::body[i] * N + I::body[jm]] = mc[i];
-                    s_stage[0][kl * N * N + I::body[jm] * N + I::body[i]] = mc[i];
-                } else if constexpr (SR::on) {
-                    s_stage[0][kl * B * N + i * N + I::body[jm]] = mc[i];
-                    s_stage[0][kl * B * N + jm * N + I::body[i]] = mc[i];
-                } else {
-                    A.Minv[mbase + (long)I::body[i] * N + I::body[jm]] = mc[i];
-                    A.Minv[mbase + (long)I::body[jm] * N + I::body[i]] = mc[i];
+            const Mat X = pri(i) ? Mat{e0, e1, e2} : Mat{e0 * co + e1 * sn, e1 * co - e0 * sn, e2};
+            // second moment of the body: tr(Ibar) / 2 - Ibar
+            const double tr = 0.5 * ((double)c[12] + c[13] + c[14]);
+            const Sym PT{(float)(tr - c[12]), (float)(tr - c[13]), (float)(tr - c[14]),
+                         -c[15], -c[16], -c[17]};
+            const V3 hT{c[18], c[19], c[20]};
+            if constexpr (p < 0) {
+                z[i] = V3{0.0f, 0.0f, 1.0f};
+                r[i] = zero3;
+                P[i] = PT;
+                h[i] = hT;
+                const V3 g{I::a0()[0], I::a0()[1], I::a0()[2]};
+                al[i] = Six{zero3, tmul(X, g)};
+                vl[i] = Six{zero3, zero3};
+                psd[i] = vl[i];
+                v[i] = pri(i) ? Six{zero3, {0.0f, 0.0f, qd[i]}} : Six{{0.0f, 0.0f, qd[i]}, zero3};
+                a[i] = al[i];
+                if constexpr (!kBias) {
+                    if (pri(i))
+                        a[i].l.z += uu[i];
+                    else
+                        a[i].a.z = uu[i];
                 }
-            }
-        }
-    } else if (valid) {
-        // the knot's lanes share the columns of M^-1
-#pragma unroll 1
-        for (int jm = h; jm < B; jm += L) {
-            float mc[B];
-#pragma unroll
-            for (int i = 0; i < B; ++i)
-                mc[i] = (i == jm) ? 1.0f : 0.0f;
-            gridq::ltl_solve<S>(Lf, dinv, mc);
-            const int gm = I::body_of(jm);
-#pragma unroll
-            for (int i = 0; i < B; ++i) {
-                if (i > jm)
-                    continue;
-                if constexpr (ST::on) {
-                    s_stage[0][kl * N * N + I::body[i] * N + gm] = mc[i];
-                    s_stage[0][kl * N * N + gm * N + I::body[i]] = mc[i];
-                } else if constexpr (SR::on) {
-                    s_stage[0][kl * B * N + i * N + gm] = mc[i];
-                    s_stage[0][kl * B * N + jm * N + I::body[i]] = mc[i];
-                } else {
-                    A.Minv[mbase + (long)I::body[i] * N + gm] = mc[i];
-                    A.Minv[mbase + (long)gm * N + I::body[i]] = mc[i];
-                }
-            }
-        }
-    }
-    float x[B];
-#pragma unroll
-    for (int i = 0; i < B; ++i)
-        x[i] = A.tau[vbase + I::body[i]] - F[i][s_index(prismatic<I>(i))];
-    gridq::ltl_solve<S>(Lf, dinv, x);
-    // the wavefront's valid knots (its first knot is block * K) and their output blocks
-    const int nv = min(K, A.nknots - block * K);
-    const long kb = (long)block * K;
-    if constexpr (ST::on) {
-        if (valid && h == 0) {
-#pragma unroll
-            for (int i = 0; i < B; ++i)
-                s_stage[1][kl * N + I::body[i]] = x[i];
-        }
-        wave_lds_sync();                      // M^-1 and qdd staged
-        flush_stage(A.Minv + kb * N * N, s_stage[0], nv * N * N, lane);
-        flush_stage(A.qdd + kb * N, s_stage[1], nv * N, lane);
-        wave_lds_sync();                      // staging free for the derivative columns
-    } else {
-        if (valid && h == 0) {
-#pragma unroll
-            for (int i = 0; i < B; ++i)
-                A.qdd[vbase + I::body[i]] = x[i];
-        }
-        if constexpr (SR::on) {
-            wave_lds_sync();                  // the rows of M^-1 staged
-            flush_rows<I>(A.Minv + kb * N * N, s_stage[0], nv, lane);
-            wave_lds_sync();                  // staging free for the derivative columns
-        }
-    }
-
-    // ------------------------------------------------------------ 5. RNEA at qdd
-    {
-        float Da[B][6], Df[B][6];
-#pragma unroll
-        for (int i = 0; i < B; ++i) {
-            const int p = S::parent[i];
-            const float* c = C + i * kConstStride;
-            if (p >= 0) {
-                x_mv(E[i], R[i], Da[p < 0 ? 0 : p], Da[i]);
-#pragma unroll
-                for (int k = 0; k < 6; ++k)
-                    xa[i][k] += Da[i][k];
             } else {
-#pragma unroll
-                for (int k = 0; k < 6; ++k)
-                    Da[i][k] = 0.0f;
+                const V3 rT{c[9], c[10], c[11]};
+                if constexpr (S::parent[p] < 0) {       // the first body's axes
+                    R[i] = X;
+                    r[i] = rT;
+                } else {
+                    R[i] = Mat{mul(R[p], X.c0), mul(R[p], X.c1), mul(R[p], X.c2)};
+                    r[i] = mul(R[p], rT);
+                }
+                z[i] = R[i].c2;
+                if (pri(i))
+                    r[i] = r[i] + z[i] * qi;
+                P[i] = turn(R[i], PT);
+                h[i] = mul(R[i], hT);
+                vl[i] = Six{v[p].a, v[p].l + cross(v[p].a, r[i])};
+                psd[i] = cross_S(i, vl[i]);
+                v[i] = add_S(i, vl[i], qd[i]);
+                al[i] = Six{a[p].a, a[p].l + cross(a[p].a, r[i])};
+                a[i] = Six{al[i].a + psd[i].a * qd[i], al[i].l + psd[i].l * qd[i]};
+                if constexpr (!kBias)
+                    a[i] = add_S(i, a[i], uu[i]);
+                if constexpr (kPark) {
+                    park[64 * (4 * i - 4)] = float4{P[i].xx, P[i].yy, P[i].zz, P[i].xy};
+                    park[64 * (4 * i - 3)] = float4{P[i].xz, P[i].yz, h[i].x, h[i].y};
+                    park[64 * (4 * i - 2)] = float4{h[i].z, psd[i].a.x, psd[i].a.y, psd[i].a.z};
+                    park[64 * (4 * i - 1)] = float4{psd[i].l.x, psd[i].l.y, psd[i].l.z, qd[i]};
+                }
             }
-            Da[i][s_index(prismatic<I>(i))] += x[i];
-            inertia_mv(c, Da[i], Df[i]);
-        }
-#pragma unroll
-        for (int i = B - 1; i >= 0; --i) {
-            const int p = S::parent[i];
-            if (p >= 0) {
-                float y[6];
-                xt_fv(E[i], R[i], Df[i], y);
-#pragma unroll
-                for (int k = 0; k < 6; ++k)
-                    Df[p][k] += y[k];
+            if constexpr (kBias) {                      // f = I a + v x* (I v)
+                const Sym J = second_to_inertia(P[i]);
+                const Six Ia = inertia(mass_of(i), h[i], J, a[i]);
+                const Six Iv = inertia(mass_of(i), h[i], J, v[i]);
+                F[i] = Six{Ia.a + cross(v[i].a, Iv.a) + cross(v[i].l, Iv.l),
+                           Ia.l + cross(v[i].a, Iv.l)};
             }
-#pragma unroll
-            for (int k = 0; k < 6; ++k)
-                F[i][k] += Df[i][k];
-        }
+        });
     }
 
-    // ------------------------------------------------------------ 6. dRNEA and dFD columns
-    // One lane per knot and a branch of up to 8 bodies: the loop is unrolled, so that j is a
-    // constant in each copy (no selects of the joint's quantities, the subtree tests folded;
-    // chain7 at 65536 knots 44.6 -> 37.1 us); otherwise one copy of the body, j at run time.
-    constexpr int kUnrollJ = (L == 1 && B <= 8) ? B : 1;
-#pragma unroll kUnrollJ
-    for (int j = h; j < B; j += L) {
-        // sources of joint j: u = q: dv += v_j x S, da += (X_j a_lambda(j)) x S,
-        // backward += X_j^T (S x* f_j); u = qd: dv += S, da += v_j x S
-        float vj[6], xaj[6], Fj[6], Ej[9], rj[3];
-        pick6<B>(v, j, vj);
-        pick6<B>(xa, j, xaj);
-        pick6<B>(F, j, Fj);
+    // ------------------------------------------------------------ inward: M by the subtrees'
+    // inertias, the bias forces, the factor
+    float Lf[B][B], dinv[B], x[B];
+    if constexpr (kMass) {
+        Sym Pc[B];
+        V3 hc[B];
 #pragma unroll
-        for (int k = 0; k < 9; ++k)
-            Ej[k] = E[0][k];
-#pragma unroll
-        for (int k = 0; k < 3; ++k)
-            rj[k] = R[0][k];
-#pragma unroll
-        for (int i = 1; i < B; ++i) {
-#pragma unroll
-            for (int k = 0; k < 9; ++k)
-                Ej[k] = (i == j) ? E[i][k] : Ej[k];
-#pragma unroll
-            for (int k = 0; k < 3; ++k)
-                rj[k] = (i == j) ? R[i][k] : rj[k];
+        for (int i = 0; i < B; ++i) {
+            Pc[i] = P[i];
+            hc[i] = h[i];
         }
-        const bool pj = (I::prism >> j) & 1ull;            // joint j is prismatic
-        float vxs[6], axs[6], srcf[6];
-        cross_S(pj, vj, vxs);
-        cross_S(pj, xaj, axs);
-        {
-            float sf[6];
-            s_crf(pj, Fj, sf);                               // S x* f_j
-            xt_fv(Ej, rj, sf, srcf);
-        }
-        // columns d/dq_j (index 0) and d/dqd_j (index 1), side by side
-        float df[2][B][6];
-        {
-            float dv[2][B][6], da[2][B][6];
+        float mc[B];
 #pragma unroll
-            for (int i = 0; i < B; ++i) {
-                const int p = S::parent[i];
-                const float* c = C + i * kConstStride;
-                if (in_subtree<S>(i, j)) {
-#pragma unroll
-                    for (int u = 0; u < 2; ++u) {
-                        float xdv[6], xda[6];
-                        if (i == j || p < 0) {
-#pragma unroll
-                            for (int k = 0; k < 6; ++k) {
-                                xdv[k] = 0.0f;
-                                xda[k] = 0.0f;
-                            }
-                        } else {
-                            x_mv(E[i], R[i], dv[u][p < 0 ? 0 : p], xdv);
-                            x_mv(E[i], R[i], da[u][p < 0 ? 0 : p], xda);
-                        }
-                        if (i == j) {
-#pragma unroll
-                            for (int k = 0; k < 6; ++k) {
-                                xdv[k] = u == 0 ? vxs[k] : (k == s_index(pj) ? 1.0f : 0.0f);
-                                xda[k] = u == 0 ? axs[k] : vxs[k];
-                            }
-                        }
-                        float dvxs[6];
-                        cross_S(prismatic<I>(i), xdv, dvxs);
-#pragma unroll
-                        for (int k = 0; k < 6; ++k) {
-                            dv[u][i][k] = xdv[k];
-                            da[u][i][k] = xda[k] + dvxs[k] * qd[i];
-                        }
-                        // df_i = I_i da_i + dv_i x* gamma_i + v_i x* (I_i dv_i)
-                        float t1[6], t2[6], t3[6], Idv[6];
-                        inertia_mv(c, da[u][i], t1);
-                        crf_mv(dv[u][i], gam[i], t2);
-                        inertia_mv(c, dv[u][i], Idv);
-                        crf_mv(v[i], Idv, t3);
-#pragma unroll
-                        for (int k = 0; k < 6; ++k)
-                            df[u][i][k] = t1[k] + t2[k] + t3[k];
+        for (int i = 0; i < B; ++i)
+            mc[i] = mass_of(i);
+        static_for<B>([&](auto ii) {
+            constexpr int i = B - 1 - decltype(ii)::v;
+            constexpr int p = S::parent[i];
+            Six f = pri(i) ? Six{cross(hc[i], z[i]), z[i] * mc[i]}
+                           : Six{mul(second_to_inertia(Pc[i]), z[i]), cross(z[i], hc[i])};
+            Lf[i][i] = dot_S(i, f);
+            static_for<i>([&](auto tt) {                // the ancestors, nearest first
+                constexpr int k = i - decltype(tt)::v;  // i, then each ancestor but the root
+                if constexpr (k == i || ((S::anc[i] >> k) & 1ull)) {
+                    constexpr int q = S::parent[k];
+                    if constexpr (q >= 0) {
+                        f.a = f.a + cross(r[k], f.l);
+                        Lf[i][q] = dot_S(q, f);
                     }
+                }
+            });
+            if constexpr (kBias) {
+                x[i] = uu[i] - dot_S(i, F[i]);
+                if constexpr (p >= 0)
+                    F[p] = Six{F[p].a + F[i].a + cross(r[i], F[i].l), F[p].l + F[i].l};
+            }
+            if constexpr (p >= 0) {
+                move_moments(Pc[i], hc[i], mc[i], r[i]);
+                Pc[p] = Sym{Pc[p].xx + Pc[i].xx, Pc[p].yy + Pc[i].yy, Pc[p].zz + Pc[i].zz,
+                            Pc[p].xy + Pc[i].xy, Pc[p].xz + Pc[i].xz, Pc[p].yz + Pc[i].yz};
+                hc[p] = hc[p] + hc[i];
+                mc[p] += mc[i];
+            }
+        });
+        if constexpr (OP == kVjp) {
+#pragma unroll
+            for (int i = 0; i < B; ++i)
+                x[i] = A.u2[vbase + I::body[i]];
+        }
+        gridq::ltl_factor<S>(Lf, dinv);
+        if constexpr (kVel) {
+            gridq::ltl_solve<S>(Lf, dinv, x);           // qdd, or taubar
+            if (valid) {
+                float* out = OP == kVjp ? A.o2 : A.o0;
+#pragma unroll
+                for (int i = 0; i < B; ++i)
+                    out[vbase + I::body[i]] = x[i];
+            }
+        }
+    }
+    if constexpr (OP == kFd)
+        return;
+
+    if constexpr (OP == kFdGrad || OP == kMinv) {
+        // M^-1: entries (i, j), i <= j, to both mirrored positions (exactly symmetric)
+        static_for<B>([&](auto jj) {
+            constexpr int j = decltype(jj)::v;
+            float m[B];
+#pragma unroll
+            for (int i = 0; i < B; ++i)
+                m[i] = (i == j) ? 1.0f : 0.0f;
+            solve_masked<S, S::anc[j] | (1ull << j), j>(Lf, dinv, m);
+#pragma unroll
+            for (int i = 0; i <= j; ++i) {
+                mine[i * B + j] = m[i];
+                mine[j * B + i] = m[i];
+            }
+        });
+        wave_lds_sync();
+        flush_blocks<I, 1>((OP == kMinv ? A.o0 : A.o1) + mb, nullptr, pool, nullptr, nv, lane);
+        if constexpr (OP == kMinv)
+            return;
+        wave_lds_sync();
+        // the parents' accelerations at qdd
+        Six d[B];
+        static_for<B>([&](auto ii) {
+            constexpr int i = decltype(ii)::v;
+            constexpr int p = S::parent[i];
+            if constexpr (p < 0) {
+                d[i] = pri(i) ? Six{zero3, {0.0f, 0.0f, x[i]}} : Six{{0.0f, 0.0f, x[i]}, zero3};
+            } else {
+                d[i] = Six{d[p].a, d[p].l + cross(d[p].a, r[i])};
+                al[i] = Six{al[i].a + d[i].a, al[i].l + d[i].l};
+                d[i] = add_S(i, d[i], x[i]);
+            }
+        });
+    }
+
+    // ------------------------------------------------------------ inward: dtau/dq, dtau/dqd from
+    // the subtrees' inertias, momenta and forces
+    if constexpr (kDer) {
+        float Dq[B][B], Dv[B][B];                       // [column][row]
+        float gq[B], gv[B];                             // VJP: the products with taubar
+        Six pdd[B];
+        Mat K[B];
+        V3 l[B];
+        float mc[B];
+#pragma unroll
+        for (int i = 0; i < B; ++i)
+            mc[i] = mass_of(i);
+        static_for<B>([&](auto ii) {
+            constexpr int i = decltype(ii)::v;
+            if constexpr (kPark && i > 0) {
+                const float4 a = park[64 * (4 * i - 4)], b = park[64 * (4 * i - 3)],
+                             c = park[64 * (4 * i - 2)], d = park[64 * (4 * i - 1)];
+                P[i] = Sym{a.x, a.y, a.z, a.w, b.x, b.y};
+                h[i] = V3{b.z, b.w, c.x};
+                psd[i] = Six{{c.y, c.z, c.w}, {d.x, d.y, d.z}};
+                qd[i] = d.w;
+            }
+            const float qdd = OP == kFdGrad ? x[i] : uu[i];
+            const Six v = add_S(i, vl[i], qd[i]);
+            const Sym J = second_to_inertia(P[i]);
+            K[i] = momentum_moment(v, h[i], P[i]);
+            l[i] = v.l * mass_of(i) + cross(v.a, h[i]);
+            Six a = add_S(i, Six{al[i].a + psd[i].a * qd[i], al[i].l + psd[i].l * qd[i]}, qdd);
+            const Six Ia = inertia(mass_of(i), h[i], J, a), Bv = bmul(K[i], l[i], v.a);
+            F[i] = Six{Ia.a + Bv.a, Ia.l + Bv.l};
+            const Six s = cross_S(i, al[i]);
+            pdd[i] = S::parent[i] < 0 ? s
+                                      : Six{s.a + cross(vl[i].a, psd[i].a),
+                                            s.l + cross(vl[i].a, psd[i].l) + cross(vl[i].l, psd[i].a)};
+            gq[i] = 0.0f;
+            gv[i] = 0.0f;
+        });
+        static_for<B>([&](auto jj) {
+            constexpr int j = B - 1 - decltype(jj)::v;
+            constexpr int p = S::parent[j];
+            const Sym J = second_to_inertia(P[j]);
+            Six f, u, w;
+            V3 b;
+            if (pri(j)) {
+                f = Six{cross(h[j], z[j]), z[j] * mc[j]};
+                b = cross(l[j], z[j]);
+            } else {
+                f = Six{mul(J, z[j]), cross(z[j], h[j])};
+                b = z[j] * (K[j].c0.x + K[j].c1.y + K[j].c2.z) - tmul(K[j], z[j]);
+            }
+            {
+                const Six Ip = inertia(mc[j], h[j], J, pdd[j]);
+                const Six Sf = pri(j) ? Six{cross(z[j], F[j].l), zero3}
+                                      : Six{cross(z[j], F[j].a), cross(z[j], F[j].l)};
+                u = Six{Ip.a + Sf.a, Ip.l + Sf.l};
+                w = Six{zero3, zero3};
+                if constexpr (p >= 0) {                 // psd of the first body is zero
+                    const Six Bp = bmul(K[j], l[j], psd[j].a);
+                    u = Six{Bp.a * 2.0f + u.a, Bp.l * 2.0f + u.l};
+                    w = inertia(mc[j], h[j], J, psd[j]);
+                }
+                if (!pri(j)) {
+                    const Six Bs = bmul(K[j], l[j], z[j]);
+                    w = Six{w.a + Bs.a, w.l + Bs.l};
+                }
+                w = Six{w.a * 2.0f, w.l * 2.0f};
+            }
+            const auto put = [&](int i, int c, float xq, float xv) {   // row i, column c
+                if constexpr (OP == kVjp) {
+                    gq[c] += xq * x[i];
+                    gv[c] += xv * x[i];
                 } else {
+                    Dq[c][i] = xq;
+                    Dv[c][i] = xv;
+                }
+            };
+            put(j, j, dot_S(j, u), dot_S(j, w));
+            const V3 b2 = b * 2.0f;
+            static_for<j>([&](auto tt) {
+                constexpr int k = j - decltype(tt)::v;
+                if constexpr (k == j || ((S::anc[j] >> k) & 1ull)) {
+                    constexpr int q = S::parent[k];
+                    if constexpr (q >= 0) {
+                        u.a = u.a + cross(r[k], u.l);
+                        w.a = w.a + cross(r[k], w.l);
+                        f.a = f.a + cross(r[k], f.l);
+                        put(q, j, dot_S(q, u), dot_S(q, w));
+                        float y = dot(f.a, pdd[q].a) + dot(f.l, pdd[q].l);
+                        float t = pri(q) ? 0.0f : dot(b2, z[q]);
+                        if constexpr (S::parent[q] >= 0) {
+                            y += dot(b2, psd[q].a);
+                            t += 2.0f * (dot(f.a, psd[q].a) + dot(f.l, psd[q].l));
+                        }
+                        put(j, q, y, t);
+                    }
+                }
+            });
+            if constexpr (p >= 0) {
+                K[p].c0 = K[p].c0 + K[j].c0 + l[j] * r[j].x;
+                K[p].c1 = K[p].c1 + K[j].c1 + l[j] * r[j].y;
+                K[p].c2 = K[p].c2 + K[j].c2 + l[j] * r[j].z;
+                l[p] = l[p] + l[j];
+                F[p] = Six{F[p].a + F[j].a + cross(r[j], F[j].l), F[p].l + F[j].l};
+                move_moments(P[j], h[j], mc[j], r[j]);
+                P[p] = Sym{P[p].xx + P[j].xx, P[p].yy + P[j].yy, P[p].zz + P[j].zz,
+                           P[p].xy + P[j].xy, P[p].xz + P[j].xz, P[p].yz + P[j].yz};
+                h[p] = h[p] + h[j];
+                mc[p] += mc[j];
+            }
+        });
+        if constexpr (OP == kVjp) {
+            if (valid) {
 #pragma unroll
-                    for (int u = 0; u < 2; ++u)
-#pragma unroll
-                        for (int k = 0; k < 6; ++k)
-                            df[u][i][k] = 0.0f;
+                for (int i = 0; i < B; ++i) {
+                    A.o0[vbase + I::body[i]] = -gq[i];
+                    A.o1[vbase + I::body[i]] = -gv[i];
                 }
             }
+            return;
         }
-        float dx[2][B];
+        float* const o0 = (OP == kFdGrad ? A.o2 : A.o0) + mb;
+        float* const o1 = (OP == kFdGrad ? A.o3 : A.o1) + mb;
+        const auto columns = [&](float (&D)[B][B], float* to) {
+            static_for<B>([&](auto jj) {
+                constexpr int j = decltype(jj)::v;
+                constexpr unsigned long long m = relatives<S>(j);
+                if constexpr (OP == kFdGrad)
+                    solve_masked<S, m, B - 1>(Lf, dinv, D[j]);
 #pragma unroll
-        for (int i = B - 1; i >= 0; --i) {
-            const int p = S::parent[i];
-            const bool live = in_subtree<S>(i, j) || ((S::anc[j < 0 ? 0 : j] >> i) & 1ull);
-#pragma unroll
-            for (int u = 0; u < 2; ++u)
-                dx[u][i] = df[u][i][s_index(prismatic<I>(i))];
-            if (p >= 0 && live) {
-#pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    float y[6];
-                    xt_fv(E[i], R[i], df[u][i], y);
-                    const float sel = (u == 0 && i == j) ? 1.0f : 0.0f;
-#pragma unroll
-                    for (int k = 0; k < 6; ++k)
-                        df[u][p < 0 ? 0 : p][k] += y[k] + sel * srcf[k];
-                }
-            }
-        }
-        gridq::ltl_solve<S>(Lf, dinv, dx[0]);
-        gridq::ltl_solve<S>(Lf, dinv, dx[1]);
-        if (valid) {
-            const int gj = I::body_of(j);
-#pragma unroll
-            for (int i = 0; i < B; ++i) {
-                if constexpr (ST::on) {
-                    s_stage[0][kl * N * N + I::body[i] * N + gj] = -dx[0][i];
-                    s_stage[1][kl * N * N + I::body[i] * N + gj] = -dx[1][i];
-                } else if constexpr (SR::on) {
-                    s_stage[0][kl * B * N + i * N + gj] = -dx[0][i];
-                    s_stage[1][kl * B * N + i * N + gj] = -dx[1][i];
-                } else {
-                    A.dqdd_dq[mbase + (long)I::body[i] * N + gj] = -dx[0][i];
-                    A.dqdd_dqd[mbase + (long)I::body[i] * N + gj] = -dx[1][i];
-                }
-            }
-        }
-    }
-    if constexpr (ST::on) {
-        wave_lds_sync();                      // every column staged
-        flush_stage(A.dqdd_dq + kb * N * N, s_stage[0], nv * N * N, lane);
-        flush_stage(A.dqdd_dqd + kb * N * N, s_stage[1], nv * N * N, lane);
-    }
-    if constexpr (SR::on) {
-        wave_lds_sync();                      // every column staged
-        flush_rows<I>(A.dqdd_dq + kb * N * N, s_stage[0], nv, lane);
-        flush_rows<I>(A.dqdd_dqd + kb * N * N, s_stage[1], nv, lane);
-    }
-    if (valid && N > B && !SR::on) {
-        // this branch's rows hold zeros in the other branches' columns
-        for (int e = h; e < B * N; e += L) {
-            const int i = e / N, c2 = e % N;
-            if (!I::contains(c2)) {
-                const long o = mbase + (long)I::body_of(i) * N + c2;
-                A.Minv[o] = 0.0f;
-                A.dqdd_dq[o] = 0.0f;
-                A.dqdd_dqd[o] = 0.0f;
-            }
+                for (int i = 0; i < B; ++i)
+                    to[i * B + j] = OP == kFdGrad ? -D[j][i] : (((m >> i) & 1ull) ? D[j][i] : 0.0f);
+            });
+        };
+        columns(Dq, mine);
+        if constexpr (Y::NT == 2) {
+            columns(Dv, mine + Y::tile);
+            wave_lds_sync();
+            flush_blocks<I, 2>(o0, o1, pool, pool + Y::tile, nv, lane);
+        } else {
+            wave_lds_sync();
+            flush_blocks<I, 1>(o0, nullptr, pool, nullptr, nv, lane);
+            wave_lds_sync();
+            columns(Dv, mine);
+            wave_lds_sync();
+            flush_blocks<I, 1>(o1, nullptr, pool, nullptr, nv, lane);
         }
     }
 }
@@ -872,27 +968,46 @@ __device__ __forceinline__ void run_minv(const grid::Args& A, int block)
 #if !GRID_LONG_BRANCH
 
 // defined by the generated epilogue: workgroup -> (branch, 64 knots)
-__device__ void grid_dispatch_s(const grid::Args& args, int block);
+template <int OP>
+__device__ void grid_dispatch_s(const gridv::BatchArgs& args, int block);
 
 extern "C" __global__ void __launch_bounds__(64) grid_fdgrad_serial(grid::Args args)
 {
-    grid_dispatch_s(args, (int)blockIdx.x);
+    const gridv::BatchArgs a{args.nknots, args.q, args.qd, args.tau, nullptr,
+                        args.qdd, args.Minv, args.dqdd_dq, args.dqdd_dqd};
+    grid_dispatch_s<gridv::kFdGrad>(a, (int)blockIdx.x);
 }
 
-// defined by the generated epilogue: workgroup -> (branch, 16 knots), four lanes per knot
-__device__ void grid_dispatch_s4(const grid::Args& args, int block);
+// the standalone algorithms in the same layout (their arguments as gridq::OpArgs)
+struct SerialOpArgs {
+    int nknots;
+    const float *q, *qd, *u, *u2;
+    float *out0, *out1, *out2;
+};
 
-extern "C" __global__ void __launch_bounds__(64) grid_fdgrad_serial4(grid::Args args)
+extern "C" __global__ void __launch_bounds__(64) grid_serial_fd(SerialOpArgs x)
 {
-    grid_dispatch_s4(args, (int)blockIdx.x);
+    const gridv::BatchArgs a{x.nknots, x.q, x.qd, x.u, nullptr, x.out0, nullptr, nullptr, nullptr};
+    grid_dispatch_s<gridv::kFd>(a, (int)blockIdx.x);
 }
 
-// defined by the generated epilogue: workgroup -> (branch, 32 knots), two lanes per knot
-__device__ void grid_dispatch_s2(const grid::Args& args, int block);
-
-extern "C" __global__ void __launch_bounds__(64) grid_fdgrad_serial2(grid::Args args)
+extern "C" __global__ void __launch_bounds__(64) grid_serial_minv(SerialOpArgs x)
 {
-    grid_dispatch_s2(args, (int)blockIdx.x);
+    const gridv::BatchArgs a{x.nknots, x.q,     nullptr, nullptr, nullptr,
+                             x.out0,   nullptr, nullptr, nullptr};
+    grid_dispatch_s<gridv::kMinv>(a, (int)blockIdx.x);
+}
+
+extern "C" __global__ void __launch_bounds__(64) grid_serial_idgrad(SerialOpArgs x)
+{
+    const gridv::BatchArgs a{x.nknots, x.q, x.qd, x.u, nullptr, x.out0, x.out1, nullptr, nullptr};
+    grid_dispatch_s<gridv::kIdGrad>(a, (int)blockIdx.x);
+}
+
+extern "C" __global__ void __launch_bounds__(64) grid_serial_vjp(SerialOpArgs x)
+{
+    const gridv::BatchArgs a{x.nknots, x.q, x.qd, x.u, x.u2, x.out0, x.out1, x.out2, nullptr};
+    grid_dispatch_s<gridv::kVjp>(a, (int)blockIdx.x);
 }
 
 #endif  // GRID_LONG_BRANCH

@@ -6,33 +6,8 @@
 // (Group<g>: NB branches of shape S). Each lane keeps its own body's quantities in registers
 // and meets the others through LDS; a workgroup is one wavefront, so no barrier is needed.
 //
-// Every quantity of a problem is expressed along one set of axes, those of the branch's first
-// body, but about the origin of the body that it belongs to. Moving a spatial vector from a
-// body to its parent is then one cross product with the offset r between the origins (6 FMA
-// against 24 for a full transform), and the offsets stay as short as the links, which keeps
-// float32 as accurate as it is in body axes. Gravity enters as the base acceleration turned
-// into these axes.
-//
-// With z_i the joint axis, S_i = (z_i, 0) for a revolute joint or (0, z_i) for a prismatic one,
-// v_l, a_l the velocity and acceleration of the parent taken at the origin of i, and
-//   psd_i = v_l x S_i,   pdd_i = a_l x S_i + v_l x psd_i,
-// the derivatives of inverse dynamics need only quantities of the subtree of j (superscript c):
-// the inertia I^c_j, the force f^c_j and B^c_j with B v = v x* I v, and with
-//   F1_j = I^c_j S_j,  b_j = B^c_j^T S_j,
-//   u_j = 2 B^c_j psd_j + I^c_j pdd_j + S_j x* f^c_j,   w_j = 2 (B^c_j S_j + I^c_j psd_j)
-// they are, for i = j or i an ancestor of j,
-//   M_ij = S_i . F1_j,   dtau_i/dq_j = S_i . u_j,   dtau_i/dqd_j = S_i . w_j,
-//   dtau_j/dq_i = 2 b_j . psd_i + F1_j . pdd_i,
-//   dtau_j/dqd_i = 2 (b_j . S_i + F1_j . psd_i)         (i an ancestor of j),
-// all other entries zero: one column of two six-vectors moved up the ancestor path replaces a
-// sweep over the tree per column (Algorithm 1 evaluates the same derivatives column by column).
-// For particles of mass m at p (from the origin) moving at u, B = [[sum m ((p . u) 1 - u p^T),
-// 0], [-(sum m u) x, 0]], so B^c travels as K = sum m u p^T (9 floats) and the momentum
-// l = sum m u, and the rotational inertia travels as P = sum m p p^T (J = tr(P) 1 - P):
-//   about an origin moved by -r: P' = P + (h + m r) r^T + r h^T, h' = h + m r, K' = K + l r^T.
-//
-// M^-1 comes from M = L^T L (sparse along ancestor paths), which every lane of a problem factors
-// for itself from the rows of M in LDS: 57 (7-body chain) to 324 (18-body tree) FMAs in
+// The formulation is that of grid_axes.hip. M^-1 comes from M = L^T L (sparse along ancestor
+// paths), which every lane of a problem factors for itself from the rows of M in LDS: 57 (7-body chain) to 324 (18-body tree) FMAs in
 // registers against one LDS round trip per level for a shared factor. Lane j then solves for
 // column j of M^-1, dqdd/dq and dqdd/dqd.
 //
@@ -45,79 +20,9 @@
 
 namespace gridt {
 
-using grids::flush_stage;
 using grids::wave_lds_sync;
 
-struct Args {
-    int nknots;
-    const float* q;
-    const float* qd;      // unused by M^-1
-    const float* u;       // tau (dFD, FD), qdd (dID, VJP), unused (M^-1)
-    const float* u2;      // g (VJP)
-    float* o0;            // qdd (dFD, FD), M^-1 (M^-1), dtau/dq (dID), qbar (VJP)
-    float* o1;            // M^-1 (dFD), dtau/dqd (dID), qdbar (VJP)
-    float* o2;            // dqdd/dq (dFD), taubar (VJP)
-    float* o3;            // dqdd/dqd (dFD)
-};
-
-enum Op : int { kFdGrad = 0, kFd = 1, kMinv = 2, kIdGrad = 3, kVjp = 4 };
-
-struct V3 {
-    float x, y, z;
-};
-
-__device__ __forceinline__ V3 operator+(V3 a, V3 b) { return {a.x + b.x, a.y + b.y, a.z + b.z}; }
-__device__ __forceinline__ V3 operator-(V3 a, V3 b) { return {a.x - b.x, a.y - b.y, a.z - b.z}; }
-__device__ __forceinline__ V3 operator*(V3 a, float s) { return {a.x * s, a.y * s, a.z * s}; }
-__device__ __forceinline__ float dot(V3 a, V3 b) { return a.x * b.x + a.y * b.y + a.z * b.z; }
-__device__ __forceinline__ V3 cross(V3 a, V3 b)
-{
-    return {a.y * b.z - a.z * b.y, a.z * b.x - a.x * b.z, a.x * b.y - a.y * b.x};
-}
-__device__ __forceinline__ V3 sel(bool c, V3 a, V3 b)
-{
-    return {c ? a.x : b.x, c ? a.y : b.y, c ? a.z : b.z};
-}
-
-struct Six {        // spatial vector [angular; linear]
-    V3 a, l;
-};
-
-struct Sym {        // symmetric 3x3
-    float xx, yy, zz, xy, xz, yz;
-};
-
-struct Mat {        // 3x3 by columns
-    V3 c0, c1, c2;
-};
-
-__device__ __forceinline__ V3 mul(const Sym& s, V3 v)
-{
-    return {s.xx * v.x + s.xy * v.y + s.xz * v.z, s.xy * v.x + s.yy * v.y + s.yz * v.z,
-            s.xz * v.x + s.yz * v.y + s.zz * v.z};
-}
-__device__ __forceinline__ V3 mul(const Mat& m, V3 v)
-{
-    return m.c0 * v.x + m.c1 * v.y + m.c2 * v.z;
-}
-__device__ __forceinline__ V3 tmul(const Mat& m, V3 v) { return {dot(m.c0, v), dot(m.c1, v), dot(m.c2, v)}; }
-
-// rigid-body inertia: mass, first moment h, second moment P about the origin
-// I x = [J w + h x v; m v + w x h], J = tr(P) 1 - P
-__device__ __forceinline__ Six inertia(float m, V3 h, const Sym& J, Six x)
-{
-    return {mul(J, x.a) + cross(h, x.l), x.l * m + cross(x.a, h)};
-}
-__device__ __forceinline__ Sym second_to_inertia(const Sym& P)
-{
-    return {P.yy + P.zz, P.xx + P.zz, P.xx + P.yy, -P.xy, -P.xz, -P.yz};
-}
-// B x = [tr(K) w - K w; w x l] (only the angular part of x enters)
-__device__ __forceinline__ Six bmul(const Mat& K, V3 l, V3 w)
-{
-    const float tr = K.c0.x + K.c1.y + K.c2.z;
-    return {w * tr - mul(K, w), cross(w, l)};
-}
+using namespace gridv;
 
 // compile-time facts of a shape
 template <class S>
@@ -197,11 +102,6 @@ constexpr int team_floats()
     return Lay<G>::floats;
 }
 
-// 16 bytes at a 4-byte aligned address (global memory takes them at any dword)
-struct __attribute__((packed, aligned(4))) F4 {
-    float x, y, z, w;
-};
-
 __device__ __forceinline__ void flush_block(float* dst, const float* src, int cnt, int lane)
 {
     const int n4 = cnt / 4;
@@ -273,7 +173,7 @@ __device__ __forceinline__ void flush_tiles(const float* pool, float* d0, float*
 }
 
 template <class G, int OP>
-__device__ __forceinline__ void run_team(const Args& A, int block, float* pool)
+__device__ __forceinline__ void run_team(const BatchArgs& A, int block, float* pool)
 {
     using S = typename G::S;
     using Y = Lay<G>;
@@ -454,16 +354,7 @@ __device__ __forceinline__ void run_team(const Args& A, int block, float* pool)
     }
 
     // ------------------------------------------------------------ the body's own inertia
-    Sym P;
-    {
-        // R P_T R^T
-        const V3 c0 = mul(R, V3{PT.xx, PT.xy, PT.xz}), c1 = mul(R, V3{PT.xy, PT.yy, PT.yz}),
-                 c2 = mul(R, V3{PT.xz, PT.yz, PT.zz});
-        const V3 r0{R.c0.x, R.c1.x, R.c2.x}, r1{R.c0.y, R.c1.y, R.c2.y}, r2{R.c0.z, R.c1.z, R.c2.z};
-        P = Sym{dot(r0, V3{c0.x, c1.x, c2.x}), dot(r1, V3{c0.y, c1.y, c2.y}),
-                dot(r2, V3{c0.z, c1.z, c2.z}), dot(r1, V3{c0.x, c1.x, c2.x}),
-                dot(r2, V3{c0.x, c1.x, c2.x}), dot(r2, V3{c0.y, c1.y, c2.y})};
-    }
+    Sym P = turn(R, PT);
     V3 h = mul(R, hT);
     const Sym P1 = P;                                  // the body alone (for the qdd increment)
     const V3 h1 = h;
@@ -473,10 +364,7 @@ __device__ __forceinline__ void run_team(const Args& A, int block, float* pool)
     if constexpr (kVel) {
         const Six v = add_S(vl, qd);
         l = v.l * m + cross(v.a, h);
-        // K = v h^T + w x P (by columns)
-        K.c0 = v.l * h.x + cross(v.a, V3{P.xx, P.xy, P.xz});
-        K.c1 = v.l * h.y + cross(v.a, V3{P.xy, P.yy, P.yz});
-        K.c2 = v.l * h.z + cross(v.a, V3{P.xz, P.yz, P.zz});
+        K = momentum_moment(v, h, P);
         Six a = Six{al.a + psd.a * qd, al.l + psd.l * qd};
         if constexpr (!kBias)
             a = add_S(a, ui);
@@ -492,11 +380,10 @@ __device__ __forceinline__ void run_team(const Args& A, int block, float* pool)
 #pragma unroll
         for (int c = 0; c < T::max_children(lev); ++c) {
             if (depth == lev && rank == c) {
-                const V3 g = h + r * mC;               // h about the parent's origin
-                float o[28] = {P.xx + g.x * r.x + r.x * h.x, P.yy + g.y * r.y + r.y * h.y,
-                               P.zz + g.z * r.z + r.z * h.z, P.xy + g.x * r.y + r.x * h.y,
-                               P.xz + g.x * r.z + r.x * h.z, P.yz + g.y * r.z + r.y * h.z,
-                               g.x, g.y, g.z};
+                Sym Q = P;
+                V3 g = h;
+                move_moments(Q, g, mC, r);
+                float o[28] = {Q.xx, Q.yy, Q.zz, Q.xy, Q.xz, Q.yz, g.x, g.y, g.z};
                 if constexpr (kVel) {
                     const V3 n = F.a + cross(r, F.l);
                     const float f[6] = {n.x, n.y, n.z, F.l.x, F.l.y, F.l.z};
@@ -819,36 +706,36 @@ __device__ __forceinline__ void run_team(const Args& A, int block, float* pool)
 
 // defined by the generated epilogue: workgroup -> (group of branches, knots)
 template <int OP>
-__device__ void grid_dispatch_t(const gridt::Args& args, int block);
+__device__ void grid_dispatch_t(const gridv::BatchArgs& args, int block);
 
 extern "C" __global__ void __launch_bounds__(64) grid_fdgrad_team(grid::Args args)
 {
-    const gridt::Args a{args.nknots, args.q, args.qd, args.tau, nullptr,
+    const gridv::BatchArgs a{args.nknots, args.q, args.qd, args.tau, nullptr,
                         args.qdd, args.Minv, args.dqdd_dq, args.dqdd_dqd};
     grid_dispatch_t<gridt::kFdGrad>(a, (int)blockIdx.x);
 }
 
 extern "C" __global__ void __launch_bounds__(64) grid_team_fd(gridq::OpArgs x)
 {
-    const gridt::Args a{x.nknots, x.q, x.qd, x.u, nullptr, x.out0, nullptr, nullptr, nullptr};
+    const gridv::BatchArgs a{x.nknots, x.q, x.qd, x.u, nullptr, x.out0, nullptr, nullptr, nullptr};
     grid_dispatch_t<gridt::kFd>(a, (int)blockIdx.x);
 }
 
 extern "C" __global__ void __launch_bounds__(64) grid_team_minv(gridq::OpArgs x)
 {
-    const gridt::Args a{x.nknots, x.q, nullptr, nullptr, nullptr, x.out0, nullptr, nullptr, nullptr};
+    const gridv::BatchArgs a{x.nknots, x.q, nullptr, nullptr, nullptr, x.out0, nullptr, nullptr, nullptr};
     grid_dispatch_t<gridt::kMinv>(a, (int)blockIdx.x);
 }
 
 extern "C" __global__ void __launch_bounds__(64) grid_team_idgrad(gridq::OpArgs x)
 {
-    const gridt::Args a{x.nknots, x.q, x.qd, x.u, nullptr, x.out0, x.out1, nullptr, nullptr};
+    const gridv::BatchArgs a{x.nknots, x.q, x.qd, x.u, nullptr, x.out0, x.out1, nullptr, nullptr};
     grid_dispatch_t<gridt::kIdGrad>(a, (int)blockIdx.x);
 }
 
 extern "C" __global__ void __launch_bounds__(64) grid_team_vjp(gridq::OpArgs x)
 {
-    const gridt::Args a{x.nknots, x.q, x.qd, x.u, x.u2, x.out0, x.out1, x.out2, nullptr};
+    const gridv::BatchArgs a{x.nknots, x.q, x.qd, x.u, x.u2, x.out0, x.out1, x.out2, nullptr};
     grid_dispatch_t<gridt::kVjp>(a, (int)blockIdx.x);
 }
 
