@@ -12,6 +12,7 @@ Both run in the HIP library on torch's current stream; torch provides the memory
 from __future__ import annotations
 
 import torch
+from torch.autograd import forward_ad as fwAD
 
 from . import grid
 
@@ -53,7 +54,15 @@ class ForwardDynamics(torch.autograd.Function):
 
 
 def forward_dynamics(model: "grid.Model", q, qd, tau, mode: str = "jacobians"):
-    """qdd = FD(q, qd, tau) for [N, n] float32 CUDA tensors, differentiable in all three."""
+    """qdd = FD(q, qd, tau) for [N, n] float32 CUDA tensors, differentiable in all three. Plain
+    tensors run ForwardDynamics' two steps in native code (_gridtorch), the backward without the
+    interpreter: its lock and wake-ups took most of a step (chain7, 6007 knots: 127 us)."""
+    if (mode in ("jacobians", "adjoint") and grid._plain_torch(q) and
+            fwAD._current_level < 0):
+        qdd = grid._native().forward_dynamics(model, model.n, model.device, q, qd, tau,
+                                              mode == "jacobians")
+        if qdd is not None:
+            return qdd
     return ForwardDynamics.apply(q, qd, tau, model, mode)
 
 

@@ -3,7 +3,8 @@
 Steps:
   1. embed the device sources csrc/grid_device.hip, grid_fused.hip, grid_axes.hip,
      grid_serial.hip, grid_ops.hip and grid_team.hip into generated includes (_build/<name>_src.inc);
-  2. compile the host runtime (csrc/*.cpp) with hipcc into libgrid.so;
+  2. compile the host runtime (csrc/*.cpp) with hipcc into libgrid.so, and the torch-facing
+     calls (csrc/grid_torch.cpp) into _gridtorch.so;
   3. compile the device source with hipcc for gfx950 behind a generated chain prelude
      (a full offline compile check; -save-temps keeps the ISA under _build/);
   4. run the library's own code generator + hiprtc for every topology the tests,
@@ -71,6 +72,29 @@ def build_library(verbose=False, out=None, sanitize=False) -> str:
            os.path.join(CSRC, "grid_batch.cpp"), os.path.join(CSRC, "grid_noalloc.hip"),
            os.path.join(CSRC, "grid_io.hip"),
            "-lhiprtc", "-lpthread", "-o", target + ".tmp"]
+    _run(cmd, verbose)
+    os.replace(target + ".tmp", target)
+    return target
+
+
+def build_torch_module(verbose=False) -> str:
+    """_gridtorch.so in-tree: the torch-facing calls (csrc/grid_torch.cpp, host code only)."""
+    import sysconfig
+
+    import torch
+    root = os.path.dirname(torch.__file__)
+    target = os.path.join(HERE, "_gridtorch.so")
+    inc = [os.path.join(root, "include"),
+           os.path.join(root, "include", "torch", "csrc", "api", "include"),
+           os.path.join(os.path.dirname(os.path.dirname(HIPCC)) or "/opt/rocm", "include"),
+           sysconfig.get_paths()["include"]]
+    cmd = ["g++", "-std=c++17", "-O2", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1",
+           "-DUSE_ROCM=1", "-DTORCH_EXTENSION_NAME=_gridtorch",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           *[x for i in inc for x in ("-isystem", i)], os.path.join(CSRC, "grid_torch.cpp"),
+           "-L" + os.path.join(root, "lib"), "-Wl,-rpath," + os.path.join(root, "lib"), "-lc10",
+           "-lc10_hip", "-ltorch_cpu", "-ltorch_hip", "-ltorch", "-ltorch_python", "-o",
+           target + ".tmp"]
     _run(cmd, verbose)
     os.replace(target + ".tmp", target)
     return target
@@ -204,6 +228,7 @@ def build(verbose=False):
     if ROOT not in sys.path:
         sys.path.insert(0, ROOT)
     build_library(verbose)
+    build_torch_module(verbose)
     offline_compile_check(verbose)
     precompile(verbose)
     return LIB

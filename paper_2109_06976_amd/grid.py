@@ -9,7 +9,9 @@ memory and the stream.
 from __future__ import annotations
 
 import ctypes as C
+import importlib.util
 import os
+import sys
 
 import numpy as np
 
@@ -206,6 +208,48 @@ def lib():
     return _lib
 
 
+_native_mod = None
+_addr = {}      # name -> address of the loaded library's function
+
+
+def _native():
+    """The torch-facing calls in native code (_gridtorch), bound to the loaded library. For
+    callers that have torch tensors in hand (raises if the module has not been built)."""
+    global _native_mod
+    if _native_mod is None:
+        path = os.path.join(_HERE, "_gridtorch.so")
+        if not os.path.exists(path):
+            raise GridError(GRID_EDEVICE, f"{path} is missing: run __graft_entry__.build()")
+        for name in _SIGS:
+            _addr[name] = C.cast(getattr(lib(), name), C.c_void_p).value
+        spec = importlib.util.spec_from_file_location("_gridtorch", path)
+        mod = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(mod)
+        mod.bind(_addr, _check)
+        _native_mod = mod
+    return _native_mod
+
+
+def _plain_torch(x) -> bool:
+    """x is a torch.Tensor in ordinary execution: no tracing, no function or dispatch mode and no
+    functorch transform sees the call, so that it may bypass Python."""
+    torch = sys.modules.get("torch")
+    if torch is None or type(x) is not torch.Tensor:
+        return False
+    c = torch._C
+    return not (c._are_functorch_transforms_active() or c._len_torch_dispatch_stack() or
+                c._len_torch_function_stack() or c._get_tracing_state())
+
+
+def _launch(name, model, N, bufs, need, stream) -> bool:
+    """The call `name`(model, N, bufs.., stream) in native code; False when some buffer is not
+    a plain tensor (the caller then converts or rejects it)."""
+    if not _plain_torch(bufs[0]):
+        return False
+    native = _native()
+    return native.launch(_addr[name], model, model.device, int(N), bufs, need, stream) is not None
+
+
 def status_string(status: int) -> str:
     return lib().grid_status_string(status).decode()
 
@@ -336,6 +380,10 @@ class Model:
         """grid_fd_grad on device buffers (torch tensors or addresses), asynchronous."""
         if N is None:
             N = int(q.shape[0])
+        v, m = _vec_mat(N, self.n)
+        if _launch("grid_fd_grad", self, N, (q, qd, tau, qdd, Minv, dqdd_dq, dqdd_dqd),
+                   (v, v, v, v, m, m, m), stream):
+            return
         ptrs = _fd_grad_ptrs(N, self.n, self.device, q, qd, tau, qdd, Minv, dqdd_dq, dqdd_dqd)
         _check(lib().grid_fd_grad(self._h, int(N), *ptrs, _stream_handle(stream)))
 
@@ -376,6 +424,8 @@ class Model:
         """grid_id: tau = ID(q, qd, qdd)."""
         N = int(q.shape[0]) if N is None else N
         v, _ = _vec_mat(N, self.n)
+        if _launch("grid_id", self, N, (q, qd, qdd, tau), (v, v, v, v), stream):
+            return
         d = self.device
         _check(lib().grid_id(self._h, int(N), _dev(q, v, d, "q"), _dev(qd, v, d, "qd"),
                              _dev(qdd, v, d, "qdd"), _dev(tau, v, d, "tau"),
@@ -385,6 +435,8 @@ class Model:
         """grid_fd: qdd = FD(q, qd, tau)."""
         N = int(q.shape[0]) if N is None else N
         v, _ = _vec_mat(N, self.n)
+        if _launch("grid_fd", self, N, (q, qd, tau, qdd), (v, v, v, v), stream):
+            return
         d = self.device
         _check(lib().grid_fd(self._h, int(N), _dev(q, v, d, "q"), _dev(qd, v, d, "qd"),
                              _dev(tau, v, d, "tau"), _dev(qdd, v, d, "qdd"),
@@ -394,6 +446,8 @@ class Model:
         """grid_minv: M(q)^-1."""
         N = int(q.shape[0]) if N is None else N
         v, m = _vec_mat(N, self.n)
+        if _launch("grid_minv", self, N, (q, Minv), (v, m), stream):
+            return
         _check(lib().grid_minv(self._h, int(N), _dev(q, v, self.device, "q"),
                                _dev(Minv, m, self.device, "Minv"), _stream_handle(stream)))
 
@@ -409,6 +463,9 @@ class Model:
         """grid_id_grad: dtau/dq and dtau/dqd at the given qdd."""
         N = int(q.shape[0]) if N is None else N
         v, m = _vec_mat(N, self.n)
+        if _launch("grid_id_grad", self, N, (q, qd, qdd, dtau_dq, dtau_dqd), (v, v, v, m, m),
+                   stream):
+            return
         d = self.device
         _check(lib().grid_id_grad(self._h, int(N), _dev(q, v, d, "q"), _dev(qd, v, d, "qd"),
                                   _dev(qdd, v, d, "qdd"), _dev(dtau_dq, m, d, "dtau_dq"),
@@ -420,6 +477,9 @@ def fd_vjp_adjoint(model, q, qd, qdd, gbar, qbar, qdbar, taubar, N=None, stream=
     if N is None:
         N = int(gbar.shape[0])
     v, _ = _vec_mat(N, model.n)
+    if _launch("grid_fd_vjp_adjoint", model, N, (q, qd, qdd, gbar, qbar, qdbar, taubar), (v,) * 7,
+               stream):
+        return
     d = model.device
     _check(lib().grid_fd_vjp_adjoint(model.handle, int(N), _dev(q, v, d, "q"),
                                      _dev(qd, v, d, "qd"), _dev(qdd, v, d, "qdd"),
@@ -433,6 +493,9 @@ def fd_vjp(model, dqdd_dq, dqdd_dqd, Minv, gbar, qbar, qdbar, taubar, N=None, st
     if N is None:
         N = int(gbar.shape[0])
     v, m = _vec_mat(N, model.n)
+    if _launch("grid_fd_vjp", model, N, (dqdd_dq, dqdd_dqd, Minv, gbar, qbar, qdbar, taubar),
+               (m, m, m, v, v, v, v), stream):
+        return
     d = model.device
     _check(lib().grid_fd_vjp(model.handle, int(N), _dev(dqdd_dq, m, d, "dqdd_dq"),
                              _dev(dqdd_dqd, m, d, "dqdd_dqd"), _dev(Minv, m, d, "Minv"),
@@ -888,6 +951,10 @@ def codegen_precompile(robot, flags: int = 0):
 def fd_grad_torch(model: Model, q, qd, tau, stream=None):
     """Allocate outputs with torch on q's device and launch on the current stream."""
     import torch
+    if stream is None and _plain_torch(q):
+        out = _native().fd_grad(model, model.n, model.device, q, qd, tau)
+        if out is not None:
+            return out
     q, qd, tau = (x.contiguous().float() for x in (q, qd, tau))
     N, n = q.shape
     dev = q.device
