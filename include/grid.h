@@ -200,7 +200,8 @@ grid_status grid_workspace_host_buffers(grid_workspace ws, float** in, float** o
  * The host call on the workspace's pinned buffers: copies the inputs of N knots from `in` to
  * the device, runs grid_fd_grad's fused kernel, copies the outputs into `out` and waits.
  * pieces = 1: one copy each way around one launch, timed per phase (timing as in
- * grid_fd_grad_host). pieces > 1: the batch is split into that many contiguous ranges of knots
+ * grid_fd_grad_host; a copy is a kernel through the device's mapping up to a few MB, a copy-engine
+ * transfer beyond). pieces > 1: the batch is split into that many contiguous ranges of knots
  * whose copies and launches go to two streams in turn, so that one range's copies overlap
  * another's kernel; only timing->total_ms (first copy start to last copy end) is set. Each
  * launch runs the build grid_fd_grad picks for its own knot count, and its results equal

@@ -162,7 +162,8 @@ hipError_t launch_vjp(int nknots, int n, const float* dq, const float* dqd, cons
 hipError_t launch_dt(int nknots, int n, float dt, const float* dq, const float* dqd,
                      const float* Minv, float* A, float* B, hipStream_t stream);
 
-// device -> pinned host copy of n floats by a kernel (16-byte stores; both 16-byte aligned)
+// copy of n floats between device and mapped pinned host memory by a kernel (16 bytes per thread;
+// both 16-byte aligned)
 hipError_t launch_copy_out(const float* src, float* dst, size_t n, hipStream_t stream);
 
 // the library's static scratch array (grid_noalloc.hip): its device address on `device`, taken

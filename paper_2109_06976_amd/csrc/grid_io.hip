@@ -1,5 +1,6 @@
-// Copy kernel of the mapped host call (grid_fd_grad_mapped): moves the packed outputs from
-// device memory into pinned host memory through its device mapping, so that the transfer is
+// Copy kernel of the host calls (grid_fd_grad_mapped; small batches of grid_fd_grad_pinned and
+// grid_fd_grad_host, both ways): moves packed arrays between device memory and pinned host
+// memory through its device mapping, so that the transfer is
 // a kernel's stores over the host link rather than a copy-engine job (whose start-up latency
 // dominates transfers of the few hundred kilobytes a batch of knots produces).
 //

@@ -1005,6 +1005,12 @@ static grid_status issue_piece(grid_model m, grid_workspace w, int32_t N, int32_
     return GRID_OK;
 }
 
+// Up to this many output bytes a copy kernel moves both ways through the device's mapping of the
+// pinned buffers: a copy-engine job takes 6 to 18 us to start and to signal, each way (chain7 at 256
+// knots: H2D 14.8, D2H 15.1 us; 158 KB out by a kernel 7.5). From tens of MB on the engines move a
+// few percent more per second (45 MB: 797 us, 820 by a kernel; 11 MB: 209 and 205).
+constexpr size_t kKernelCopyBytes = 8u << 20;
+
 // H2D of the pinned inputs, the fused kernel and D2H into the pinned outputs for N knots, then
 // a wait. One piece: one copy each way (the packed arrays are contiguous) on the workspace's
 // stream, the three phases timed by events. Several pieces: issued on the two streams in turn,
@@ -1017,17 +1023,25 @@ static grid_status run_pinned(grid_model m, grid_workspace w, int32_t N, int32_t
     if (pieces <= 1) {
         float* d_q = w->d_in;
         float* d_qdd = w->d_out;
+        const bool by_kernel = w->h_in_dev && w->h_out_dev &&
+                               (vec + 3 * mat) * sizeof(float) <= kKernelCopyBytes;
         HIP_TRY(hipEventRecord(w->ev[0], w->stream));
-        HIP_TRY(hipMemcpyAsync(d_q, w->h_in, 3 * vec * sizeof(float), hipMemcpyHostToDevice,
-                               w->stream));
+        if (by_kernel)
+            HIP_TRY(launch_copy_out(w->h_in_dev, d_q, 3 * vec, w->stream));
+        else
+            HIP_TRY(hipMemcpyAsync(d_q, w->h_in, 3 * vec * sizeof(float), hipMemcpyHostToDevice,
+                                   w->stream));
         HIP_TRY(hipEventRecord(w->ev[1], w->stream));
         grid_status s = launch_fused(m, N, d_q, d_q + vec, d_q + 2 * vec, d_qdd, d_qdd + vec,
                                      d_qdd + vec + mat, d_qdd + vec + 2 * mat, w->stream);
         if (s != GRID_OK)
             return s;
         HIP_TRY(hipEventRecord(w->ev[2], w->stream));
-        HIP_TRY(hipMemcpyAsync(w->h_out, d_qdd, (vec + 3 * mat) * sizeof(float),
-                               hipMemcpyDeviceToHost, w->stream));
+        if (by_kernel)
+            HIP_TRY(launch_copy_out(d_qdd, w->h_out_dev, vec + 3 * mat, w->stream));
+        else
+            HIP_TRY(hipMemcpyAsync(w->h_out, d_qdd, (vec + 3 * mat) * sizeof(float),
+                                   hipMemcpyDeviceToHost, w->stream));
         HIP_TRY(hipEventRecord(w->ev[3], w->stream));
         HIP_TRY(hipStreamSynchronize(w->stream));
         if (timing) {
