@@ -125,6 +125,7 @@ def standard_models():
     # the largest robot the library accepts (32 bodies), and 32 bodies each on the base
     models.append(max_size_model())
     models.append(star_model())
+    models.extend(tree_models().values())
     return models
 
 
@@ -143,6 +144,21 @@ def max_size_model():
     from paper_2109_06976_amd import synth
     parent = np.concatenate([synth.humanoid_parent(), np.array([22, 29], np.int32)])
     return synth.random_model(parent.astype(np.int32), 47, "humanoid32")
+
+
+def tree_models():
+    """Robots whose branches lie among each other's rows, by name: a chain of 17 bodies, a tree
+    with branch points at two depths beside a chain (13 rows, so none of an even length), and
+    two chains of one shape beside a tree (8 rows)."""
+    import numpy as np
+    from paper_2109_06976_amd import synth
+    parents = {
+        "chain17": synth.chain_parent(17),
+        "branches13": np.array([-1, -1, 0, 0, 1, 2, 3, 3, 4, 6, 7, 8, 9]),
+        "pairs8": np.array([-1, -1, 0, 1, -1, 4, 4, 5]),
+    }
+    return {k: synth.random_model(p.astype(np.int32), 50 + i, k)
+            for i, (k, p) in enumerate(parents.items())}
 
 
 def prismatic_models():

@@ -381,8 +381,8 @@ static void emit_groups(std::ostringstream& os, const Topology& t, const std::ve
         const BranchShape& sh = t.shapes[g];
         const int B = sh.B;
         std::vector<float> tab;
-        std::vector<int> ints, rowmap, colmap;
-        int nb = 0, first = -1;
+        std::vector<int> ints, bodies;
+        int nb = 0, first = -1, hangs = 0;
         bool prism = false;
         for (size_t k0 = 0; k0 < t.insts.size(); ++k0) {
             const BranchInst& in = t.insts[k0];
@@ -397,13 +397,27 @@ static void emit_groups(std::ostringstream& os, const Topology& t, const std::ve
                 if (sh.parent[i] >= 0)
                     sub[sh.parent[i]] += sub[i];
             }
-            std::vector<int> depth(B), children(B), rank(B);
+            // segments: a body with one child shares its child's; tier 0 has no branches below
+            std::vector<int> depth(B), children(B), below(B), tier(B), pos(B);
             for (int i = 0; i < B; ++i) {
                 const int p = sh.parent[i];
                 depth[i] = p < 0 ? 0 : depth[p] + 1;
-                rank[i] = p < 0 ? 0 : children[p]++;
+                if (p >= 0)
+                    ++children[p];
             }
-            std::vector<int> col(t.n, -1);
+            for (int i = B - 1; i >= 0; --i) {
+                const int p = sh.parent[i];
+                if (p < 0)
+                    continue;
+                const bool same = children[p] == 1;
+                below[p] = same ? below[i] + 1 : 0;
+                tier[p] = std::max(tier[p], tier[i] + (same ? 0 : 1));
+            }
+            for (int i = 0; i < B; ++i) {
+                const int p = sh.parent[i];
+                pos[i] = p >= 0 && children[p] == 1 ? pos[p] + 1 : 0;
+                hangs = std::max(hangs, children[i] > 1 ? children[i] : 0);
+            }
             for (int i = 0; i < B; ++i) {
                 const float* c = consts.data() + in.coff + (size_t)i * kConstStride;
                 tab.insert(tab.end(), c, c + 12);
@@ -417,13 +431,42 @@ static void emit_groups(std::ostringstream& os, const Topology& t, const std::ve
                 int k = 0;
                 for (int a = sh.parent[i]; a >= 0; a = sh.parent[a], ++k)
                     words[k / 4] |= (uint32_t)a << (8 * (k % 4));
-                ints.insert(ints.end(), {in.body[i], depth[i], rank[i], children[i]});
+                const int p = sh.parent[i];
+                const int above = p >= 0 && children[p] > 1 ? tier[p] : 255;
+                ints.insert(ints.end(), {in.body[i], depth[i],
+                                         pos[i] | below[i] << 8 | tier[i] << 16 | (int)((unsigned)above << 24), 0});
                 for (uint32_t w : words)
                     ints.push_back((int)w);
-                rowmap.push_back(in.body[i]);
-                col[in.body[i]] = i;
+                bodies.push_back(in.body[i]);
             }
-            colmap.insert(colmap.end(), col.begin(), col.end());
+        }
+        // the segments that hang from a body with several children
+        std::vector<int> hanging;
+        for (int e = 0; e < nb * B; ++e) {
+            std::vector<int> kids;
+            for (int i = 0; i < B; ++i)
+                if (sh.parent[i] == e % B)
+                    kids.push_back(i);
+            for (int c = 0; c < hangs; ++c)
+                hanging.push_back(kids.size() > 1 && c < (int)kids.size() ? kids[c] : -1);
+        }
+        // the group's rows in the robot's order: the place of each branch's bodies among them,
+        // and where a run of adjacent rows begins, behind how many more rows of other groups
+        std::vector<int> sorted = bodies, rowmap, run_row, run_gap;
+        std::sort(sorted.begin(), sorted.end());
+        bool in_order = true;
+        for (size_t e = 0; e < bodies.size(); ++e) {
+            rowmap.push_back((int)(std::lower_bound(sorted.begin(), sorted.end(), bodies[e]) -
+                                   sorted.begin()));
+            in_order = in_order && rowmap[e] == (int)e;
+        }
+        int before = 0;
+        for (int e = 0; e < (int)sorted.size(); ++e) {
+            if (e == 0 || sorted[e] - e != before) {
+                run_row.push_back(e);
+                run_gap.push_back(sorted[e] - e - before);
+                before = sorted[e] - e;
+            }
         }
         os << "__device__ alignas(16) const float grid_tf_" << g << "[" << tab.size() << "] = ";
         emit_floats(os, tab.data(), tab.size());
@@ -435,14 +478,23 @@ static void emit_groups(std::ostringstream& os, const Topology& t, const std::ve
         };
         emit_ints("grid_ti_", ints);
         emit_ints("grid_tr_", rowmap);
-        emit_ints("grid_tc_", colmap);
+        if (hanging.empty())
+            hanging.push_back(-1);
+        emit_ints("grid_th_", hanging);
         os << "template <> struct Group<" << g << "> {\n    using S = Inst<" << first << ">::S;\n"
            << "    static constexpr int N = Inst<" << first << ">::N;\n    static constexpr int NB = " << nb
-           << ";\n    static constexpr bool prism = " << (prism ? "true" : "false") << ";\n"
+           << ";\n    static constexpr bool prism = " << (prism ? "true" : "false")
+           << ";\n    static constexpr bool in_order = " << (in_order ? "true" : "false")
+           << ";\n    static constexpr int NR = " << run_row.size() << ";\n"
+           << "    static constexpr int run_row[] = ";
+        emit_list(os, run_row);
+        os << ";\n    static constexpr int run_gap[] = ";
+        emit_list(os, run_gap);
+        os << ";\n"
            << "    __device__ static const float* table() { return grid_tf_" << g << "; }\n"
            << "    __device__ static const int* ints() { return grid_ti_" << g << "; }\n"
            << "    __device__ static const int* rowmap() { return grid_tr_" << g << "; }\n"
-           << "    __device__ static const int* colmap() { return grid_tc_" << g << "; }\n"
+           << "    __device__ static const int* hanging() { return grid_th_" << g << "; }\n"
            << "    __device__ static const float* a0() { return grid_a0_0; }\n};\n";
     }
 }

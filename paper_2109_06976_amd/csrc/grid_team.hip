@@ -49,16 +49,57 @@ struct Tree {
             p = S::parent[p];
         return p;
     }
-    // most children that a body of depth lev - 1 has
-    static constexpr int max_children(int lev)
+    static constexpr int children(int p)
+    {
+        int c = 0;
+        for (int i = p + 1; i < S::B; ++i)
+            c += S::parent[i] == p ? 1 : 0;
+        return c;
+    }
+    // Segments: a body with one child shares its child's. The tier of a segment is 0 without
+    // branches below it, else one more than the highest tier among those.
+    static constexpr int end_of(int i)
+    {
+        for (int k = i + 1; k < S::B; ++k)
+            if (S::parent[k] == i && children(i) == 1)
+                i = k;
+        return i;
+    }
+    static constexpr int tier(int i)
+    {
+        const int e = end_of(i);
+        int t = 0;
+        for (int k = e + 1; k < S::B; ++k) {
+            if (S::parent[k] == e) {
+                const int x = tier(k) + 1;
+                t = x > t ? x : t;
+            }
+        }
+        return t;
+    }
+    static constexpr int tiers()
+    {
+        return tier(0) + 1;
+    }
+    // bodies in the longest segment of a tier
+    static constexpr int longest(int tr)
     {
         int m = 0;
-        for (int p = 0; p < S::B; ++p) {
-            int c = 0;
-            for (int i = 0; i < S::B; ++i)
-                c += (S::parent[i] == p && depth(i) == lev) ? 1 : 0;
-            m = c > m ? c : m;
+        for (int i = 0; i < S::B; ++i) {
+            const bool head = S::parent[i] < 0 || children(S::parent[i]) != 1;
+            if (head && tier(i) == tr) {
+                const int n = depth(end_of(i)) - depth(i) + 1;
+                m = n > m ? n : m;
+            }
         }
+        return m;
+    }
+    // most segments that hang from one body
+    static constexpr int most_hanging()
+    {
+        int m = 0;
+        for (int i = 0; i < S::B; ++i)
+            m = children(i) > 1 && children(i) > m ? children(i) : m;
         return m;
     }
     static constexpr bool chain()
@@ -82,18 +123,31 @@ struct Lay {
     static constexpr int AW = MD > 0 ? (MD + 3) / 4 : 1;
     static constexpr int RS = up4(MD + 1);             // a row of M: self, then ancestors
     static constexpr int BS = up4(B);
-    static constexpr bool FULL = NB * B == N;          // the group is the whole robot
+    static constexpr int GB = NB * B;                  // the group's rows of a knot's matrix
+    static constexpr bool FULL = GB == N;              // the group is the whole robot
     // floats: six fields of a float4 per body (z and a scalar, r, psd, pdd), a vector per
     // problem, then one region that the level exchange (seven fields), M and the columns of
-    // dtau use in turn; the output tiles take the place of everything at the end
+    // dtau use in turn; the output tiles take the place of everything at the end: all three
+    // where they fit, else one after the other
     static constexpr int oX = 6 * 4 * NE;
     static constexpr int oU = oX + up4(SL * BS);
     static constexpr int exch = 7 * 4 * NE;
     static constexpr int rows = SL * B * RS;
     static constexpr int cols = 2 * SL * B * BS;
-    static constexpr int tile = FULL ? up4(KPB * N * N) : up4(SL * B * B);
+    static constexpr int tile = up4(KPB * GB * N);
     static constexpr int mx(int a, int b) { return a > b ? a : b; }
-    static constexpr int floats = mx(oU + mx(mx(exch, rows), cols), 3 * tile);
+    static constexpr int base = oU + mx(mx(exch, rows), cols);
+    static constexpr int NT = 3 * tile <= base ? 3 : 1;
+    static constexpr int floats = mx(base, NT * tile);
+    // floats that a flushed piece holds: no piece crosses the end of a run of adjacent rows
+    static constexpr int piece()
+    {
+        int w = GB * N % 4 == 0 ? 4 : (GB * N % 2 == 0 ? 2 : 1);
+        for (int k = 0; k < G::NR; ++k)
+            while (G::run_row[k] * N % w != 0)
+                w /= 2;
+        return w;
+    }
 };
 
 template <class G>
@@ -113,60 +167,49 @@ __device__ __forceinline__ void flush_block(float* dst, const float* src, int cn
         dst[e] = src[e];
 }
 
-// NM matrices' tiles ([knot][N][N], or the branch's blocks [problem][B][B] when the group is not
-// the whole robot: then its rows, zeros in the other branches' columns) to global memory
-template <class G, int NM>
-__device__ __forceinline__ void flush_tiles(const float* pool, float* d0, float* d1, float* d2,
-                                            int block, int nv, int lane)
+// rows of other groups before row `row` of the group's (its place in the robot, less `row`)
+template <class G>
+__device__ __forceinline__ int rows_before(int row)
+{
+    int n = 0;
+#pragma unroll
+    for (int r = 0; r < G::NR; ++r)
+        n += row >= G::run_row[r] ? G::run_gap[r] : 0;
+    return n;
+}
+
+// a matrix's tile ([knot][the group's rows in the robot's order][N]) to global memory, in pieces
+// of up to four floats whatever the rows (row by row, with a lane per float, it took three to
+// four times the instructions: humanoid30 at 16384 knots 82.5 us a launch, 79.2 so)
+template <class G>
+__device__ __forceinline__ void flush_tile(float* d, const float* tile, int block, int nv, int lane)
 {
     using Y = Lay<G>;
-    constexpr int B = Y::B, N = Y::N, NB = Y::NB;
-    const long kb = (long)block * Y::KPB * N * N;
+    constexpr int N = Y::N;
+    d += (long)block * Y::KPB * N * N;
     if constexpr (Y::FULL) {
-        flush_block(d0 + kb, pool, nv * N * N, lane);
-        if constexpr (NM > 1)
-            flush_block(d1 + kb, pool + Y::tile, nv * N * N, lane);
-        if constexpr (NM > 2)
-            flush_block(d2 + kb, pool + 2 * Y::tile, nv * N * N, lane);
+        flush_block(d, tile, nv * N * N, lane);
     } else {
-        // RPI rows of N floats per step; a lane keeps its column and, per branch, that column's
-        // place in the tile and the offsets of its rows (loaded once, not per knot)
-        constexpr int RPI = 64 / N, STEPS = (B + RPI - 1) / RPI;
-        const int lr = lane / N, lc = lane - lr * N;
-        int row[NB][STEPS], col[NB];
+        constexpr int W = Y::piece(), PK = Y::GB * N / W, STEPS = (Y::KPB * PK + 63) / 64;
 #pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            col[b] = G::colmap()[b * N + lc];
+        for (int k = 0; k < STEPS; ++k) {
+            const int e = k * 64 + lane;
+            const int ks = e / PK, p = (e - ks * PK) * W;
+            const int off = ks * N * N + p + rows_before<G>(p / N) * N;
+            if (e < nv * PK) {
+                float x[W];
+                if constexpr (W == 4) {
+                    const float4 v = reinterpret_cast<const float4*>(tile)[e];
+                    x[0] = v.x;
+                    x[1] = v.y;
+                    x[2] = v.z;
+                    x[3] = v.w;
+                } else {
 #pragma unroll
-            for (int k = 0; k < STEPS; ++k) {
-                const int i = k * RPI + lr;
-                row[b][k] = G::rowmap()[b * B + (i < B ? i : 0)] * N + lc;
-            }
-        }
-        if (lr >= RPI)
-            return;
-#pragma unroll
-        for (int ks = 0; ks < Y::KPB; ++ks) {
-            if (ks >= nv)
-                return;
-            float* const p0 = d0 + kb + ks * N * N;
-            float* const p1 = NM > 1 ? d1 + kb + ks * N * N : nullptr;
-            float* const p2 = NM > 2 ? d2 + kb + ks * N * N : nullptr;
-#pragma unroll
-            for (int b = 0; b < NB; ++b) {
-                const bool in = col[b] >= 0;
-                const float* src = pool + (ks * NB + b) * B * B + lr * B + (in ? col[b] : 0);
-#pragma unroll
-                for (int k = 0; k < STEPS; ++k) {
-                    if (k * RPI + RPI > B && k * RPI + lr >= B)
-                        break;
-                    const float* x = src + k * RPI * B;
-                    p0[row[b][k]] = in ? x[0] : 0.0f;
-                    if constexpr (NM > 1)
-                        p1[row[b][k]] = in ? x[Y::tile] : 0.0f;
-                    if constexpr (NM > 2)
-                        p2[row[b][k]] = in ? x[2 * Y::tile] : 0.0f;
+                    for (int w = 0; w < W; ++w)
+                        x[w] = tile[e * W + w];
                 }
+                store<W>(d + off, x);
             }
         }
     }
@@ -179,6 +222,7 @@ __device__ __forceinline__ void run_team(const BatchArgs& A, int block, float* p
     using Y = Lay<G>;
     using T = Tree<S>;
     constexpr int B = Y::B, NB = Y::NB, N = Y::N, MD = Y::MD, NE = Y::NE, BS = Y::BS;
+    constexpr int MK = T::most_hanging();
     constexpr int DZ = NE - 1;                         // the entry of zeros
     constexpr bool kVel = OP != kMinv;
     constexpr bool kMass = OP != kIdGrad;
@@ -213,7 +257,11 @@ __device__ __forceinline__ void run_team(const BatchArgs& A, int block, float* p
 
     // ------------------------------------------------------------ the lane's body
     const int4 ti = reinterpret_cast<const int4*>(G::ints())[(br * B + i) * 3];
-    const int body = ti.x, depth = ti.y, rank = ti.z, nchild = ti.w;
+    const int body = ti.x, depth = ti.y;
+    // place in its segment from the top, bodies below it there, the segment's tier, and for a
+    // segment's first body the tier of the segment that it hangs from
+    const int pos = ti.z & 255, rem = (ti.z >> 8) & 255, tier = (ti.z >> 16) & 255,
+              above = (ti.z >> 24) & 255;
     const long vo = (long)knot * N + body;
     const float qi = A.q[vo];
     const float qd = kVel ? A.qd[vo] : 0.0f;
@@ -225,7 +273,12 @@ __device__ __forceinline__ void run_team(const BatchArgs& A, int block, float* p
         for (int t = 0; t < MD; ++t)
             anc[t] = t < depth ? sb + ((aw[t / 4] >> (8 * (t % 4))) & 255) : DZ;
     }
-    const int parent = MD > 0 ? anc[0] : DZ;           // entry; the root's is the zeros
+    int hang[MK > 0 ? MK : 1];                         // entries of the segments that hang here
+#pragma unroll
+    for (int c = 0; c < MK; ++c) {
+        const int k = G::hanging()[(br * B + i) * MK + c];
+        hang[c] = k < 0 ? DZ : sb + k;
+    }
     const float4* tf = reinterpret_cast<const float4*>(G::table()) + (br * B + i) * 6;
     const float4 t0 = tf[0], t1 = tf[1], t2 = tf[2], t3 = tf[3], t4 = tf[4], t5 = tf[5];
     const V3 e0{t0.x, t0.y, t0.z}, e1{t0.w, t1.x, t1.y}, e2{t1.z, t1.w, t2.x};   // rows of E_T
@@ -290,6 +343,19 @@ __device__ __forceinline__ void run_team(const BatchArgs& A, int block, float* p
     if constexpr (kVel) {
         const float4 g = fU[sb];
         a0 = V3{g.x, g.y, g.z};
+    }
+
+    // from the ancestor at distance 1, 2, 4, .. to this body
+    V3 ds[5];
+    {
+        V3 D = r;
+#pragma unroll
+        for (int t = 0; t < MD; ++t) {
+            if (t == 0 || t == 1 || t == 3 || t == 7 || t == 15)
+                ds[t == 0 ? 0 : t == 1 ? 1 : t == 3 ? 2 : t == 7 ? 3 : 4] = D;
+            const float4 rk = fR[anc[t]];
+            D = D + V3{rk.x, rk.y, rk.z};
+        }
     }
 
     // sum over the strict ancestors k of S_k s_k, moved to this body's origin (s_k: the scalar
@@ -373,61 +439,103 @@ __device__ __forceinline__ void run_team(const BatchArgs& A, int block, float* p
     }
 
     // ------------------------------------------------------------ sums over subtrees
-    // leaves to root, level by level; siblings take turns (their rank)
-    constexpr int NF = kDer ? 7 : (kVel ? 4 : 3);      // float4 fields exchanged
+    // Within the segments of a tier by doubling: after the step of distance s a body holds the
+    // sum over 2 s bodies from it on, about its own origin. Then a segment's last body takes
+    // the sums of those that hang from it. `put` writes a body's fields, moved up by d, and
+    // `add` takes them. Level by level, one body of each chain at work, it took as many
+    // exchanges as the tree is deep, and one more for every further sibling: humanoid30 at 4096
+    // and 16384 knots 27.2 and 79.2 us a launch, 24.0 and 70.0 so; chain7 at 16384 14.7 and 12.9.
+    const auto sum_up = [&](auto nf, const auto& put, const auto& add) {
+        constexpr int NF = decltype(nf)::v;            // float4 fields exchanged
+        const auto send = [&](int to, V3 d) {
+            float o[4 * NF];
+            put(o, d);
 #pragma unroll
-    for (int lev = MD; lev >= 1; --lev) {
+            for (int e = 0; e < NF; ++e)
+                fU[e * NE + to] = float4{o[4 * e], o[4 * e + 1], o[4 * e + 2], o[4 * e + 3]};
+        };
+        const auto receive = [&](int from) {
+            float o[4 * NF];
 #pragma unroll
-        for (int c = 0; c < T::max_children(lev); ++c) {
-            if (depth == lev && rank == c) {
-                Sym Q = P;
-                V3 g = h;
-                move_moments(Q, g, mC, r);
-                float o[28] = {Q.xx, Q.yy, Q.zz, Q.xy, Q.xz, Q.yz, g.x, g.y, g.z};
-                if constexpr (kVel) {
-                    const V3 n = F.a + cross(r, F.l);
-                    const float f[6] = {n.x, n.y, n.z, F.l.x, F.l.y, F.l.z};
-#pragma unroll
-                    for (int e = 0; e < 6; ++e)
-                        o[9 + e] = f[e];
-                }
-                if constexpr (kDer) {
-                    const V3 k0 = K.c0 + l * r.x, k1 = K.c1 + l * r.y, k2 = K.c2 + l * r.z;
-                    const float f[12] = {k0.x, k0.y, k0.z, k1.x, k1.y, k1.z,
-                                         k2.x, k2.y, k2.z, l.x,  l.y,  l.z};
-#pragma unroll
-                    for (int e = 0; e < 12; ++e)
-                        o[15 + e] = f[e];
-                }
-#pragma unroll
-                for (int e = 0; e < NF; ++e)
-                    fU[e * NE + parent] = float4{o[4 * e], o[4 * e + 1], o[4 * e + 2], o[4 * e + 3]};
+            for (int e = 0; e < NF; ++e) {
+                const float4 x = fU[e * NE + from];
+                o[4 * e] = x.x;
+                o[4 * e + 1] = x.y;
+                o[4 * e + 2] = x.z;
+                o[4 * e + 3] = x.w;
             }
-            wave_lds_sync();
-            if (depth == lev - 1 && nchild > c) {
-                float o[28];
+            add(o);
+        };
+        grids::static_for<T::tiers()>([&](auto tt) {
+            constexpr int tr = decltype(tt)::v, len = T::longest(tr);
+            if constexpr (tr > 0) {
+                if (above == tr)
+                    send(me, r);
+                wave_lds_sync();
+                if (tier == tr) {
 #pragma unroll
-                for (int e = 0; e < NF; ++e) {
-                    const float4 x = fU[e * NE + me];
-                    o[4 * e] = x.x;
-                    o[4 * e + 1] = x.y;
-                    o[4 * e + 2] = x.z;
-                    o[4 * e + 3] = x.w;
+                    for (int c = 0; c < MK; ++c)
+                        if (hang[c] != DZ)
+                            receive(hang[c]);
                 }
-                P = Sym{P.xx + o[0], P.yy + o[1], P.zz + o[2], P.xy + o[3], P.xz + o[4], P.yz + o[5]};
-                h = h + V3{o[6], o[7], o[8]};
-                if constexpr (kVel)
-                    F = Six{F.a + V3{o[9], o[10], o[11]}, F.l + V3{o[12], o[13], o[14]}};
-                if constexpr (kDer) {
-                    K.c0 = K.c0 + V3{o[15], o[16], o[17]};
-                    K.c1 = K.c1 + V3{o[18], o[19], o[20]};
-                    K.c2 = K.c2 + V3{o[21], o[22], o[23]};
-                    l = l + V3{o[24], o[25], o[26]};
-                }
+                wave_lds_sync();
             }
-            wave_lds_sync();
-        }
-    }
+            grids::static_for<5>([&](auto kk) {
+                constexpr int k = decltype(kk)::v, s = 1 << k;
+                if constexpr (s < len) {
+                    if (tier == tr && pos >= s)
+                        send(anc[s - 1], ds[k]);
+                    wave_lds_sync();
+                    if (tier == tr && rem >= s)
+                        receive(me);
+                    wave_lds_sync();
+                }
+            });
+        });
+    };
+    constexpr int NF = kDer ? 7 : (kVel ? 4 : 3);
+    float ms = m;                                      // the mass that P and h stand for
+    sum_up(
+        grids::Int<NF>{},
+        [&](float (&o)[4 * NF], V3 d) {
+            Sym Q = P;
+            V3 g = h;
+            move_moments(Q, g, ms, d);
+            const float f[10] = {Q.xx, Q.yy, Q.zz, Q.xy, Q.xz, Q.yz, g.x, g.y, g.z, ms};
+#pragma unroll
+            for (int e = 0; e < 10; ++e)
+                o[e] = f[e];
+            if constexpr (kVel) {
+                const V3 n = F.a + cross(d, F.l);
+                const float y[6] = {n.x, n.y, n.z, F.l.x, F.l.y, F.l.z};
+#pragma unroll
+                for (int e = 0; e < 6; ++e)
+                    o[10 + e] = y[e];
+            }
+            if constexpr (kDer) {
+                const V3 k0 = K.c0 + l * d.x, k1 = K.c1 + l * d.y, k2 = K.c2 + l * d.z;
+                const float y[12] = {k0.x, k0.y, k0.z, k1.x, k1.y, k1.z,
+                                     k2.x, k2.y, k2.z, l.x,  l.y,  l.z};
+#pragma unroll
+                for (int e = 0; e < 12; ++e)
+                    o[16 + e] = y[e];
+            }
+            if constexpr (!kVel)
+                o[10] = o[11] = 0.0f;
+        },
+        [&](const float (&o)[4 * NF]) {
+            P = Sym{P.xx + o[0], P.yy + o[1], P.zz + o[2], P.xy + o[3], P.xz + o[4], P.yz + o[5]};
+            h = h + V3{o[6], o[7], o[8]};
+            ms += o[9];
+            if constexpr (kVel)
+                F = Six{F.a + V3{o[10], o[11], o[12]}, F.l + V3{o[13], o[14], o[15]}};
+            if constexpr (kDer) {
+                K.c0 = K.c0 + V3{o[16], o[17], o[18]};
+                K.c1 = K.c1 + V3{o[19], o[20], o[21]};
+                K.c2 = K.c2 + V3{o[22], o[23], o[24]};
+                l = l + V3{o[25], o[26], o[27]};
+            }
+        });
 
     // S_k . f for the body k beside z_k, and for this body
     const auto dot_S = [&](float4 zk, float4 rk, Six f) {
@@ -516,23 +624,18 @@ __device__ __forceinline__ void run_team(const BatchArgs& A, int block, float* p
         const Six da = path_sum();
         al = Six{al.a + da.a, al.l + da.l};
         Six f = inertia(m, h1, second_to_inertia(P1), add_S(da, xi));
+        sum_up(
+            grids::Int<2>{},
+            [&](float (&o)[8], V3 d) {
+                const V3 n = f.a + cross(d, f.l);
+                const float y[8] = {n.x, n.y, n.z, f.l.x, f.l.y, f.l.z, 0.0f, 0.0f};
 #pragma unroll
-        for (int lev = MD; lev >= 1; --lev) {
-#pragma unroll
-            for (int c = 0; c < T::max_children(lev); ++c) {
-                if (depth == lev && rank == c) {
-                    const V3 n = f.a + cross(r, f.l);
-                    fU[parent] = float4{n.x, n.y, n.z, f.l.x};
-                    fU[NE + parent] = float4{f.l.y, f.l.z, 0.0f, 0.0f};
-                }
-                wave_lds_sync();
-                if (depth == lev - 1 && nchild > c) {
-                    const float4 x = fU[me], y = fU[NE + me];
-                    f = Six{f.a + V3{x.x, x.y, x.z}, f.l + V3{x.w, y.x, y.y}};
-                }
-                wave_lds_sync();
-            }
-        }
+                for (int e = 0; e < 8; ++e)
+                    o[e] = y[e];
+            },
+            [&](const float (&o)[8]) {
+                f = Six{f.a + V3{o[0], o[1], o[2]}, f.l + V3{o[3], o[4], o[5]}};
+            });
         F = Six{F.a + f.a, F.l + f.l};
     }
 
@@ -640,28 +743,46 @@ __device__ __forceinline__ void run_team(const BatchArgs& A, int block, float* p
     }
     wave_lds_sync();                                   // everything in LDS has been read
     // where entry (row k, this lane's column) of a tile goes
-    constexpr int TS = Y::tile;
-    float* tl = pool + (Y::FULL ? ks * N * N : slot * B * B);
-    constexpr int LD = Y::FULL ? N : B;
-    const int cj = Y::FULL ? body : i;
+    constexpr int TS = Y::NT == 3 ? Y::tile : 0;
+    float* const tl = pool + ks * Y::GB * N;
     int rows[B];
 #pragma unroll
     for (int k = 0; k < B; ++k)
-        rows[k] = (Y::FULL && NB > 1) ? G::rowmap()[br * B + k] : k;
-    if constexpr (Y::FULL && NB > 1) {                 // zeros between branches
-        constexpr int NM = OP == kFdGrad ? 3 : (OP == kIdGrad ? 2 : 1);
-        for (int e = lane; e < NM * TS / 4; e += 64)
+        rows[k] = (NB == 1 || G::in_order) ? br * B + k : G::rowmap()[br * B + k];
+    int own = br * B + i;
+    if constexpr (NB > 1 && !G::in_order)
+        own = G::rowmap()[own];
+    constexpr int NM = OP == kFdGrad ? 3 : (OP == kIdGrad ? 2 : 1);
+    if constexpr (B < N) {                             // zeros in the other branches' columns
+        for (int e = lane; e < (Y::NT == 3 ? NM : 1) * Y::tile / 4; e += 64)
             reinterpret_cast<float4*>(pool)[e] = float4{0.0f, 0.0f, 0.0f, 0.0f};
         wave_lds_sync();
     }
-    if constexpr (OP == kIdGrad) {
+    float* const dst[3] = {OP == kFdGrad ? A.o1 : A.o0, OP == kFdGrad ? A.o2 : A.o1, A.o3};
+    // matrix `mat` is in its tile
+    const auto tile_done = [&](int mat) {
+        if constexpr (Y::NT == 3) {
+            if (mat == NM - 1) {
+                wave_lds_sync();
 #pragma unroll
-        for (int k = 0; k < B; ++k) {
-            tl[rows[k] * LD + cj] = cq[k];
-            tl[TS + rows[k] * LD + cj] = cqd[k];
+                for (int k = 0; k < NM; ++k)
+                    flush_tile<G>(dst[k], pool + k * TS, block, nv, lane);
+            }
+        } else {
+            wave_lds_sync();
+            flush_tile<G>(dst[mat], pool, block, nv, lane);
+            wave_lds_sync();
         }
-        wave_lds_sync();
-        flush_tiles<G, 2>(pool, A.o0, A.o1, nullptr, block, nv, lane);
+    };
+    const auto put_column = [&](int mat, const float (&x)[B], float sign) {
+#pragma unroll
+        for (int k = 0; k < B; ++k)
+            tl[mat * TS + rows[k] * N + body] = sign * x[k];
+        tile_done(mat);
+    };
+    if constexpr (OP == kIdGrad) {
+        put_column(0, cq, 1.0f);
+        put_column(1, cqd, 1.0f);
         return;
     }
     if constexpr (kMass) {
@@ -674,27 +795,17 @@ __device__ __forceinline__ void run_team(const BatchArgs& A, int block, float* p
 #pragma unroll
         for (int k = 0; k < B; ++k) {
             if (k <= i) {
-                tl[rows[k] * LD + cj] = mc[k];
-                tl[cj * LD + rows[k]] = mc[k];
+                tl[rows[k] * N + body] = mc[k];
+                tl[own * N + rows[k] + rows_before<G>(rows[k])] = mc[k];
             }
         }
-    }
-    if constexpr (OP == kMinv) {
-        wave_lds_sync();
-        flush_tiles<G, 1>(pool, A.o0, nullptr, nullptr, block, nv, lane);
-        return;
+        tile_done(0);
     }
     if constexpr (OP == kFdGrad) {
         gridq::ltl_solve<S>(Lf, dinv, cq);
-#pragma unroll
-        for (int k = 0; k < B; ++k)
-            tl[TS + rows[k] * LD + cj] = -cq[k];
+        put_column(1, cq, -1.0f);
         gridq::ltl_solve<S>(Lf, dinv, cqd);
-#pragma unroll
-        for (int k = 0; k < B; ++k)
-            tl[2 * TS + rows[k] * LD + cj] = -cqd[k];
-        wave_lds_sync();
-        flush_tiles<G, 3>(pool, A.o1, A.o2, A.o3, block, nv, lane);
+        put_column(2, cqd, -1.0f);
     }
 }
 
