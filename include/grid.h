@@ -479,15 +479,17 @@ grid_status grid_fd_vjp_adjoint(grid_model m, int32_t N, const float* q, const f
 
 /* ------------------------------------------------------------------ autotuning
  *
- * The fused kernel exists in eight builds, which share four kernels. Build 0 spreads each spatial
+ * The fused kernel exists in eight builds, which share five kernels. Build 0 spreads each spatial
  * vector over the four lanes of a quad and gives every derivative column its own quad (few
  * instructions per lane: low latency). Build 4 is build 0 split over three roles on different
  * wavefronts of a workgroup (RNEA and dtau/du at qdd = 0; M, qdd and the qdd-dependent part of
  * dtau/dq; M^-1), the shortest dependency chain. Build 5 gives each (knot, branch) problem one
  * lane (no repeated work: the fewest instructions per knot, the longest latency). Build 1 gives
- * each body of a problem one lane, so that a wavefront holds several problems, while that takes
- * at most two wavefronts per SIMD, and runs build 5's kernel beyond. Builds 2, 3 and 6 are the
- * same as build 1 and build 7 the same as build 5 (indices that tables may hold).
+ * each body of a problem one lane, so that a wavefront holds several problems, up to a batch
+ * size that depends on the longest branch (none for branches of up to 4 bodies), and one
+ * lane per problem beyond. One lane per problem runs as two wavefronts with half of the outputs
+ * each while every one of them has a SIMD to itself, except in build 7. Builds 2, 3 and 6 are the
+ * same as build 1 (indices that tables may hold).
  * A robot with a base branch of more than 8 bodies runs one lane per body as every build but 4,
  * and as build 4 for batches of more than 256 knots (its long branch does not fit one lane, and
  * the three-role kernel gives it a workgroup per knot).

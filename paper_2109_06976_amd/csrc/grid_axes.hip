@@ -32,15 +32,19 @@ struct BatchArgs {
     int nknots;
     const float* q;
     const float* qd;      // unused by M^-1
-    const float* u;       // tau (dFD, FD), qdd (dID, VJP), unused (M^-1)
+    const float* u;       // tau (dFD, FD), qdd (ID, dID, VJP), unused (M^-1)
     const float* u2;      // g (VJP)
-    float* o0;            // qdd (dFD, FD), M^-1 (M^-1), dtau/dq (dID), qbar (VJP)
+    float* o0;            // qdd (dFD, FD), tau (ID), M^-1 (M^-1), dtau/dq (dID), qbar (VJP)
     float* o1;            // M^-1 (dFD), dtau/dqd (dID), qdbar (VJP)
     float* o2;            // dqdd/dq (dFD), taubar (VJP)
     float* o3;            // dqdd/dqd (dFD)
 };
 
-enum Op : int { kFdGrad = 0, kFd = 1, kMinv = 2, kIdGrad = 3, kVjp = 4 };
+// ..Q, ..V: half of dID (dtau/dq; dtau/dqd) and of dFD (qdd and dqdd/dq; M^-1 and dqdd/dqd)
+enum Op : int {
+    kFdGrad = 0, kFd = 1, kMinv = 2, kIdGrad = 3, kVjp = 4, kId = 5,
+    kIdGradQ = 6, kIdGradV = 7, kFdGradQ = 8, kFdGradV = 9
+};
 
 // 16 bytes at a 4-byte aligned address (global memory takes them at any dword)
 struct __attribute__((packed, aligned(4))) F4 {

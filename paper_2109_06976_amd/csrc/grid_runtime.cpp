@@ -262,7 +262,32 @@ int fused_variant_for(grid_model m, int32_t N)
     return kVariantTeam;
 }
 
-// The build whose kernel runs a batch of N knots under the index `variant`
+// One lane per body, or one per problem? The latter issues a third of the instructions but takes
+// the same time for 64 knots as for 16384, longer the longer the branch: the former while its
+// wavefronts are at most two per compute unit for each body of the longest branch beyond four
+// (dFD, by body and by problem: chain of 4 at 1024 knots 5.8 and 5.4 us; of 5 at 4096, 1.3 per
+// unit, 7.4 and 7.2; of 6 at 8192, 3.2 per unit, 8.8 and 9.4, at 16384 11.1 and 9.9; of 7 at 8192,
+// 3.6 per unit, 10.2 and 12.1, at 16384 12.9 both; of 8 at 16384, 8 per unit, 14.7 and 18.6, at
+// 32768 27.8 and 19.9; quad12, branches of 3, at 4096 6.8 and 6.1; dID of a chain of 7 at 8192 7.6
+// and 8.4, at 16384 9.8 and 8.9)
+static bool lane_per_body(grid_model m, int64_t N)
+{
+    int longest = 0;
+    for (const BranchShape& s : m->topo.shapes)
+        longest = std::max(longest, s.B);
+    return longest > 8 || (longest > 4 && workgroups_team(m->topo, N) <=
+                                              2 * (int64_t)m->compute_units * (longest - 4));
+}
+
+// One lane per problem: two wavefronts with half of the outputs each while there is a SIMD for
+// every one of them (figures at the kernels)
+static bool in_halves(grid_model m, int64_t N)
+{
+    return 2 * workgroups_serial(m->topo, N) <= 4 * (int64_t)m->compute_units;
+}
+
+// The build whose kernel runs a batch of N knots under the index `variant`; kVariantSerial2 stands
+// for one lane per problem in halves
 int kernel_of(grid_model m, int variant, int32_t N)
 {
     if (long_branch(m->topo)) {
@@ -273,16 +298,14 @@ int kernel_of(grid_model m, int variant, int32_t N)
     case kVariantQuad:
     case kVariantPipe:
         return variant;
-    case kVariantSerial:
     case kVariantSerial2:
         return kVariantSerial;
+    case kVariantSerial:
+        return in_halves(m, N) ? kVariantSerial2 : kVariantSerial;
     default:
-        // One lane per body while its wavefronts are at most two per SIMD; beyond, one lane per
-        // problem, which issues a third of the instructions but takes as long for 64 knots as for
-        // 65536 (chain7 at 16384 knots, 1.8 wavefronts per SIMD: 14.7 and 17.3 us, at 32768 25.4
-        // and 18.7; quad12 at 8192, 1.6 per SIMD: 8.9 both, at 16384 14.5 and 10.2)
-        return workgroups_team(m->topo, N) <= 8 * (int64_t)m->compute_units ? kVariantTeam
-                                                                            : kVariantSerial;
+        return lane_per_body(m, N) ? kVariantTeam
+               : in_halves(m, N)   ? kVariantSerial2
+                                   : kVariantSerial;
     }
 }
 
@@ -306,6 +329,9 @@ grid_status launch_fused_variant(grid_model m, int variant, int32_t N, const flo
         break;
     case kVariantTeam:
         blocks = workgroups_team(m->topo, N);
+        break;
+    case kVariantSerial2:
+        blocks = 2 * workgroups_serial(m->topo, N);
         break;
     default:
         blocks = workgroups_serial(m->topo, N);
@@ -597,12 +623,13 @@ grid_status grid_model_create(const grid_model_desc* desc, int32_t device, uint3
                                            "grid_stage_drnea", "grid_stage_fdgrad"};
     static const char* const kVariants[kNumVariants] = {
         "grid_fdgrad_quad", "grid_fdgrad_team", nullptr, nullptr,
-        "grid_fdgrad_pipe", "grid_fdgrad_serial", nullptr, nullptr};
+        "grid_fdgrad_pipe", "grid_fdgrad_serial", nullptr, "grid_fdgrad_serial_halves"};
     m->compute_units = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
     hipError_t e = hipModuleLoadData(&m->module, code.data());
     for (int k = 0; k < kNumVariants && e == hipSuccess; ++k)
-        // build 4 lives in the pipe module alone; only the kernels that kernel_of names exist
-        if (k != kVariantPipe && kernel_of(m, k, 1) == k)
+        // build 4 lives in the pipe module alone; a long branch has neither the quad kernel nor
+        // those with one lane per problem
+        if (kVariants[k] && k != kVariantPipe && (k == kVariantTeam || !long_branch(m->topo)))
             e = hipModuleGetFunction(&m->fused_variant[k], m->module, kVariants[k]);
     static const char* const kOps[kNumOps] = {"grid_op_id", "grid_op_fd", "grid_op_minv",
                                               "grid_op_idgrad", "grid_op_vjp"};
@@ -614,11 +641,13 @@ grid_status grid_model_create(const grid_model_desc* desc, int32_t device, uint3
     for (int k = 0; k < kNumOps && e == hipSuccess; ++k)
         if (kTeamOps[k])
             e = hipModuleGetFunction(&m->team_op[k], m->module, kTeamOps[k]);
-    static const char* const kSerialOps[kNumOps] = {nullptr, "grid_serial_fd", "grid_serial_minv",
+    static const char* const kSerialOps[kNumOps] = {"grid_serial_id", "grid_serial_fd", "grid_serial_minv",
                                                     "grid_serial_idgrad", "grid_serial_vjp"};
     for (int k = 0; k < kNumOps && e == hipSuccess; ++k)
         if (kSerialOps[k] && !long_branch(m->topo))
             e = hipModuleGetFunction(&m->serial_op[k], m->module, kSerialOps[k]);
+    if (e == hipSuccess && !long_branch(m->topo))
+        e = hipModuleGetFunction(&m->idgrad_halves, m->module, "grid_serial_idgrad_halves");
     for (int k = 0; k < 5 && e == hipSuccess; ++k)
         e = hipModuleGetFunction(&m->stage[k], m->module, kStages[k]);
     static const char* const kMinvRoutes[2] = {"grid_minv_serial", "grid_minv_direct"};
@@ -723,20 +752,25 @@ static grid_status launch_op(grid_model m, int op, int32_t N, const float* q, co
     const int64_t blocks = workgroups_op(m->topo, N, op);
     const int waves = op == kOpIdGrad ? m->topo.waves : 1;
     // The quad layout's quads repeat the shared sweeps: beyond two wavefronts of it per SIMD the
-    // batch forms take over. FD and M^-1 then run one lane per problem (chain7 FD at 4096 knots, two
-    // per SIMD: 6.1 us, 5.4 in that form, M^-1 4.2 and 4.7, at 8192 6.0 and 4.8). dID and the VJP
-    // first run one lane per body (chain7 dID at 4096 knots, four per SIMD: 11.9 and 7.9; 10.5 with
-    // one lane per problem), up to one and a half wavefronts of that per SIMD (at 32768 18.8 and
-    // 12.0; quad12 at 8192, 1.6 per SIMD: dID 6.6 both, VJP 5.6 and 4.6). A long branch runs one
-    // lane per body at every size (humanoid30 at 16 knots: FD 9.6 us in the quad layout, 8.6).
-    const int64_t cu = m->compute_units;
-    if (m->team_op[op] && (long_branch(m->topo) || blocks * waves > 8 * cu)) {
-        const int64_t team = workgroups_team(m->topo, N);
-        const bool one_lane = m->serial_op[op] && (op == kOpFd || op == kOpMinv || team > 6 * cu);
-        HIP_TRY(hipModuleLaunchKernel(
-            one_lane ? m->serial_op[op] : m->team_op[op],
-            (unsigned)(one_lane ? workgroups_serial(m->topo, N) : team), 1, 1, 64u, 1, 1, 0,
-            (hipStream_t)stream, params, nullptr));
+    // batch forms take over. ID, FD and M^-1 then run one lane per problem (chain7 FD at 4096
+    // knots, two per SIMD: 6.1 us, 5.4 in that form, M^-1 4.2 and 4.7, at 8192 6.0 and 4.8; ID
+    // beside its kernel), dID and the VJP one lane per body first. A long branch runs one lane per
+    // body at every size (humanoid30 at 16 knots: FD 9.6 us in the quad layout, 8.6), but for ID
+    // (at 512 and 4096 knots 5.7 and 5.9 us in the quad layout, 5.2 and 7.1).
+    const bool longb = long_branch(m->topo);
+    if (blocks * waves > 8 * (int64_t)m->compute_units ? m->team_op[op] || m->serial_op[op]
+                                                       : longb && m->team_op[op]) {
+        hipFunction_t fn = m->serial_op[op];
+        int64_t count = longb ? 0 : workgroups_serial(m->topo, N);
+        if (longb || ((op == kOpIdGrad || op == kOpVjp) && lane_per_body(m, N))) {
+            fn = m->team_op[op];
+            count = workgroups_team(m->topo, N);
+        } else if (op == kOpIdGrad && in_halves(m, N)) {
+            fn = m->idgrad_halves;
+            count *= 2;
+        }
+        HIP_TRY(hipModuleLaunchKernel(fn, (unsigned)count, 1, 1, 64u, 1, 1, 0,
+                                      (hipStream_t)stream, params, nullptr));
         return GRID_OK;
     }
     HIP_TRY(hipModuleLaunchKernel(m->op[op], (unsigned)blocks, 1, 1, 64u * (unsigned)waves, 1, 1, 0,

@@ -1,4 +1,4 @@
-// One lane per (knot, branch) problem (gfx950): grid_fdgrad_serial, the batch forms of FD, M^-1,
+// One lane per (knot, branch) problem (gfx950): grid_fdgrad_serial, the batch forms of ID, FD, M^-1,
 // dID and the adjoint VJP, and M^-1 alone by two routes.
 //
 // Every lane of a wavefront works on the same branch of the same robot for a different knot,
@@ -22,12 +22,8 @@
 
 namespace grids {
 
-using grid::crf_mv;
-using grid::cross_S;
-using grid::inertia_mv;
 using grid::kConstStride;
 using grid::prismatic;
-using grid::s_crf;
 using grid::s_index;
 using grid::x_mv;
 using grid::xt_fv;
@@ -286,13 +282,14 @@ __device__ __forceinline__ void flush_blocks(float* d0, float* d1, const float* 
 // computed once), and what a lane parks while it factors M and writes M^-1: 16 floats for every
 // body but the first. Without parking a branch of 7 bodies holds 330 floats there, which move
 // through the accumulation registers and scratch memory (65536 knots 21.4 us, 20.2 with it); one
-// of 3 bodies has room (7.0 us at 128 knots, 7.7 with it)
+// of 3 bodies has room (7.0 us at 128 knots, 7.7 with it), and so have the halves of dFD (7 bodies
+// at 32768 knots 14.3, 22.8 with it: the LDS then leaves room for too few wavefronts)
 template <class I, int OP>
 struct SerialLds {
     static constexpr int B = I::S::B;
     static constexpr bool kPark = B > 4 && (OP == gridv::kFdGrad || OP == gridv::kVjp);
-    static constexpr bool kTiles = OP != gridv::kFd && OP != gridv::kVjp;
-    static constexpr int NT = !kTiles ? 0 : (B > 4 || OP == gridv::kMinv ? 1 : 2);
+    static constexpr bool kTiles = OP != gridv::kFd && OP != gridv::kVjp && OP != gridv::kId;
+    static constexpr int NT = !kTiles ? 0 : (B <= 4 && (OP == gridv::kFdGrad || OP == gridv::kIdGrad) ? 2 : 1);
     static constexpr int tile = 64 * B * B;
     static constexpr int floats = NT * tile + (kPark ? 16 * 64 * (B - 1) : 0) + 4;
 };
@@ -352,9 +349,13 @@ __device__ __forceinline__ void run_serial(const gridv::BatchArgs& A, int block,
     constexpr int N = I::N;
     using Y = SerialLds<I, OP>;
     constexpr bool kVel = OP != kMinv;
-    constexpr bool kMass = OP != kIdGrad;
-    constexpr bool kBias = OP == kFdGrad || OP == kFd;
-    constexpr bool kDer = OP != kFd && OP != kMinv;
+    constexpr bool kIdDer = OP == kIdGrad || OP == kIdGradQ || OP == kIdGradV;
+    constexpr bool kMass = !kIdDer && OP != kId;
+    constexpr bool kFdDer = OP == kFdGrad || OP == kFdGradQ || OP == kFdGradV;
+    constexpr bool kQ = OP != kIdGradV && OP != kFdGradV;   // dq's matrix is wanted, dqd's
+    constexpr bool kV = OP != kIdGradQ && OP != kFdGradQ;
+    constexpr bool kBias = OP == kFdGrad || OP == kFdGradQ || OP == kFd;
+    constexpr bool kDer = kIdDer || kFdDer || OP == kVjp;
     constexpr bool kPark = Y::kPark;
     const int lane = (int)threadIdx.x;
     const int kraw = block * 64 + lane;
@@ -458,7 +459,7 @@ __device__ __forceinline__ void run_serial(const gridv::BatchArgs& A, int block,
                     park[64 * (4 * i - 1)] = float4{psd[i].l.x, psd[i].l.y, psd[i].l.z, qd[i]};
                 }
             }
-            if constexpr (kBias) {                      // f = I a + v x* (I v)
+            if constexpr (kBias || OP == kId) {         // f = I a + v x* (I v)
                 const Sym J = second_to_inertia(P[i]);
                 const Six Ia = inertia(mass_of(i), h[i], J, a[i]);
                 const Six Iv = inertia(mass_of(i), h[i], J, v[i]);
@@ -466,6 +467,18 @@ __device__ __forceinline__ void run_serial(const gridv::BatchArgs& A, int block,
                            Ia.l + cross(v[i].a, Iv.l)};
             }
         });
+    }
+
+    if constexpr (OP == kId) {
+        static_for<B>([&](auto ii) {
+            constexpr int i = B - 1 - decltype(ii)::v;
+            constexpr int p = S::parent[i];
+            if (valid)
+                A.o0[vbase + I::body[i]] = dot_S(i, F[i]);
+            if constexpr (p >= 0)
+                F[p] = Six{F[p].a + F[i].a + cross(r[i], F[i].l), F[p].l + F[i].l};
+        });
+        return;
     }
 
     // ------------------------------------------------------------ inward: M by the subtrees'
@@ -518,7 +531,7 @@ __device__ __forceinline__ void run_serial(const gridv::BatchArgs& A, int block,
                 x[i] = A.u2[vbase + I::body[i]];
         }
         gridq::ltl_factor<S>(Lf, dinv);
-        if constexpr (kVel) {
+        if constexpr (kBias || OP == kVjp) {
             gridq::ltl_solve<S>(Lf, dinv, x);           // qdd, or taubar
             if (valid) {
                 float* out = OP == kVjp ? A.o2 : A.o0;
@@ -531,7 +544,7 @@ __device__ __forceinline__ void run_serial(const gridv::BatchArgs& A, int block,
     if constexpr (OP == kFd)
         return;
 
-    if constexpr (OP == kFdGrad || OP == kMinv) {
+    if constexpr (OP == kFdGrad || OP == kFdGradV || OP == kMinv) {
         // M^-1: entries (i, j), i <= j, to both mirrored positions (exactly symmetric)
         static_for<B>([&](auto jj) {
             constexpr int j = decltype(jj)::v;
@@ -551,6 +564,8 @@ __device__ __forceinline__ void run_serial(const gridv::BatchArgs& A, int block,
         if constexpr (OP == kMinv)
             return;
         wave_lds_sync();
+    }
+    if constexpr (OP == kFdGrad || OP == kFdGradQ) {
         // the parents' accelerations at qdd
         Six d[B];
         static_for<B>([&](auto ii) {
@@ -588,7 +603,7 @@ __device__ __forceinline__ void run_serial(const gridv::BatchArgs& A, int block,
                 psd[i] = Six{{c.y, c.z, c.w}, {d.x, d.y, d.z}};
                 qd[i] = d.w;
             }
-            const float qdd = OP == kFdGrad ? x[i] : uu[i];
+            const float qdd = kFdDer ? (kBias ? x[i] : 0.0f) : uu[i];
             const Six v = add_S(i, vl[i], qd[i]);
             const Sym J = second_to_inertia(P[i]);
             K[i] = momentum_moment(v, h[i], P[i]);
@@ -686,21 +701,27 @@ __device__ __forceinline__ void run_serial(const gridv::BatchArgs& A, int block,
             }
             return;
         }
-        float* const o0 = (OP == kFdGrad ? A.o2 : A.o0) + mb;
-        float* const o1 = (OP == kFdGrad ? A.o3 : A.o1) + mb;
+        float* const o0 = (kFdDer ? A.o2 : A.o0) + mb;
+        float* const o1 = (kFdDer ? A.o3 : A.o1) + mb;
         const auto columns = [&](float (&D)[B][B], float* to) {
             static_for<B>([&](auto jj) {
                 constexpr int j = decltype(jj)::v;
                 constexpr unsigned long long m = relatives<S>(j);
-                if constexpr (OP == kFdGrad)
+                if constexpr (kFdDer)
                     solve_masked<S, m, B - 1>(Lf, dinv, D[j]);
 #pragma unroll
                 for (int i = 0; i < B; ++i)
-                    to[i * B + j] = OP == kFdGrad ? -D[j][i] : (((m >> i) & 1ull) ? D[j][i] : 0.0f);
+                    to[i * B + j] = kFdDer ? -D[j][i] : (((m >> i) & 1ull) ? D[j][i] : 0.0f);
             });
         };
-        columns(Dq, mine);
-        if constexpr (Y::NT == 2) {
+        if constexpr (kQ)
+            columns(Dq, mine);
+        if constexpr (!kQ || !kV) {
+            if constexpr (kV)
+                columns(Dv, mine);
+            wave_lds_sync();
+            flush_blocks<I, 1>(kQ ? o0 : o1, nullptr, pool, nullptr, nv, lane);
+        } else if constexpr (Y::NT == 2) {
             columns(Dv, mine + Y::tile);
             wave_lds_sync();
             flush_blocks<I, 2>(o0, o1, pool, pool + Y::tile, nv, lane);
@@ -978,6 +999,20 @@ extern "C" __global__ void __launch_bounds__(64) grid_fdgrad_serial(grid::Args a
     grid_dispatch_s<gridv::kFdGrad>(a, (int)blockIdx.x);
 }
 
+// dFD by two wavefronts: qdd and dqdd/dq; M^-1 and dqdd/dqd. Each repeats the axes, the inertias
+// and the factor, 27 % more instructions in all, but runs 0.6 of them: chain7 at 32768 knots 18.7
+// us by one wavefront, 14.3 by two, at 65536 20.2 and 24.0
+extern "C" __global__ void __launch_bounds__(64) grid_fdgrad_serial_halves(grid::Args args)
+{
+    const gridv::BatchArgs a{args.nknots, args.q, args.qd, args.tau, nullptr,
+                        args.qdd, args.Minv, args.dqdd_dq, args.dqdd_dqd};
+    const int half = (int)gridDim.x / 2, b = (int)blockIdx.x;
+    if (b < half)
+        grid_dispatch_s<gridv::kFdGradQ>(a, b);
+    else
+        grid_dispatch_s<gridv::kFdGradV>(a, b - half);
+}
+
 // the standalone algorithms in the same layout (their arguments as gridq::OpArgs)
 struct SerialOpArgs {
     int nknots;
@@ -1002,6 +1037,28 @@ extern "C" __global__ void __launch_bounds__(64) grid_serial_idgrad(SerialOpArgs
 {
     const gridv::BatchArgs a{x.nknots, x.q, x.qd, x.u, nullptr, x.out0, x.out1, nullptr, nullptr};
     grid_dispatch_s<gridv::kIdGrad>(a, (int)blockIdx.x);
+}
+
+// dID by two wavefronts, one matrix each: chain7 at 32768 knots 11.9 us by one, 9.8 by two, at
+// 65536 13.5 and 16.4
+extern "C" __global__ void __launch_bounds__(64) grid_serial_idgrad_halves(SerialOpArgs x)
+{
+    const int half = (int)gridDim.x / 2, b = (int)blockIdx.x;
+    if (b < half) {
+        const gridv::BatchArgs a{x.nknots, x.q, x.qd, x.u, nullptr, x.out0, nullptr, nullptr, nullptr};
+        grid_dispatch_s<gridv::kIdGradQ>(a, b);
+    } else {
+        const gridv::BatchArgs a{x.nknots, x.q, x.qd, x.u, nullptr, nullptr, x.out1, nullptr, nullptr};
+        grid_dispatch_s<gridv::kIdGradV>(a, b - half);
+    }
+}
+
+// against the quad layout's (grid_ops.hip): chain7 at 32768 and 65536 knots 4.2 and 6.4 us there,
+// 4.3 and 4.5 here; quad12 at 8192, 16384 and 32768 3.0 / 3.7 / 5.3 and 3.2 / 3.1 / 3.2
+extern "C" __global__ void __launch_bounds__(64) grid_serial_id(SerialOpArgs x)
+{
+    const gridv::BatchArgs a{x.nknots, x.q, x.qd, x.u, nullptr, x.out0, nullptr, nullptr, nullptr};
+    grid_dispatch_s<gridv::kId>(a, (int)blockIdx.x);
 }
 
 extern "C" __global__ void __launch_bounds__(64) grid_serial_vjp(SerialOpArgs x)
