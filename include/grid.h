@@ -479,7 +479,7 @@ grid_status grid_fd_vjp_adjoint(grid_model m, int32_t N, const float* q, const f
 
 /* ------------------------------------------------------------------ autotuning
  *
- * The fused kernel exists in eight builds, which share five kernels. Build 0 spreads each spatial
+ * The fused kernel exists in eight builds, which share six kernels. Build 0 spreads each spatial
  * vector over the four lanes of a quad and gives every derivative column its own quad (few
  * instructions per lane: low latency). Build 4 is build 0 split over three roles on different
  * wavefronts of a workgroup (RNEA and dtau/du at qdd = 0; M, qdd and the qdd-dependent part of
@@ -487,12 +487,12 @@ grid_status grid_fd_vjp_adjoint(grid_model m, int32_t N, const float* q, const f
  * lane (no repeated work: the fewest instructions per knot, the longest latency). Build 1 gives
  * each body of a problem one lane, so that a wavefront holds several problems, up to a batch
  * size that depends on the longest branch (none for branches of up to 4 bodies), and one
- * lane per problem beyond. One lane per problem runs as two wavefronts with half of the outputs
- * each while every one of them has a SIMD to itself, except in build 7. Builds 2, 3 and 6 are the
- * same as build 1 (indices that tables may hold).
+ * lane per problem beyond. Either runs as two wavefronts with half of the outputs each while the
+ * device holds them side by side. Builds 3 and 6 are the same as build 1 (indices that tables may
+ * hold); build 2 is one lane per body and build 7 one lane per problem, never in halves.
  * A robot with a base branch of more than 8 bodies runs one lane per body as every build but 4,
- * and as build 4 for batches of more than 256 knots (its long branch does not fit one lane, and
- * the three-role kernel gives it a workgroup per knot).
+ * and as build 4 for batches of more than 8 knots (its long branch does not fit one lane, and the
+ * three-role kernel gives it a workgroup per knot).
  * Untuned, a batch runs build 4 while its wavefronts fit one per SIMD of the device, build 0
  * while its fit, build 1 beyond, build 6 from 64 knots per compute unit and build 5 from 128,
  * except for a robot with a base branch of more than 8 bodies: build 4 up to 4096 knots, build 6

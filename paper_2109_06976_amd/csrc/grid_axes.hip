@@ -46,6 +46,14 @@ enum Op : int {
     kIdGradQ = 6, kIdGradV = 7, kFdGradQ = 8, kFdGradV = 9
 };
 
+// a workgroup's LDS, one array for all the calls of a kernel that want the same size
+template <int FLOATS>
+__device__ __forceinline__ float* lds()
+{
+    __shared__ __align__(16) float p[FLOATS];
+    return p;
+}
+
 // 16 bytes at a 4-byte aligned address (global memory takes them at any dword)
 struct __attribute__((packed, aligned(4))) F4 {
     float x, y, z, w;

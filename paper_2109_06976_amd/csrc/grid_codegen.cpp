@@ -505,8 +505,8 @@ static void emit_groups(std::ostringstream& os, const Topology& t, const std::ve
 // kernel arguments are loaded. (A workgroup past the end would still only recompute the last
 // knot and store nothing: every store checks its knot.) `@` in per_block and call stands for
 // the branch's Inst, or for a group of branches (`type` Group).
-// `pool`, when given, is an expression in @ for the LDS floats one branch needs: the dispatch
-// then holds one array of the largest such size, `pool`, that every branch's call shares
+// `pool`, when given, is an expression in @ for the LDS floats one branch needs: every branch's
+// call then shares one array of the largest such size
 static void emit_dispatch(std::ostringstream& os, const char* type, size_t count,
                           const char* sig, const std::string& per_block,
                           const std::string& call, const std::string& pool = "")
@@ -519,10 +519,10 @@ static void emit_dispatch(std::ostringstream& os, const char* type, size_t count
     };
     os << sig << "\n{\n    int b = block;\n";
     if (!pool.empty()) {
-        os << "    __shared__ __align__(16) float pool[grids::cmax(";
+        os << "    float* const pool = gridv::lds<grids::cmax(";
         for (size_t k = 0; k < count; ++k)
             os << (k ? ", " : "") << inst(k, pool);
-        os << ")];\n";
+        os << ")>();\n";
     }
     for (size_t k = 0; k < count; ++k) {
         auto sub = [&](const std::string& x) { return inst(k, x); };

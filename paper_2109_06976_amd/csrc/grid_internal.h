@@ -15,11 +15,12 @@ namespace grid_impl {
 constexpr int kMaxBodies = 32;      // the 2B derivative columns of a branch fit one wavefront
 constexpr int kConstStride = 24;    // floats of device constants per body
 
-// builds of the fused kernel (grid.h). Five kernels: quad layout, one lane per body, quad layout
-// in three roles, one lane per (knot, branch) problem and the same in two halves; kernel_of says
-// which of them an index runs
+// builds of the fused kernel (grid.h). Six kernels: quad layout, one lane per body and the same in
+// two halves, quad layout in three roles, one lane per (knot, branch) problem and the same in two
+// halves; kernel_of says which of them an index runs
 constexpr int kVariantQuad = 0;
 constexpr int kVariantTeam = 1;
+constexpr int kVariantTeam2 = 2;
 constexpr int kVariantPipe = 4;
 constexpr int kVariantSerial = 5;
 constexpr int kVariantSerial4 = 6;
@@ -186,7 +187,7 @@ struct grid_model_s {
     hipFunction_t op[grid_impl::kNumOps] = {};                    // see kOpId
     hipFunction_t team_op[grid_impl::kNumOps] = {};   // their forms with one lane per body,
     hipFunction_t serial_op[grid_impl::kNumOps] = {}; // and with one lane per problem
-    hipFunction_t idgrad_halves = nullptr;            // dID so, by two wavefronts
+    hipFunction_t serial_idgrad_halves = nullptr;     // dID so, by two wavefronts
     hipFunction_t minv_route[2] = {};   // M^-1 one lane per knot: L^T L, direct
     std::vector<std::pair<int32_t, int>> tuned;   // (largest N, variant), ascending N
     hipModule_t module = nullptr;

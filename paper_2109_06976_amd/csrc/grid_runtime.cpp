@@ -232,9 +232,10 @@ grid_status launch(hipFunction_t fn, unsigned blocks, unsigned threads, int32_t 
 
 namespace grid_impl {
 
-// The largest batch of a robot with a long branch that the three-role kernel runs faster than
-// one lane per body (humanoid30, see kernel_of)
-constexpr int kPipeLongKnots = 256;
+// The largest batch of a robot with a long branch that the three-role kernel runs as fast as one
+// lane per body in halves (humanoid30 at 1, 4, 16, 128 and 256 knots 11.4 / 11.5 / 11.7 / 12.0 / 16.2
+// us, and 11.5 / 11.5 / 11.5 / 11.5 / 11.9: a quarter of the wavefronts)
+constexpr int kPipeLongKnots = 8;
 
 int fused_variant_for(grid_model m, int32_t N)
 {
@@ -279,33 +280,42 @@ static bool lane_per_body(grid_model m, int64_t N)
                                               2 * (int64_t)m->compute_units * (longest - 4));
 }
 
-// One lane per problem: two wavefronts with half of the outputs each while there is a SIMD for
-// every one of them (figures at the kernels)
-static bool in_halves(grid_model m, int64_t N)
+// Two wavefronts with half of the outputs each: one lane per problem while there is a SIMD for
+// every one of them (a long branch takes all of a SIMD's registers), one lane per body while there
+// are at most two per SIMD (figures at the kernels)
+static bool problems_in_halves(grid_model m, int64_t N)
 {
     return 2 * workgroups_serial(m->topo, N) <= 4 * (int64_t)m->compute_units;
 }
+static bool bodies_in_halves(grid_model m, int64_t N)
+{
+    return 2 * workgroups_team(m->topo, N) <= 8 * (int64_t)m->compute_units;
+}
 
-// The build whose kernel runs a batch of N knots under the index `variant`; kVariantSerial2 stands
-// for one lane per problem in halves
+// The build whose kernel runs a batch of N knots under the index `variant`; kVariantTeam2 and
+// kVariantSerial2 stand for the halves here
 int kernel_of(grid_model m, int variant, int32_t N)
 {
+    const int team = bodies_in_halves(m, N) ? kVariantTeam2 : kVariantTeam;
+    const int serial = problems_in_halves(m, N) ? kVariantSerial2 : kVariantSerial;
     if (long_branch(m->topo)) {
         // a long branch: a lane does not hold it, and the three-role kernel gives it a workgroup
-        return variant == kVariantPipe && N <= kPipeLongKnots ? kVariantPipe : kVariantTeam;
+        if (variant == kVariantPipe && N <= kPipeLongKnots)
+            return kVariantPipe;
+        return variant == kVariantTeam2 ? kVariantTeam : team;
     }
     switch (variant) {
     case kVariantQuad:
     case kVariantPipe:
         return variant;
+    case kVariantTeam2:
+        return kVariantTeam;
+    case kVariantSerial:
+        return serial;
     case kVariantSerial2:
         return kVariantSerial;
-    case kVariantSerial:
-        return in_halves(m, N) ? kVariantSerial2 : kVariantSerial;
     default:
-        return lane_per_body(m, N) ? kVariantTeam
-               : in_halves(m, N)   ? kVariantSerial2
-                                   : kVariantSerial;
+        return lane_per_body(m, N) ? team : serial;
     }
 }
 
@@ -329,6 +339,9 @@ grid_status launch_fused_variant(grid_model m, int variant, int32_t N, const flo
         break;
     case kVariantTeam:
         blocks = workgroups_team(m->topo, N);
+        break;
+    case kVariantTeam2:
+        blocks = 2 * workgroups_team(m->topo, N);
         break;
     case kVariantSerial2:
         blocks = 2 * workgroups_serial(m->topo, N);
@@ -622,14 +635,15 @@ grid_status grid_model_create(const grid_model_desc* desc, int32_t device, uint3
     static const char* const kStages[5] = {"grid_stage_rnea", "grid_stage_minv", "grid_stage_qdd",
                                            "grid_stage_drnea", "grid_stage_fdgrad"};
     static const char* const kVariants[kNumVariants] = {
-        "grid_fdgrad_quad", "grid_fdgrad_team", nullptr, nullptr,
+        "grid_fdgrad_quad", "grid_fdgrad_team", "grid_fdgrad_team_halves", nullptr,
         "grid_fdgrad_pipe", "grid_fdgrad_serial", nullptr, "grid_fdgrad_serial_halves"};
     m->compute_units = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
     hipError_t e = hipModuleLoadData(&m->module, code.data());
     for (int k = 0; k < kNumVariants && e == hipSuccess; ++k)
         // build 4 lives in the pipe module alone; a long branch has neither the quad kernel nor
         // those with one lane per problem
-        if (kVariants[k] && k != kVariantPipe && (k == kVariantTeam || !long_branch(m->topo)))
+        if (kVariants[k] && k != kVariantPipe &&
+            (k == kVariantTeam || k == kVariantTeam2 || !long_branch(m->topo)))
             e = hipModuleGetFunction(&m->fused_variant[k], m->module, kVariants[k]);
     static const char* const kOps[kNumOps] = {"grid_op_id", "grid_op_fd", "grid_op_minv",
                                               "grid_op_idgrad", "grid_op_vjp"};
@@ -647,7 +661,7 @@ grid_status grid_model_create(const grid_model_desc* desc, int32_t device, uint3
         if (kSerialOps[k] && !long_branch(m->topo))
             e = hipModuleGetFunction(&m->serial_op[k], m->module, kSerialOps[k]);
     if (e == hipSuccess && !long_branch(m->topo))
-        e = hipModuleGetFunction(&m->idgrad_halves, m->module, "grid_serial_idgrad_halves");
+        e = hipModuleGetFunction(&m->serial_idgrad_halves, m->module, "grid_serial_idgrad_halves");
     for (int k = 0; k < 5 && e == hipSuccess; ++k)
         e = hipModuleGetFunction(&m->stage[k], m->module, kStages[k]);
     static const char* const kMinvRoutes[2] = {"grid_minv_serial", "grid_minv_direct"};
@@ -760,15 +774,14 @@ static grid_status launch_op(grid_model m, int op, int32_t N, const float* q, co
     const bool longb = long_branch(m->topo);
     if (blocks * waves > 8 * (int64_t)m->compute_units ? m->team_op[op] || m->serial_op[op]
                                                        : longb && m->team_op[op]) {
-        hipFunction_t fn = m->serial_op[op];
-        int64_t count = longb ? 0 : workgroups_serial(m->topo, N);
-        if (longb || ((op == kOpIdGrad || op == kOpVjp) && lane_per_body(m, N))) {
-            fn = m->team_op[op];
-            count = workgroups_team(m->topo, N);
-        } else if (op == kOpIdGrad && in_halves(m, N)) {
-            fn = m->idgrad_halves;
-            count *= 2;
-        }
+        const bool body = longb || ((op == kOpIdGrad || op == kOpVjp) && lane_per_body(m, N));
+        // (dID with one lane per body does not gain: humanoid30 at 128 knots 9.0 and 8.3 us, at 2048
+        // 11.8 and 12.9)
+        const bool halves = op == kOpIdGrad && !body && problems_in_halves(m, N);
+        const int64_t count = body ? workgroups_team(m->topo, N)
+                                   : (halves ? 2 : 1) * workgroups_serial(m->topo, N);
+        hipFunction_t fn = body ? m->team_op[op]
+                                : (halves ? m->serial_idgrad_halves : m->serial_op[op]);
         HIP_TRY(hipModuleLaunchKernel(fn, (unsigned)count, 1, 1, 64u, 1, 1, 0,
                                       (hipStream_t)stream, params, nullptr));
         return GRID_OK;

@@ -13,10 +13,10 @@
 //
 // Bound by the latency of its chain of LDS exchanges up to a few wavefronts per SIMD, by VALU
 // issue beyond. humanoid30: 236 us per launch at 4096 knots and 648 at 16384 on the kernels it
-// took the place of, 28 and 82 here; chain7 at 4096 knots 11.4 and 10.7, quad12 7.8 and 6.8.
+// took the place of, 24.0 and 70 here; chain7 at 4096 knots 11.4 and 9.2, quad12 7.8 and 6.8.
 // FD / M^-1 / dID / VJP against the quad layout's (grid_ops.hip): humanoid30 at 4096 knots 46 /
-// 31 / 192 / 68 and 12 / 12 / 18 / 18 us, at 128 9.8 / 9.7 / 11.3 / 14.1 and 8.7 / 8.0 / 11.1 /
-// 12.0; chain7 at 32768 29 / 16 / 77 / 53 and 13 / 11 / 19 / 19.
+// 31 / 192 / 68 and 11 / 11 / 15 / 16 us, at 128 9.8 / 9.7 / 11.3 / 14.1 and 7.4 / 6.8 / 9.1 /
+// 10.4; chain7 at 32768 29 / 16 / 77 / 53 and 12 / 10 / 17 / 17.
 
 namespace gridt {
 
@@ -226,8 +226,11 @@ __device__ __forceinline__ void run_team(const BatchArgs& A, int block, float* p
     constexpr int DZ = NE - 1;                         // the entry of zeros
     constexpr bool kVel = OP != kMinv;
     constexpr bool kMass = OP != kIdGrad;
-    constexpr bool kBias = OP == kFdGrad || OP == kFd;
-    constexpr bool kDer = OP == kFdGrad || OP == kIdGrad || OP == kVjp;
+    constexpr bool kFdDer = OP == kFdGrad || OP == kFdGradQ || OP == kFdGradV;
+    constexpr bool kBias = OP == kFdGrad || OP == kFdGradQ || OP == kFd;
+    constexpr bool kDer = kFdDer || OP == kIdGrad || OP == kVjp;
+    constexpr bool kQ = OP != kFdGradV, kV = OP != kFdGradQ;   // dq's matrix is wanted, dqd's
+    constexpr bool kForce = kVel && kQ;
     constexpr bool kPrism = G::prism;
 
     const int lane = (int)threadIdx.x;
@@ -396,9 +399,11 @@ __device__ __forceinline__ void run_team(const BatchArgs& A, int block, float* p
         psd = cross_S(vl);
         fP0[me] = float4{psd.a.x, psd.a.y, psd.a.z, psd.l.x};
         fP1[me] = float4{psd.l.y, psd.l.z, 0.0f, 0.0f};
-        if constexpr (!kBias)
+        if constexpr (!kBias && kForce)
             fQ1[me] = float4{ui, 0.0f, 0.0f, 0.0f};    // the given qdd
         wave_lds_sync();
+    }
+    if constexpr (kForce) {
         // a_lambda with qdd = 0 (dFD, FD) or the given qdd: a0 + sum of psd_k qd_k + S_k qdd_k
         al = Six{{0.0f, 0.0f, 0.0f}, a0};
         V3 D = r;
@@ -431,6 +436,9 @@ __device__ __forceinline__ void run_team(const BatchArgs& A, int block, float* p
         const Six v = add_S(vl, qd);
         l = v.l * m + cross(v.a, h);
         K = momentum_moment(v, h, P);
+    }
+    if constexpr (kForce) {
+        const Six v = add_S(vl, qd);
         Six a = Six{al.a + psd.a * qd, al.l + psd.l * qd};
         if constexpr (!kBias)
             a = add_S(a, ui);
@@ -493,7 +501,8 @@ __device__ __forceinline__ void run_team(const BatchArgs& A, int block, float* p
             });
         });
     };
-    constexpr int NF = kDer ? 7 : (kVel ? 4 : 3);
+    constexpr int NF = kDer ? (kForce ? 7 : 6) : (kForce ? 4 : 3);
+    constexpr int KO = kForce ? 16 : 10;               // where K and l begin
     float ms = m;                                      // the mass that P and h stand for
     sum_up(
         grids::Int<NF>{},
@@ -505,7 +514,7 @@ __device__ __forceinline__ void run_team(const BatchArgs& A, int block, float* p
 #pragma unroll
             for (int e = 0; e < 10; ++e)
                 o[e] = f[e];
-            if constexpr (kVel) {
+            if constexpr (kForce) {
                 const V3 n = F.a + cross(d, F.l);
                 const float y[6] = {n.x, n.y, n.z, F.l.x, F.l.y, F.l.z};
 #pragma unroll
@@ -518,10 +527,11 @@ __device__ __forceinline__ void run_team(const BatchArgs& A, int block, float* p
                                      k2.x, k2.y, k2.z, l.x,  l.y,  l.z};
 #pragma unroll
                 for (int e = 0; e < 12; ++e)
-                    o[16 + e] = y[e];
+                    o[KO + e] = y[e];
             }
-            if constexpr (!kVel)
-                o[10] = o[11] = 0.0f;
+#pragma unroll
+            for (int e = kDer ? KO + 12 : (kForce ? 16 : 10); e < 4 * NF; ++e)
+                o[e] = 0.0f;
         },
         [&](const float (&o)[4 * NF]) {
             P = Sym{P.xx + o[0], P.yy + o[1], P.zz + o[2], P.xy + o[3], P.xz + o[4], P.yz + o[5]};
@@ -530,10 +540,10 @@ __device__ __forceinline__ void run_team(const BatchArgs& A, int block, float* p
             if constexpr (kVel)
                 F = Six{F.a + V3{o[10], o[11], o[12]}, F.l + V3{o[13], o[14], o[15]}};
             if constexpr (kDer) {
-                K.c0 = K.c0 + V3{o[16], o[17], o[18]};
-                K.c1 = K.c1 + V3{o[19], o[20], o[21]};
-                K.c2 = K.c2 + V3{o[22], o[23], o[24]};
-                l = l + V3{o[25], o[26], o[27]};
+                K.c0 = K.c0 + V3{o[KO], o[KO + 1], o[KO + 2]};
+                K.c1 = K.c1 + V3{o[KO + 3], o[KO + 4], o[KO + 5]};
+                K.c2 = K.c2 + V3{o[KO + 6], o[KO + 7], o[KO + 8]};
+                l = l + V3{o[KO + 9], o[KO + 10], o[KO + 11]};
             }
         });
 
@@ -588,7 +598,7 @@ __device__ __forceinline__ void run_team(const BatchArgs& A, int block, float* p
 
     // ------------------------------------------------------------ qdd, or taubar
     float xi = 0.0f;                                   // this joint's qdd (dFD, FD), taubar (VJP)
-    if constexpr (OP != kMinv && OP != kIdGrad) {
+    if constexpr (kBias || OP == kVjp) {
         float x[BS];
 #pragma unroll
         for (int e = 0; e < BS / 4; ++e) {
@@ -617,7 +627,7 @@ __device__ __forceinline__ void run_team(const BatchArgs& A, int block, float* p
     if constexpr (OP == kFd)
         return;
 
-    if constexpr (OP == kFdGrad) {
+    if constexpr (kBias) {
         // the increment from qdd = 0 to qdd: Da_lambda, Df, summed over subtrees
         fZ[me] = float4{z.x, z.y, z.z, xi};
         wave_lds_sync();
@@ -641,13 +651,15 @@ __device__ __forceinline__ void run_team(const BatchArgs& A, int block, float* p
 
     // ------------------------------------------------------------ dtau/dq, dtau/dqd
     if constexpr (kDer) {
-        Six pdd;
-        {
+        Six pdd{};
+        if constexpr (kQ) {
             const Six x = cross_S(al);
             pdd = Six{x.a + cross(vl.a, psd.a), x.l + cross(vl.a, psd.l) + cross(vl.l, psd.a)};
         }
-        fQ0[me] = float4{pdd.a.x, pdd.a.y, pdd.a.z, pdd.l.x};
-        fQ1[me] = float4{pdd.l.y, pdd.l.z, 0.0f, 0.0f};
+        if constexpr (kQ) {
+            fQ0[me] = float4{pdd.a.x, pdd.a.y, pdd.a.z, pdd.l.x};
+            fQ1[me] = float4{pdd.l.y, pdd.l.z, 0.0f, 0.0f};
+        }
         if constexpr (!T::chain()) {                   // entries off the ancestor paths
             for (int e = lane; e < Y::cols / 4; e += 64)
                 reinterpret_cast<float4*>(sT)[e] = float4{0.0f, 0.0f, 0.0f, 0.0f};
@@ -671,8 +683,10 @@ __device__ __forceinline__ void run_team(const BatchArgs& A, int block, float* p
         }
         wave_lds_sync();
         float* const col = sT + me * BS;               // this body's column
-        col[i] = dot_me(u);
-        col[TQ + i] = dot_me(w);
+        if constexpr (kQ)
+            col[i] = dot_me(u);
+        if constexpr (kV)
+            col[TQ + i] = dot_me(w);
         Six g = F1;
         V3 s = r;
         const V3 b2 = b * 2.0f;
@@ -691,11 +705,15 @@ __device__ __forceinline__ void run_team(const BatchArgs& A, int block, float* p
             const float y1 = 2.0f * (bs + dot(g.a, pa) + dot(g.l, pl));
             if (t < depth) {
                 const int k = anc[t] - sb;
-                col[k] = x0;
-                col[TQ + k] = x1;
                 float* const row = sT + anc[t] * BS + i;
-                row[0] = y0;
-                row[TQ] = y1;
+                if constexpr (kQ) {
+                    col[k] = x0;
+                    row[0] = y0;
+                }
+                if constexpr (kV) {
+                    col[TQ + k] = x1;
+                    row[TQ] = y1;
+                }
             }
             s = V3{rk.x, rk.y, rk.z};
         }
@@ -752,13 +770,14 @@ __device__ __forceinline__ void run_team(const BatchArgs& A, int block, float* p
     int own = br * B + i;
     if constexpr (NB > 1 && !G::in_order)
         own = G::rowmap()[own];
-    constexpr int NM = OP == kFdGrad ? 3 : (OP == kIdGrad ? 2 : 1);
+    constexpr int NM = OP == kFdGrad ? 3 : (OP == kIdGrad || OP == kFdGradV ? 2 : 1);
     if constexpr (B < N) {                             // zeros in the other branches' columns
         for (int e = lane; e < (Y::NT == 3 ? NM : 1) * Y::tile / 4; e += 64)
             reinterpret_cast<float4*>(pool)[e] = float4{0.0f, 0.0f, 0.0f, 0.0f};
         wave_lds_sync();
     }
-    float* const dst[3] = {OP == kFdGrad ? A.o1 : A.o0, OP == kFdGrad ? A.o2 : A.o1, A.o3};
+    float* const dst[3] = {OP == kFdGradQ ? A.o2 : (kFdDer ? A.o1 : A.o0),
+                           OP == kFdGrad ? A.o2 : (OP == kFdGradV ? A.o3 : A.o1), A.o3};
     // matrix `mat` is in its tile
     const auto tile_done = [&](int mat) {
         if constexpr (Y::NT == 3) {
@@ -785,7 +804,7 @@ __device__ __forceinline__ void run_team(const BatchArgs& A, int block, float* p
         put_column(1, cqd, 1.0f);
         return;
     }
-    if constexpr (kMass) {
+    if constexpr (kMass && kV) {
         float mc[B];
 #pragma unroll
         for (int k = 0; k < B; ++k)
@@ -801,11 +820,13 @@ __device__ __forceinline__ void run_team(const BatchArgs& A, int block, float* p
         }
         tile_done(0);
     }
-    if constexpr (OP == kFdGrad) {
+    if constexpr (kFdDer && kQ) {
         gridq::ltl_solve<S>(Lf, dinv, cq);
-        put_column(1, cq, -1.0f);
+        put_column(kV ? 1 : 0, cq, -1.0f);
+    }
+    if constexpr (kFdDer && kV) {
         gridq::ltl_solve<S>(Lf, dinv, cqd);
-        put_column(2, cqd, -1.0f);
+        put_column(kQ ? 2 : 1, cqd, -1.0f);
     }
 }
 
@@ -824,6 +845,21 @@ extern "C" __global__ void __launch_bounds__(64) grid_fdgrad_team(grid::Args arg
     const gridv::BatchArgs a{args.nknots, args.q, args.qd, args.tau, nullptr,
                         args.qdd, args.Minv, args.dqdd_dq, args.dqdd_dqd};
     grid_dispatch_t<gridt::kFdGrad>(a, (int)blockIdx.x);
+}
+
+// dFD by two wavefronts: qdd and dqdd/dq; M^-1 and dqdd/dqd, which needs neither accelerations nor
+// forces. humanoid30 at 128, 1024, 1536 and 2048 knots 14.1 / 16.0 / 16.6 / 17.5 us by one, 11.5 /
+// 13.7 / 15.1 / 17.4 by two, at 4096 24.1 and 30.0; chain7 at 1024, 4096 and 8192 8.4 / 9.1 / 10.0
+// and 7.5 / 8.5 / 9.7, at 16384 12.7 and 18.4
+extern "C" __global__ void __launch_bounds__(64) grid_fdgrad_team_halves(grid::Args args)
+{
+    const gridv::BatchArgs a{args.nknots, args.q, args.qd, args.tau, nullptr,
+                        args.qdd, args.Minv, args.dqdd_dq, args.dqdd_dqd};
+    const int half = (int)gridDim.x / 2, b = (int)blockIdx.x;
+    if (b < half)
+        grid_dispatch_t<gridv::kFdGradQ>(a, b);
+    else
+        grid_dispatch_t<gridv::kFdGradV>(a, b - half);
 }
 
 extern "C" __global__ void __launch_bounds__(64) grid_team_fd(gridq::OpArgs x)

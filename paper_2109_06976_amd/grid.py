@@ -823,10 +823,10 @@ BUILD_QUAD, BUILD_LANE, BUILD_LANE_W2, BUILD_LANE_W4, BUILD_PIPE, BUILD_SERIAL, 
 MIXED_ONE_LAUNCH, MIXED_PERSISTENT, MIXED_PER_ROBOT = range(3)
 MIXED_MODES = ("one_launch", "persistent", "per_robot")
 JOINT_REVOLUTE, JOINT_PRISMATIC, JOINT_FIXED = 0, 1, 2
-# each build's kernel. Builds 1 to 3 and 6 leave one lane per body for one lane per problem as
-# batches grow, and that (build 5 too) runs as grid_fdgrad_serial_halves while two wavefronts per
-# problem leave no SIMD with two; a robot with a base branch of more than 8 bodies runs
-# grid_fdgrad_team as all of them but build 4, and as build 4 beyond 256 knots
+# each build's kernel. Builds 1, 3 and 6 leave one lane per body for one lane per problem as
+# batches grow; up to a batch size either runs as its _halves kernel (two wavefronts with half of
+# the outputs each), except as builds 2 and 7. A robot with a base branch of more than 8 bodies runs
+# grid_fdgrad_team as all of them but build 4, and as build 4 beyond 8 knots
 BUILD_KERNELS = ("grid_fdgrad_quad", "grid_fdgrad_team", "grid_fdgrad_team", "grid_fdgrad_team",
                  "grid_fdgrad_pipe", "grid_fdgrad_serial", "grid_fdgrad_team",
                  "grid_fdgrad_serial")

@@ -80,3 +80,27 @@ def test_inverse_dynamics_on_large_batches(orc, name, per_cu):
         check((name, "dID dqd"), dqd[it].cpu().numpy(), np.stack([b for _, b in ref]), 1e-3)
     finally:
         m.close()
+
+
+@pytest.mark.parametrize("build", [grid.BUILD_LANE, grid.BUILD_LANE_W2])
+@pytest.mark.parametrize("name", ["chain7", "humanoid30", "humanoid30-prism"])
+def test_gradient_by_bodies_in_halves_and_whole(orc, name, build):
+    import torch
+    robot = {**prismatic_models(), "chain7": synth.chain7(), "humanoid30": synth.humanoid30()}[name]
+    n = robot.n
+    m = grid.Model(robot)
+    try:
+        grid.tune_apply(m, {1 << 22: build})
+        for N in (1, 9, 10, 61):
+            print(f"[gpu] dFD build {build} {name} N={N}", flush=True)
+            kn = synth.random_knots(n, N, 1900 + N)
+            ins = [torch.from_numpy(a).cuda() for a in (kn.q, kn.qd, kn.tau)]
+            outs = [torch.full((N, n) + (n,) * (k > 0), float("nan"), device="cuda")
+                    for k in range(4)]
+            m.fd_grad(*ins, *outs, N=N)
+            torch.cuda.synchronize()
+            ref = orc.fd_grad_batch(robot, kn.q, kn.qd, kn.tau)
+            for key, out in zip(("qdd", "Minv", "dqdd_dq", "dqdd_dqd"), outs):
+                check((name, N, key), out.cpu().numpy(), ref[key], 1e-4 if key == "qdd" else 1e-3)
+    finally:
+        m.close()
