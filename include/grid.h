@@ -177,8 +177,8 @@ grid_status grid_workspace_destroy(grid_workspace ws);
  * Host-pointer variant (the paper's CPU-side call, Sec. IV-A): copies q, qd, tau to
  * the device, runs grid_fd_grad, copies the outputs back and waits. Host buffers are
  * ordinary (pageable) memory in the layouts above; they are staged through the
- * workspace's pinned buffers. `timing` (may be NULL) receives HIP-event times of the
- * three phases. Errors: EINVAL (N > max_knots of the workspace, NULL pointers, a
+ * workspace's pinned buffers. `timing` (may be NULL) receives the device's times of the
+ * three phases (of its clock where the copies are kernels, of events else). Errors: EINVAL (N > max_knots of the workspace, NULL pointers, a
  * workspace made for another model), EDEVICE.
  */
 grid_status grid_fd_grad_host(grid_model m, grid_workspace ws, int32_t N, const float* q,

@@ -165,8 +165,12 @@ hipError_t launch_dt(int nknots, int n, float dt, const float* dq, const float* 
                      const float* Minv, float* A, float* B, hipStream_t stream);
 
 // copy of n floats between device and mapped pinned host memory by a kernel (16 bytes per thread;
-// both 16-byte aligned)
-hipError_t launch_copy_out(const float* src, float* dst, size_t n, hipStream_t stream);
+// both 16-byte aligned); stamps: two device-clock values from each of its copy_blocks(n) workgroups
+// (n below 2^29), or NULL
+constexpr int kMaxCopyBlocks = 1024;
+int copy_blocks(size_t n);
+hipError_t launch_copy_out(const float* src, float* dst, size_t n, hipStream_t stream,
+                           uint64_t* stamps = nullptr);
 
 // the library's static scratch array (grid_noalloc.hip): its device address on `device`, taken
 // once with that device current; noalloc_scratch returns it (NULL before the setup)
@@ -208,4 +212,7 @@ struct grid_workspace_s {
     float* h_out = nullptr;
     float* h_in_dev = nullptr;          // the device's mapping of h_in and h_out (NULL if the
     float* h_out_dev = nullptr;         // runtime gives none: the mapped call is unsupported)
+    uint64_t* stamps = nullptr;         // pinned: the copy kernels' clock values, in then out
+    uint64_t* stamps_dev = nullptr;     // (NULL: events time the phases)
+    int clock_khz = 0;
 };

@@ -296,26 +296,26 @@ static bool bodies_in_halves(grid_model m, int64_t N)
 // kVariantSerial2 stand for the halves here
 int kernel_of(grid_model m, int variant, int32_t N)
 {
-    const int team = bodies_in_halves(m, N) ? kVariantTeam2 : kVariantTeam;
-    const int serial = problems_in_halves(m, N) ? kVariantSerial2 : kVariantSerial;
-    if (long_branch(m->topo)) {
-        // a long branch: a lane does not hold it, and the three-role kernel gives it a workgroup
-        if (variant == kVariantPipe && N <= kPipeLongKnots)
-            return kVariantPipe;
-        return variant == kVariantTeam2 ? kVariantTeam : team;
-    }
+    const auto bodies = [&] { return bodies_in_halves(m, N) ? kVariantTeam2 : kVariantTeam; };
+    const auto problems = [&] {
+        return problems_in_halves(m, N) ? kVariantSerial2 : kVariantSerial;
+    };
+    if (variant == kVariantPipe && (!long_branch(m->topo) || N <= kPipeLongKnots))
+        return variant;
+    // a long branch: a lane does not hold it, and the three-role kernel gives it a workgroup
+    if (long_branch(m->topo))
+        return variant == kVariantTeam2 ? kVariantTeam : bodies();
     switch (variant) {
     case kVariantQuad:
-    case kVariantPipe:
         return variant;
     case kVariantTeam2:
         return kVariantTeam;
     case kVariantSerial:
-        return serial;
+        return problems();
     case kVariantSerial2:
         return kVariantSerial;
     default:
-        return lane_per_body(m, N) ? team : serial;
+        return lane_per_body(m, N) ? bodies() : problems();
     }
 }
 
@@ -990,9 +990,16 @@ grid_status grid_workspace_create(grid_model m, int32_t max_knots, grid_workspac
         hipHostGetDevicePointer(&pin_out, w->h_out, 0) == hipSuccess) {
         w->h_in_dev = static_cast<float*>(pin_in);
         w->h_out_dev = static_cast<float*>(pin_out);
-    } else {
-        (void)hipGetLastError();
+        void* pin = nullptr;
+        if (hipDeviceGetAttribute(&w->clock_khz, hipDeviceAttributeWallClockRate, m->device) ==
+                hipSuccess &&
+            w->clock_khz > 0 &&
+            hipHostMalloc(&w->stamps, 4 * kMaxCopyBlocks * sizeof(uint64_t),
+                          hipHostMallocDefault) == hipSuccess &&
+            hipHostGetDevicePointer(&pin, w->stamps, 0) == hipSuccess)
+            w->stamps_dev = static_cast<uint64_t*>(pin);
     }
+    (void)hipGetLastError();
     *out = w;
     return GRID_OK;
 }
@@ -1020,6 +1027,8 @@ grid_status grid_workspace_destroy(grid_workspace w)
         (void)hipHostFree(w->h_in);
     if (w->h_out)
         (void)hipHostFree(w->h_out);
+    if (w->stamps)
+        (void)hipHostFree(w->stamps);
     delete w;
     return GRID_OK;
 }
@@ -1058,9 +1067,23 @@ static grid_status issue_piece(grid_model m, grid_workspace w, int32_t N, int32_
 // few percent more per second (45 MB: 797 us, 820 by a kernel; 11 MB: 209 and 205).
 constexpr size_t kKernelCopyBytes = 8u << 20;
 
+// the first and the last clock value that a copy kernel's workgroups left
+struct ClockSpan {
+    uint64_t begin, end;
+};
+static ClockSpan clock_span(const uint64_t* stamps, int blocks)
+{
+    ClockSpan s{stamps[0], stamps[1]};
+    for (int b = 1; b < blocks; ++b) {
+        s.begin = std::min(s.begin, stamps[2 * b]);
+        s.end = std::max(s.end, stamps[2 * b + 1]);
+    }
+    return s;
+}
+
 // H2D of the pinned inputs, the fused kernel and D2H into the pinned outputs for N knots, then
 // a wait. One piece: one copy each way (the packed arrays are contiguous) on the workspace's
-// stream, the three phases timed by events. Several pieces: issued on the two streams in turn,
+// stream, the three phases timed if asked for. Several pieces: issued on the two streams in turn,
 // so that the copies of one overlap the kernel of another; only the total is timed.
 static grid_status run_pinned(grid_model m, grid_workspace w, int32_t N, int32_t pieces,
                               grid_timing* timing)
@@ -1072,26 +1095,46 @@ static grid_status run_pinned(grid_model m, grid_workspace w, int32_t N, int32_t
         float* d_qdd = w->d_out;
         const bool by_kernel = w->h_in_dev && w->h_out_dev &&
                                (vec + 3 * mat) * sizeof(float) <= kKernelCopyBytes;
-        HIP_TRY(hipEventRecord(w->ev[0], w->stream));
+        // the phases are timed by the copy kernels' clock values, or by events
+        uint64_t* const clock = timing && by_kernel ? w->stamps_dev : nullptr;
+        uint64_t* const clock_out = clock ? clock + 2 * kMaxCopyBlocks : nullptr;
+        const bool events = timing && !clock;
+        if (events)
+            HIP_TRY(hipEventRecord(w->ev[0], w->stream));
         if (by_kernel)
-            HIP_TRY(launch_copy_out(w->h_in_dev, d_q, 3 * vec, w->stream));
+            HIP_TRY(launch_copy_out(w->h_in_dev, d_q, 3 * vec, w->stream, clock));
         else
             HIP_TRY(hipMemcpyAsync(d_q, w->h_in, 3 * vec * sizeof(float), hipMemcpyHostToDevice,
                                    w->stream));
-        HIP_TRY(hipEventRecord(w->ev[1], w->stream));
+        if (events)
+            HIP_TRY(hipEventRecord(w->ev[1], w->stream));
         grid_status s = launch_fused(m, N, d_q, d_q + vec, d_q + 2 * vec, d_qdd, d_qdd + vec,
                                      d_qdd + vec + mat, d_qdd + vec + 2 * mat, w->stream);
         if (s != GRID_OK)
             return s;
-        HIP_TRY(hipEventRecord(w->ev[2], w->stream));
+        if (events)
+            HIP_TRY(hipEventRecord(w->ev[2], w->stream));
         if (by_kernel)
-            HIP_TRY(launch_copy_out(d_qdd, w->h_out_dev, vec + 3 * mat, w->stream));
+            HIP_TRY(launch_copy_out(d_qdd, w->h_out_dev, vec + 3 * mat, w->stream, clock_out));
         else
             HIP_TRY(hipMemcpyAsync(w->h_out, d_qdd, (vec + 3 * mat) * sizeof(float),
                                    hipMemcpyDeviceToHost, w->stream));
-        HIP_TRY(hipEventRecord(w->ev[3], w->stream));
+        if (events)
+            HIP_TRY(hipEventRecord(w->ev[3], w->stream));
         HIP_TRY(hipStreamSynchronize(w->stream));
-        if (timing) {
+        if (clock) {
+            const ClockSpan in = clock_span(w->stamps, copy_blocks(3 * vec));
+            const ClockSpan res = clock_span(w->stamps + 2 * kMaxCopyBlocks,
+                                             copy_blocks(vec + 3 * mat));
+            const auto ms = [w](uint64_t from, uint64_t to) {
+                return (float)((double)(int64_t)(to - from) / w->clock_khz);
+            };
+            timing->h2d_ms = ms(in.begin, in.end);
+            timing->kernel_ms = ms(in.end, res.begin);
+            timing->d2h_ms = ms(res.begin, res.end);
+            timing->total_ms = ms(in.begin, res.end);
+        }
+        if (events) {
             HIP_TRY(hipEventElapsedTime(&timing->h2d_ms, w->ev[0], w->ev[1]));
             HIP_TRY(hipEventElapsedTime(&timing->kernel_ms, w->ev[1], w->ev[2]));
             HIP_TRY(hipEventElapsedTime(&timing->d2h_ms, w->ev[2], w->ev[3]));
