@@ -239,7 +239,7 @@ def robot_sweeps(torch, grid, synth, args):
             s, a = time_steps(torch, call, max(200, args.steps // 5), 50)
             res[str(NK)] = {"knot_evals_per_s": NK / s, "ms_per_step": s * 1e3,
                             "kernel_avg_us": a * 1e6,
-                            "kernel": grid.BUILD_KERNELS[grid.build_for(model, NK)],
+                            "kernel": grid.kernel_for(model, NK),
                             "alu_frac": algorithmic_flops(name) * NK / a / 1e12 / PEAK_FP32_TFLOPS}
             del ins, outs, call
         model.close()
@@ -339,7 +339,7 @@ def mixed_batches(torch, grid, synth, chain_model, steps):
 def io_sweep(torch, grid, synth, reps):
     """The paper's multiple-computation sweep (Sec. V-B, Fig. 4) on each robot: per batch size,
     the fused kernel with inputs resident in device memory (compute only), and the host call on
-    the workspace's pinned buffers split into H2D / kernel / D2H (HIP events), the same call
+    the workspace's pinned buffers split into H2D / kernel / D2H (the device's times), the same call
     cut into overlapping pieces, the mapped call (no copy engines: the kernel reads the pinned
     inputs, a copy kernel or the fused kernel itself writes the pinned outputs), and the call on
     pageable host arrays (staged through the pinned buffers)."""
@@ -351,7 +351,7 @@ def io_sweep(torch, grid, synth, reps):
         robot = synth.model_by_name(name)
         n = robot.n
         m = grid.Model(robot)
-        tuned = grid.tune(m, list(synth.SWEEP_KNOTS))
+        grid.tune(m, list(synth.SWEEP_KNOTS))
         ws = grid.Workspace(m, max(synth.SWEEP_KNOTS))
         rows = {}
         for N in synth.SWEEP_KNOTS:
@@ -405,7 +405,7 @@ def io_sweep(torch, grid, synth, reps):
                 ws.fd_grad_host(kn.q, kn.qd, kn.tau)
             pageable = (time.perf_counter() - t0) / reps * 1e6
             rows[str(N)] = {
-                "build": grid.BUILD_KERNELS[tuned[N]],
+                "build": grid.kernel_for(m, N),
                 "compute_knot_evals_per_s": N / wall, "kernel_us": gpu * 1e6,
                 "alu_frac": algorithmic_flops(name) * N / gpu / 1e12 / PEAK_FP32_TFLOPS,
                 "step_us": wall * 1e6,
@@ -432,10 +432,10 @@ def serve(args, grid, synth, chain_model=None):
     probs = [0.5, 0.3, 0.2]
     # the server's launches run the build each model's tuning picks for the batch's knot
     # count: tune at the batch sizes it can launch (requests of 16-256 knots, batches up to
-    # 2048); untuned, a batch beyond one wavefront per SIMD would take the lane layout
+    # 2048)
     batch_ns = [16, 32, 64, 128, 256, 512, 1024, 2048]
-    tuned_builds = {rb.name.split("-")[0]: {str(k): grid.BUILD_KERNELS[v]
-                                            for k, v in grid.tune(m, batch_ns).items()}
+    tuned_builds = {rb.name.split("-")[0]: {str(k): grid.kernel_for(m, k)
+                                            for k in grid.tune(m, batch_ns)}
                     for rb, m in zip(robots, models)}
     out = {"workload": "Poisson arrivals, chain7/quad12/humanoid30 at 50/30/20 %, "
                        "N ~ U{16..256}, latency = outputs in host memory - scheduled arrival",
@@ -621,8 +621,9 @@ def main():
     if args.build >= 0:
         grid.tune_apply(model, {1 << 22: args.build})
     else:
-        for b, name in enumerate(grid.BUILD_KERNELS):
+        for b in range(len(grid.BUILD_KERNELS)):
             grid.tune_apply(model, {1 << 22: b})
+            name = grid.kernel_for(model, N)
             st, ks = time_steps(torch, launch, max(200, args.steps // 10), 50)
             builds[name] = {"us_per_step": round(st * 1e6, 3),
                             "kernel_avg_us": round(ks * 1e6, 3)}
@@ -651,13 +652,13 @@ def main():
     flop_launch = fl["total"] * N
     achieved_tflops = flop_launch / (avg_ms * 1e-3) / 1e12
     workload = f"{args.robot}-N{N}"
-    counters = measured_counters(workload, grid.BUILD_KERNELS[build], model.code_hash)
+    counters = measured_counters(workload, grid.kernel_for(model, N), model.code_hash)
     traffic = counters.get("bytes_per_launch")
     executed = counters.get("executed_fp32_flop_per_launch")
     roofline = {"bound": "alu", "achieved": round(achieved_tflops, 4), "peak": PEAK_FP32_TFLOPS,
                 "unit": "TFLOP/s", "frac": achieved_tflops / PEAK_FP32_TFLOPS,
                 "traffic": traffic,
-                "kernel": grid.BUILD_KERNELS[build], "kernel_avg_us": round(avg_ms * 1e3, 3),
+                "kernel": grid.kernel_for(model, N), "kernel_avg_us": round(avg_ms * 1e3, 3),
                 "flop_per_knot": fl["total"],
                 "flop_per_knot_source": "oracle formulation, instrumented "
                                         "(profiles/flops_per_knot.json)",
@@ -755,7 +756,7 @@ def main():
             s, a = time_steps(torch, l2, max(200, args.steps // 5), 50)
             sweep[str(NK)] = {"knot_evals_per_s": NK / s, "ms_per_step": s * 1e3,
                               "kernel_avg_us": a * 1e6,
-                              "kernel": grid.BUILD_KERNELS[grid.build_for(model, NK)],
+                              "kernel": grid.kernel_for(model, NK),
                               "alu_frac": fl["total"] * NK / a / 1e12 / PEAK_FP32_TFLOPS}
             del i2, o2
         result["sweep"] = sweep

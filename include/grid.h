@@ -520,6 +520,10 @@ grid_status grid_tune_apply(grid_model m, const int32_t* Ns, const int32_t* buil
 /* The build (0..7) a batch of N >= 1 knots runs with the model's current tuning. */
 grid_status grid_build_for(grid_model m, int32_t N, int32_t* build);
 
+/* The kernel it so runs (a build takes another kernel as batches grow); NULL if m is NULL or
+ * N < 1. */
+const char* grid_kernel_for(grid_model m, int32_t N);
+
 /* ------------------------------------------------------------------ serving
  *
  * A server accepts dFD requests (a model index, N knots, host arrays) from any number of

@@ -870,6 +870,11 @@ grid_status grid_build_for(grid_model m, int32_t N, int32_t* build)
     return GRID_OK;
 }
 
+const char* grid_kernel_for(grid_model m, int32_t N)
+{
+    return m && N >= 1 ? grid_impl::kernel_name(m, N) : nullptr;
+}
+
 }  // extern "C"
 
 namespace grid_impl {

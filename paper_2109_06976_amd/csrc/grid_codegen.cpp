@@ -689,7 +689,8 @@ static const char* const kCompileOptions[] = {
 // the pipe kernel's own module: each of its wavefronts has a SIMD to itself and runs one long
 // dependent chain, so it is scheduled for instruction-level parallelism rather than
 // occupancy (chain7, N = 128: 4.65 against 4.97 us per launch; quad12 and humanoid30
-// unchanged). The throughput builds keep the default (build 2 at N = 16384 lost 9% with it).
+// unchanged). The other kernels keep the default (one lane per derivative column, as in the staged
+// pipeline, lost 9% with it at 16384 knots).
 static const char* const kIlpOptions[] = {"-mllvm", "-amdgpu-sched-strategy=max-ilp"};
 
 static uint64_t fnv1a(const std::string& s, uint64_t h = 1469598103934665603ull)

@@ -153,6 +153,7 @@ grid_status launch_fused_variant(grid_model m, int variant, int32_t N, const flo
                                  float* dq, float* dqd, hipStream_t stream);
 int fused_variant_for(grid_model m, int32_t N);
 int kernel_of(grid_model m, int variant, int32_t N);
+const char* kernel_name(grid_model m, int32_t N);
 bool long_branch(const Topology& t);
 void load_tuning(grid_model m);
 std::string cache_dir();

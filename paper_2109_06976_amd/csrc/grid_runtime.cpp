@@ -232,6 +232,16 @@ grid_status launch(hipFunction_t fn, unsigned blocks, unsigned threads, int32_t 
 
 namespace grid_impl {
 
+// the kernels by the number that kernel_of gives them
+static const char* const kKernels[kNumVariants] = {
+    "grid_fdgrad_quad", "grid_fdgrad_team", "grid_fdgrad_team_halves", nullptr,
+    "grid_fdgrad_pipe", "grid_fdgrad_serial", nullptr, "grid_fdgrad_serial_halves"};
+
+const char* kernel_name(grid_model m, int32_t N)
+{
+    return kKernels[kernel_of(m, fused_variant_for(m, N), N)];
+}
+
 // The largest batch of a robot with a long branch that the three-role kernel runs as fast as one
 // lane per body in halves (humanoid30 at 1, 4, 16, 128 and 256 knots 11.4 / 11.5 / 11.7 / 12.0 / 16.2
 // us, and 11.5 / 11.5 / 11.5 / 11.5 / 11.9: a quarter of the wavefronts)
@@ -246,7 +256,7 @@ int fused_variant_for(grid_model m, int32_t N)
         return m->tuned.back().second;
     // untuned: the three-role kernel while its wavefronts fit one per SIMD of the device (the
     // lowest-latency form), then build 0 while its fit (it has fewer: chain7 at 1024 knots 6.6 us,
-    // build 4 7.0, build 1 9.6; quad12 at 512 4.3 / 4.5 / 5.9), the batch kernels beyond (indices
+    // build 4 6.8, build 1 7.5; quad12 at 512 4.3 / 4.4 / 5.1), the batch kernels beyond (indices
     // 1, 6 and 5: kernel_of says which). A robot with a long branch keeps the index of the
     // three-role build up to 4096 knots
     const int64_t simds = 4 * (int64_t)m->compute_units;
@@ -634,17 +644,14 @@ grid_status grid_model_create(const grid_model_desc* desc, int32_t device, uint3
     m->code_hash = source_hash(machine_code(code) + machine_code(pipe_code));
     static const char* const kStages[5] = {"grid_stage_rnea", "grid_stage_minv", "grid_stage_qdd",
                                            "grid_stage_drnea", "grid_stage_fdgrad"};
-    static const char* const kVariants[kNumVariants] = {
-        "grid_fdgrad_quad", "grid_fdgrad_team", "grid_fdgrad_team_halves", nullptr,
-        "grid_fdgrad_pipe", "grid_fdgrad_serial", nullptr, "grid_fdgrad_serial_halves"};
     m->compute_units = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
     hipError_t e = hipModuleLoadData(&m->module, code.data());
     for (int k = 0; k < kNumVariants && e == hipSuccess; ++k)
         // build 4 lives in the pipe module alone; a long branch has neither the quad kernel nor
         // those with one lane per problem
-        if (kVariants[k] && k != kVariantPipe &&
+        if (kKernels[k] && k != kVariantPipe &&
             (k == kVariantTeam || k == kVariantTeam2 || !long_branch(m->topo)))
-            e = hipModuleGetFunction(&m->fused_variant[k], m->module, kVariants[k]);
+            e = hipModuleGetFunction(&m->fused_variant[k], m->module, kKernels[k]);
     static const char* const kOps[kNumOps] = {"grid_op_id", "grid_op_fd", "grid_op_minv",
                                               "grid_op_idgrad", "grid_op_vjp"};
     for (int k = 0; k < kNumOps && e == hipSuccess; ++k)

@@ -135,6 +135,7 @@ _SIGS = {
     "grid_tune_apply": (C.c_int32, [C.c_void_p, C.POINTER(C.c_int32), C.POINTER(C.c_int32),
                                     C.c_int32]),
     "grid_build_for": (C.c_int32, [C.c_void_p, C.c_int32, C.POINTER(C.c_int32)]),
+    "grid_kernel_for": (C.c_char_p, [C.c_void_p, C.c_int32]),
     "grid_id": (C.c_int32, [C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p,
                             C.c_void_p, C.c_void_p]),
     "grid_fd": (C.c_int32, [C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p,
@@ -837,6 +838,11 @@ def build_for(model, N):
     b = C.c_int32(0)
     _check(lib().grid_build_for(model.handle, int(N), C.byref(b)))
     return b.value
+
+
+def kernel_for(model, N):
+    """grid_kernel_for: the kernel a batch of N knots runs."""
+    return lib().grid_kernel_for(model.handle, int(N)).decode()
 
 
 class Server:
