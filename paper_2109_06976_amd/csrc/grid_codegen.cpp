@@ -538,6 +538,19 @@ static void emit_dispatch(std::ostringstream& os, const char* type, size_t count
     os << "}\n";
 }
 
+// the kernels with one lane per body (grid_team.hip says which of them a module holds)
+static void emit_team(std::ostringstream& os, const Topology& t, const std::vector<float>& consts)
+{
+    emit_groups(os, t, consts);
+    os << "#line 1 \"grid_team.hip\"\n";
+    os << grid_team_src;
+    os << "\n// generated: workgroup -> (group of branches, knots), one lane per body\n";
+    emit_dispatch(os, "Group", t.shapes.size(),
+                  "template <int OP>\n__device__ void grid_dispatch_t(const gridv::BatchArgs& a, int block)",
+                  "gridt::Lay<@>::KPB", "gridt::run_team<@, OP>(a, b, pool)",
+                  "gridt::team_floats<@>()");
+}
+
 std::string generate_source(const Topology& t, const std::vector<float>& consts,
                             const double gravity[3], uint32_t flags)
 {
@@ -578,18 +591,12 @@ std::string generate_source(const Topology& t, const std::vector<float>& consts,
     os << "\n// generated: workgroup -> (branch, problem group), standalone algorithms\n";
     emit_dispatch(os, "Inst", t.insts.size(), "template <int OP>\n__device__ void grid_dispatch_op(const gridq::OpArgs& a, int block)",
              "gridq::op_problems<@::S, OP>()", "gridq::run_op<@, OP>(a, b)");
-    emit_groups(os, t, consts);
-    os << "#line 1 \"grid_team.hip\"\n";
-    os << grid_team_src;
-    os << "\n// generated: workgroup -> (group of branches, knots), one lane per body\n";
-    emit_dispatch(os, "Group", t.shapes.size(),
-                  "template <int OP>\n__device__ void grid_dispatch_t(const gridv::BatchArgs& a, int block)",
-                  "gridt::Lay<@>::KPB", "gridt::run_team<@, OP>(a, b, pool)",
-                  "gridt::team_floats<@>()");
+    emit_team(os, t, consts);
     return os.str();
 }
 
-// The pipe kernel (build 4) alone, for its own module compiled with the ILP schedule.
+// The three-role kernel (build 4) and dFD with one lane per body, for their own module compiled
+// with the ILP schedule.
 std::string generate_pipe_source(const Topology& t, const std::vector<float>& consts,
                                  const double gravity[3])
 {
@@ -609,6 +616,11 @@ std::string generate_pipe_source(const Topology& t, const std::vector<float>& co
     os << "extern \"C\" __global__ void __launch_bounds__(64 * GRID_PIPE_WAVES) "
           "grid_fdgrad_pipe(grid::Args args)\n{\n"
           "    grid_dispatch_p(args, (int)blockIdx.x);\n}\n";
+    os << "#line 1 \"grid_axes.hip\"\n";
+    os << grid_axes_src;
+    os << "#line 1 \"grid_serial.hip\"\n";
+    os << grid_serial_src;
+    emit_team(os, t, consts);
     return os.str();
 }
 
@@ -686,8 +698,8 @@ static const char* const kCompileOptions[] = {
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
 };
 
-// the pipe kernel's own module: each of its wavefronts has a SIMD to itself and runs one long
-// dependent chain, so it is scheduled for instruction-level parallelism rather than
+// the module of the pipe kernel and of dFD by one lane per body: each wavefront has a SIMD to itself,
+// or nearly, and runs one long dependent chain, so it is scheduled for instruction-level parallelism rather than
 // occupancy (chain7, N = 128: 4.65 against 4.97 us per launch; quad12 and humanoid30
 // unchanged). The other kernels keep the default (one lane per derivative column, as in the staged
 // pipeline, lost 9% with it at 16384 knots).

@@ -196,7 +196,7 @@ struct grid_model_s {
     hipFunction_t minv_route[2] = {};   // M^-1 one lane per knot: L^T L, direct
     std::vector<std::pair<int32_t, int>> tuned;   // (largest N, variant), ascending N
     hipModule_t module = nullptr;
-    hipModule_t pipe_module = nullptr;  // build 4 alone, compiled with the ILP schedule
+    hipModule_t pipe_module = nullptr;  // build 4 and dFD by bodies, compiled with the ILP schedule
     hipFunction_t stage[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
 };
 

@@ -647,10 +647,10 @@ grid_status grid_model_create(const grid_model_desc* desc, int32_t device, uint3
     m->compute_units = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
     hipError_t e = hipModuleLoadData(&m->module, code.data());
     for (int k = 0; k < kNumVariants && e == hipSuccess; ++k)
-        // build 4 lives in the pipe module alone; a long branch has neither the quad kernel nor
-        // those with one lane per problem
-        if (kKernels[k] && k != kVariantPipe &&
-            (k == kVariantTeam || k == kVariantTeam2 || !long_branch(m->topo)))
+        // a long branch has neither the quad kernel nor those with one lane per problem; the others
+        // live in the pipe module
+        if ((k == kVariantQuad || k == kVariantSerial || k == kVariantSerial2) &&
+            !long_branch(m->topo))
             e = hipModuleGetFunction(&m->fused_variant[k], m->module, kKernels[k]);
     static const char* const kOps[kNumOps] = {"grid_op_id", "grid_op_fd", "grid_op_minv",
                                               "grid_op_idgrad", "grid_op_vjp"};
@@ -676,9 +676,9 @@ grid_status grid_model_create(const grid_model_desc* desc, int32_t device, uint3
         e = hipModuleGetFunction(&m->minv_route[k], m->module, kMinvRoutes[k]);
     if (e == hipSuccess)
         e = hipModuleLoadData(&m->pipe_module, pipe_code.data());
-    if (e == hipSuccess)   // build 4 from its own module
-        e = hipModuleGetFunction(&m->fused_variant[kVariantPipe], m->pipe_module,
-                                 "grid_fdgrad_pipe");
+    for (int k : {kVariantPipe, kVariantTeam, kVariantTeam2})
+        if (e == hipSuccess)
+            e = hipModuleGetFunction(&m->fused_variant[k], m->pipe_module, kKernels[k]);
     if (e != hipSuccess) {
         grid_model_destroy(m);
         return hip_fail(e, "module load");

@@ -13,7 +13,7 @@
 //
 // Bound by the latency of its chain of LDS exchanges up to a few wavefronts per SIMD, by VALU
 // issue beyond. humanoid30: 236 us per launch at 4096 knots and 648 at 16384 on the kernels it
-// took the place of, 24.0 and 70 here; chain7 at 4096 knots 11.4 and 9.2, quad12 7.8 and 6.8.
+// took the place of, 23.5 and 69 here; chain7 at 4096 knots 11.4 and 8.8, quad12 7.8 and 6.8.
 // FD / M^-1 / dID / VJP against the quad layout's (grid_ops.hip): humanoid30 at 4096 knots 46 /
 // 31 / 192 / 68 and 11 / 11 / 15 / 16 us, at 128 9.8 / 9.7 / 11.3 / 14.1 and 7.4 / 6.8 / 9.1 /
 // 10.4; chain7 at 32768 29 / 16 / 77 / 53 and 12 / 10 / 17 / 17.
@@ -832,14 +832,16 @@ __device__ __forceinline__ void run_team(const BatchArgs& A, int block, float* p
 
 }  // namespace gridt
 
-// kernels of a one-robot module (a module of several robots defines GRID_PIPE_ONLY and its
-// own entry point, grid_fdgrad_pipe_mixed)
-#ifndef GRID_PIPE_ONLY
-
 // defined by the generated epilogue: workgroup -> (group of branches, knots)
 template <int OP>
 __device__ void grid_dispatch_t(const gridv::BatchArgs& args, int block);
 
+#ifdef GRID_PIPE_ONLY
+
+// dFD lives in the module with the three-role kernel, compiled for instruction-level parallelism:
+// humanoid30 at 128, 4096 and 16384 knots 11.4 / 24.1 / 70.2 us by the default schedule, 11.2 / 23.5
+// / 69.1 by that; chain7 at 1024 and 16384 7.6 / 12.9 and 7.2 / 12.7. dID has fewer wavefronts per
+// SIMD by it (humanoid30 at 4096 knots 15.2 and 18.3) and stays with the other algorithms
 extern "C" __global__ void __launch_bounds__(64) grid_fdgrad_team(grid::Args args)
 {
     const gridv::BatchArgs a{args.nknots, args.q, args.qd, args.tau, nullptr,
@@ -861,6 +863,8 @@ extern "C" __global__ void __launch_bounds__(64) grid_fdgrad_team_halves(grid::A
     else
         grid_dispatch_t<gridv::kFdGradV>(a, b - half);
 }
+
+#else
 
 extern "C" __global__ void __launch_bounds__(64) grid_team_fd(gridq::OpArgs x)
 {
