@@ -244,7 +244,7 @@ const char* kernel_name(grid_model m, int32_t N)
 
 // The largest batch of a robot with a long branch that the three-role kernel runs as fast as one
 // lane per body in halves (humanoid30 at 1, 4, 16, 128 and 256 knots 11.4 / 11.5 / 11.7 / 12.0 / 16.2
-// us, and 11.5 / 11.5 / 11.5 / 11.5 / 11.9: a quarter of the wavefronts)
+// us, and 11.3 up to 128 knots, 11.7 at 256: a quarter of the wavefronts)
 constexpr int kPipeLongKnots = 8;
 
 int fused_variant_for(grid_model m, int32_t N)
