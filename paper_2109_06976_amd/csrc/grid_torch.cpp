@@ -9,7 +9,7 @@
 // Each entry point takes only what it can run exactly as the Python code would: torch.Tensor
 // objects (no subclass) that are contiguous float32 and large enough, on the model's device. It
 // returns None for anything else, and the caller then takes the Python path, which converts or
-// raises. The library's functions
+// raises. The tensors that the backward step gets back are checked like arguments. The library's functions
 // come as addresses from the ctypes binding, so both sides call the library that is loaded.
 #include <torch/extension.h>
 
@@ -36,10 +36,11 @@ struct Library {
     Text last_error = nullptr;
     StatusText status_string = nullptr;
 };
-// set once when the module is loaded, before any call; `fail` raises the binding's GridError (it
-// stays for the process, like the module)
+// set once when the module is loaded, before any call; `fail` raises the binding's GridError (these
+// stay for the process, like the module)
 Library g_lib;
 PyObject* g_fail = nullptr;
+PyObject* g_dev = nullptr;   // the binding's own check of a buffer (raises, or returns its address)
 
 // with the interpreter lock held: the binding's own exception
 void check(int32_t status)
@@ -71,16 +72,19 @@ void* stream_of(const at::Tensor& t)
     return (void*)c10::hip::getCurrentHIPStreamMasqueradingAsCUDA(t.device().index()).stream();
 }
 
+bool fits(const at::Tensor& t, int64_t device)
+{
+    return t.is_cuda() && t.scalar_type() == at::kFloat && t.layout() == at::kStrided &&
+           t.is_contiguous() && t.device().index() == device && !t.is_neg();
+}
+
 // a contiguous float32 tensor on GPU `device` (not a subclass of torch.Tensor but its Parameter)
 const at::Tensor* plain(PyObject* o, int64_t device)
 {
     if (!THPVariable_CheckExact(o))
         return nullptr;
     const at::Tensor& t = THPVariable_Unpack(o);
-    return t.is_cuda() && t.scalar_type() == at::kFloat && t.layout() == at::kStrided &&
-                   t.is_contiguous() && t.device().index() == device && !t.is_neg()
-               ? &t
-               : nullptr;
+    return fits(t, device) ? &t : nullptr;
 }
 
 float* data(const at::Tensor& t)
@@ -90,6 +94,25 @@ float* data(const at::Tensor& t)
 const float* cdata(const at::Tensor& t)
 {
     return static_cast<const float*>(t.const_data_ptr());
+}
+
+// The address of a tensor that the backward step was handed with at least `need` elements. A saved
+// tensor is whatever the caller's unpack hook returned, if one is set, so it is checked like an
+// argument; one that does not fit goes to the binding's own check, which raises.
+const float* checked(const at::Tensor& t, int64_t device, int64_t need, const char* what)
+{
+    if (t.defined() && fits(t, device) && t.numel() >= need)
+        return cdata(t);
+    py::gil_scoped_acquire gil;
+    PyObject* a = PyObject_CallFunction(g_dev, "NLLs", py::cast(t).release().ptr(),
+                                        (long long)need, (long long)device, what);
+    if (!a) {
+        python_error e;   // carries the Python exception out of the engine's thread
+        e.persist();
+        throw e;
+    }
+    const py::object address = py::reinterpret_steal<py::object>(a);
+    return address.is_none() ? nullptr : reinterpret_cast<const float*>(address.cast<uintptr_t>());
 }
 
 struct Outputs {
@@ -159,12 +182,21 @@ struct Dynamics : torch::autograd::Function<Dynamics> {
         }
         void* stream = stream_of(g);
         const int32_t N = (int32_t)g.size(0);
-        if (ctx->saved_data["jacobians"].toBool())
-            check_unlocked(g_lib.vjp(h, N, cdata(saved[1]), cdata(saved[2]), cdata(saved[0]), cdata(g),
-                            data(a), data(b), data(c), stream));
-        else
-            check_unlocked(g_lib.vjp_adjoint(h, N, cdata(saved[0]), cdata(saved[1]), cdata(saved[2]),
-                                    cdata(g), data(a), data(b), data(c), stream));
+        const int64_t device = g.device().index(), vec = g.numel(), mat = vec * g.size(1);
+        const float* x[3];
+        if (ctx->saved_data["jacobians"].toBool()) {
+            const char* const names[3] = {"Minv", "dqdd_dq", "dqdd_dqd"};
+            for (int k = 0; k < 3; ++k)
+                x[k] = checked(saved[k], device, mat, names[k]);
+            check_unlocked(g_lib.vjp(h, N, x[1], x[2], x[0], checked(g, device, vec, "gbar"), data(a),
+                                     data(b), data(c), stream));
+        } else {
+            const char* const names[3] = {"q", "qd", "qdd"};
+            for (int k = 0; k < 3; ++k)
+                x[k] = checked(saved[k], device, vec, names[k]);
+            check_unlocked(g_lib.vjp_adjoint(h, N, x[0], x[1], x[2], checked(g, device, vec, "gbar"),
+                                             data(a), data(b), data(c), stream));
+        }
         return {a, b, c, at::Tensor(), at::Tensor()};
     }
 };
@@ -259,8 +291,9 @@ py::object launch(uintptr_t fn, const py::object& model, int64_t device, int64_t
 
 PYBIND11_MODULE(_gridtorch, m)
 {
-    m.def("bind", [](const std::map<std::string, uintptr_t>& f, py::object fail) {
+    m.def("bind", [](const std::map<std::string, uintptr_t>& f, py::object fail, py::object dev) {
         g_fail = fail.release().ptr();
+        g_dev = dev.release().ptr();
         g_lib.fd_grad = reinterpret_cast<Vec7>(f.at("grid_fd_grad"));
         g_lib.fd = reinterpret_cast<Fd>(f.at("grid_fd"));
         g_lib.vjp = reinterpret_cast<Vjp>(f.at("grid_fd_vjp"));

@@ -226,7 +226,7 @@ def _native():
         spec = importlib.util.spec_from_file_location("_gridtorch", path)
         mod = importlib.util.module_from_spec(spec)
         spec.loader.exec_module(mod)
-        mod.bind(_addr, _check)
+        mod.bind(_addr, _check, _dev)
         _native_mod = mod
     return _native_mod
 
