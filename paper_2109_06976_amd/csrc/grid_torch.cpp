@@ -169,10 +169,12 @@ struct Dynamics : torch::autograd::Function<Dynamics> {
     static torch::autograd::variable_list backward(torch::autograd::AutogradContext* ctx,
                                                    torch::autograd::variable_list grads)
     {
+        // first, and outside any dispatch guard: an unpack hook may run the caller's graph again
+        // (checkpointing without re-entrant autograd recomputes its region there)
+        const auto saved = ctx->get_saved_variables();
         at::AutoDispatchBelowADInplaceOrView below;
         const at::Tensor g = grads[0].contiguous().to(at::kFloat);
         at::Tensor a = at::empty_like(g), b = at::empty_like(g), c = at::empty_like(g);
-        const auto saved = ctx->get_saved_variables();
         const auto held =
             c10::static_intrusive_pointer_cast<Held>(ctx->saved_data["model"].toCapsule());
         Handle h;

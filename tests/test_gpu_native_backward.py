@@ -1,5 +1,6 @@
 """The native forward-dynamics node under saved-tensor hooks on an MI355X: what the caller's unpack
-hook returns is checked like an argument before a launch."""
+hook returns is checked like an argument before a launch, and a region under checkpointing is
+recomputed in the unpack hook with its graph."""
 import pytest
 
 from paper_2109_06976_amd import grid, synth
@@ -45,3 +46,23 @@ def test_backward_refuses_unpacked_tensors_that_do_not_fit(model, mode, kind):
     with pytest.raises(grid.GridError) as e:
         torch.autograd.grad(qdd, ins, torch.ones_like(qdd))
     assert e.value.status == grid.GRID_EINVAL
+
+
+@pytest.mark.parametrize("mode", ["jacobians", "adjoint"])
+def test_checkpointed_region_is_recomputed_with_its_graph(model, mode):
+    import torch
+    from torch.utils.checkpoint import checkpoint
+    from paper_2109_06976_amd import autograd
+    ins = inputs(torch)
+
+    def region(q, qd, tau):
+        # what precedes the node saves tensors of its own; the Euler step after it saves none
+        qdd = autograd.forward_dynamics(model, q.sin() * q, qd, tau, mode)
+        return qd + 0.01 * qdd
+
+    w = torch.linspace(-1.0, 1.0, 7, device="cuda")
+    print(f"[gpu] checkpointed region, {mode}", flush=True)
+    want = torch.autograd.grad((region(*ins) * w).sum(), ins)
+    got = torch.autograd.grad((checkpoint(region, *ins, use_reentrant=False) * w).sum(), ins)
+    for a, b in zip(got, want):
+        assert torch.equal(a, b)
