@@ -26,15 +26,11 @@ using Vec7 = int32_t (*)(Handle, int32_t, const float*, const float*, const floa
 using Fd = int32_t (*)(Handle, int32_t, const float*, const float*, const float*, float*, void*);
 using Vjp = int32_t (*)(Handle, int32_t, const float*, const float*, const float*, const float*,
                         float*, float*, float*, void*);
-using Text = const char* (*)();
-using StatusText = const char* (*)(int32_t);
 
 struct Library {
     Vec7 fd_grad = nullptr;
     Fd fd = nullptr;
     Vjp vjp = nullptr, vjp_adjoint = nullptr;
-    Text last_error = nullptr;
-    StatusText status_string = nullptr;
 };
 // set once when the module is loaded, before any call; `fail` raises the binding's GridError (these
 // stay for the process, like the module)
@@ -49,12 +45,23 @@ void check(int32_t status)
         py::reinterpret_borrow<py::object>(g_fail)(status);
 }
 
-// on the autograd engine's threads: the same text
+// with the interpreter lock held and a Python exception set: carries it out of the autograd
+// engine's thread
+[[noreturn]] void raise_set()
+{
+    python_error e;
+    e.persist();
+    throw e;
+}
+
+// on the autograd engine's threads: the same exception (the library's message is this thread's)
 void check_unlocked(int32_t status)
 {
-    if (status != 0)
-        throw std::runtime_error(std::string(g_lib.status_string(status)) + ": " +
-                                 g_lib.last_error());
+    if (status == 0)
+        return;
+    py::gil_scoped_acquire gil;
+    Py_XDECREF(PyObject_CallFunction(g_fail, "i", (int)status));
+    raise_set();
 }
 
 // the handle of a grid.Model (a ctypes pointer object; None once the model is closed)
@@ -106,11 +113,8 @@ const float* checked(const at::Tensor& t, int64_t device, int64_t need, const ch
     py::gil_scoped_acquire gil;
     PyObject* a = PyObject_CallFunction(g_dev, "NLLs", py::cast(t).release().ptr(),
                                         (long long)need, (long long)device, what);
-    if (!a) {
-        python_error e;   // carries the Python exception out of the engine's thread
-        e.persist();
-        throw e;
-    }
+    if (!a)
+        raise_set();
     const py::object address = py::reinterpret_steal<py::object>(a);
     return address.is_none() ? nullptr : reinterpret_cast<const float*>(address.cast<uintptr_t>());
 }
@@ -300,8 +304,6 @@ PYBIND11_MODULE(_gridtorch, m)
         g_lib.fd = reinterpret_cast<Fd>(f.at("grid_fd"));
         g_lib.vjp = reinterpret_cast<Vjp>(f.at("grid_fd_vjp"));
         g_lib.vjp_adjoint = reinterpret_cast<Vjp>(f.at("grid_fd_vjp_adjoint"));
-        g_lib.last_error = reinterpret_cast<Text>(f.at("grid_last_error"));
-        g_lib.status_string = reinterpret_cast<StatusText>(f.at("grid_status_string"));
     });
     m.def("fd_grad", &fd_grad);
     m.def("forward_dynamics", &forward_dynamics);

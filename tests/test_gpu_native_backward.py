@@ -66,3 +66,18 @@ def test_checkpointed_region_is_recomputed_with_its_graph(model, mode):
     got = torch.autograd.grad((checkpoint(region, *ins, use_reentrant=False) * w).sum(), ins)
     for a, b in zip(got, want):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("mode", ["jacobians", "adjoint"])
+def test_backward_raises_the_library_error(mode):
+    import torch
+    from paper_2109_06976_amd import autograd
+    m = grid.Model(synth.chain7())
+    ins = inputs(torch)
+    qdd = autograd.forward_dynamics(m, *ins, mode)
+    torch.cuda.synchronize()
+    m.close()
+    print(f"[gpu] model closed before the backward step, {mode}", flush=True)
+    with pytest.raises(grid.GridError) as e:
+        torch.autograd.grad(qdd, ins, torch.ones_like(qdd))
+    assert e.value.status == grid.GRID_EINVAL
