@@ -64,6 +64,14 @@ void check_unlocked(int32_t status)
     raise_set();
 }
 
+// a library call without the interpreter lock: a launch waits when the hardware queue is full
+template <class F>
+int32_t unlocked(const F& call)
+{
+    py::gil_scoped_release released;
+    return call();
+}
+
 // the handle of a grid.Model (a ctypes pointer object; None once the model is closed)
 Handle handle_of(const py::object& model)
 {
@@ -130,8 +138,10 @@ Outputs run_fd_grad(Handle h, const at::Tensor& q, const at::Tensor& qd, const a
     const auto opt = q.options().requires_grad(false);
     Outputs o{at::empty({N, n}, opt), at::empty({N, n, n}, opt), at::empty({N, n, n}, opt),
               at::empty({N, n, n}, opt)};
-    check(g_lib.fd_grad(h, (int32_t)N, cdata(q), cdata(qd), cdata(tau), data(o.qdd), data(o.Minv),
-                        data(o.dq), data(o.dqd), stream));
+    check(unlocked([&] {
+        return g_lib.fd_grad(h, (int32_t)N, cdata(q), cdata(qd), cdata(tau), data(o.qdd),
+                             data(o.Minv), data(o.dq), data(o.dqd), stream);
+    }));
     return o;
 }
 
@@ -165,7 +175,9 @@ struct Dynamics : torch::autograd::Function<Dynamics> {
             return o.qdd;
         }
         at::Tensor qdd = at::empty_like(q);
-        check(g_lib.fd(h, (int32_t)q.size(0), cdata(q), cdata(qd), cdata(tau), data(qdd), stream));
+        check(unlocked([&] {
+            return g_lib.fd(h, (int32_t)q.size(0), cdata(q), cdata(qd), cdata(tau), data(qdd), stream);
+        }));
         ctx->save_for_backward({q, qd, qdd});
         return qdd;
     }
@@ -269,27 +281,23 @@ py::object launch(uintptr_t fn, const py::object& model, int64_t device, int64_t
     Handle h = handle_of(model);
     const int32_t n = (int32_t)N;
     using V = void*;
-    int32_t st;
-    switch (count) {
-    case 2:
-        st = reinterpret_cast<int32_t (*)(V, int32_t, V, V, V)>(fn)(h, n, p[0], p[1], s);
-        break;
-    case 4:
-        st = reinterpret_cast<int32_t (*)(V, int32_t, V, V, V, V, V)>(fn)(h, n, p[0], p[1], p[2],
-                                                                         p[3], s);
-        break;
-    case 5:
-        st = reinterpret_cast<int32_t (*)(V, int32_t, V, V, V, V, V, V)>(fn)(
-            h, n, p[0], p[1], p[2], p[3], p[4], s);
-        break;
-    case 7:
-        st = reinterpret_cast<int32_t (*)(V, int32_t, V, V, V, V, V, V, V, V)>(fn)(
-            h, n, p[0], p[1], p[2], p[3], p[4], p[5], p[6], s);
-        break;
-    default:
+    if (count != 2 && count != 4 && count != 5 && count != 7)
         return py::none();
-    }
-    check(st);
+    check(unlocked([&]() -> int32_t {
+        switch (count) {
+        case 2:
+            return reinterpret_cast<int32_t (*)(V, int32_t, V, V, V)>(fn)(h, n, p[0], p[1], s);
+        case 4:
+            return reinterpret_cast<int32_t (*)(V, int32_t, V, V, V, V, V)>(fn)(h, n, p[0], p[1],
+                                                                               p[2], p[3], s);
+        case 5:
+            return reinterpret_cast<int32_t (*)(V, int32_t, V, V, V, V, V, V)>(fn)(
+                h, n, p[0], p[1], p[2], p[3], p[4], s);
+        default:
+            return reinterpret_cast<int32_t (*)(V, int32_t, V, V, V, V, V, V, V, V)>(fn)(
+                h, n, p[0], p[1], p[2], p[3], p[4], p[5], p[6], s);
+        }
+    }));
     return py::bool_(true);
 }
 
