@@ -58,7 +58,7 @@ def forward_dynamics(model: "grid.Model", q, qd, tau, mode: str = "jacobians"):
     tensors run ForwardDynamics' two steps in native code (_gridtorch), the backward without the
     interpreter: its lock and wake-ups took most of a step (chain7, 6007 knots: 127 us)."""
     if (mode in ("jacobians", "adjoint") and grid._plain_torch(q) and
-            fwAD._current_level < 0):
+            fwAD._current_level < 0 and grid._native()):
         qdd = grid._native().forward_dynamics(model, model.n, model.device, q, qd, tau,
                                               mode == "jacobians")
         if qdd is not None:

@@ -77,13 +77,30 @@ def build_library(verbose=False, out=None, sanitize=False) -> str:
     return target
 
 
-def build_torch_module(verbose=False) -> str:
-    """_gridtorch.so in-tree: the torch-facing calls (csrc/grid_torch.cpp, host code only)."""
+def torch_root() -> str | None:
+    """The folder of a torch installation that has its C++ headers, or None."""
+    try:
+        import torch
+    except ImportError:
+        return None
+    root = os.path.dirname(torch.__file__)
+    header = os.path.join(root, "include", "torch", "csrc", "api", "include", "torch", "torch.h")
+    return root if os.path.exists(header) else None
+
+
+def build_torch_module(verbose=False) -> str | None:
+    """_gridtorch.so in-tree: the torch-facing calls (csrc/grid_torch.cpp, host code only). None
+    where torch's headers are not there: those calls then go through ctypes."""
     import sysconfig
 
-    import torch
-    root = os.path.dirname(torch.__file__)
+    root = torch_root()
     target = os.path.join(HERE, "_gridtorch.so")
+    if root is None:
+        print("no torch headers: _gridtorch.so is not built", flush=True)
+        if os.path.exists(target):   # of another torch
+            os.remove(target)
+        return None
+    import torch
     inc = [os.path.join(root, "include"),
            os.path.join(root, "include", "torch", "csrc", "api", "include"),
            os.path.join(os.path.dirname(os.path.dirname(HIPCC)) or "/opt/rocm", "include"),

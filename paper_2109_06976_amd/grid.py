@@ -209,21 +209,22 @@ def lib():
     return _lib
 
 
+_NATIVE_PATH = os.path.join(_HERE, "_gridtorch.so")
 _native_mod = None
 _addr = {}      # name -> address of the loaded library's function
 
 
 def _native():
-    """The torch-facing calls in native code (_gridtorch), bound to the loaded library. For
-    callers that have torch tensors in hand (raises if the module has not been built)."""
+    """The torch-facing calls in native code (_gridtorch), bound to the loaded library, for
+    callers that have torch tensors in hand. None where the module has not been built (it needs
+    torch's headers): the same library calls then go through ctypes."""
     global _native_mod
     if _native_mod is None:
-        path = os.path.join(_HERE, "_gridtorch.so")
-        if not os.path.exists(path):
-            raise GridError(GRID_EDEVICE, f"{path} is missing: run __graft_entry__.build()")
+        if not os.path.exists(_NATIVE_PATH):
+            return None
         for name in _SIGS:
             _addr[name] = C.cast(getattr(lib(), name), C.c_void_p).value
-        spec = importlib.util.spec_from_file_location("_gridtorch", path)
+        spec = importlib.util.spec_from_file_location("_gridtorch", _NATIVE_PATH)
         mod = importlib.util.module_from_spec(spec)
         spec.loader.exec_module(mod)
         mod.bind(_addr, _check, _dev)
@@ -248,7 +249,8 @@ def _launch(name, model, N, bufs, need, stream) -> bool:
     if not _plain_torch(bufs[0]):
         return False
     native = _native()
-    return native.launch(_addr[name], model, model.device, int(N), bufs, need, stream) is not None
+    return native is not None and native.launch(_addr[name], model, model.device, int(N), bufs,
+                                                need, stream) is not None
 
 
 def status_string(status: int) -> str:
@@ -958,7 +960,7 @@ def codegen_precompile(robot, flags: int = 0):
 def fd_grad_torch(model: Model, q, qd, tau, stream=None):
     """Allocate outputs with torch on q's device and launch on the current stream."""
     import torch
-    if stream is None and _plain_torch(q):
+    if stream is None and _plain_torch(q) and _native():
         out = _native().fd_grad(model, model.n, model.device, q, qd, tau)
         if out is not None:
             return out
