@@ -78,12 +78,13 @@ def build_library(verbose=False, out=None, sanitize=False) -> str:
 
 
 def torch_root() -> str | None:
-    """The folder of a torch installation that has its C++ headers, or None."""
-    try:
-        import torch
-    except ImportError:
+    """The folder of a torch installation that has its C++ headers, or None (torch is not
+    imported: see precompile)."""
+    import importlib.util
+    spec = importlib.util.find_spec("torch")
+    if spec is None or not spec.submodule_search_locations:
         return None
-    root = os.path.dirname(torch.__file__)
+    root = spec.submodule_search_locations[0]
     header = os.path.join(root, "include", "torch", "csrc", "api", "include", "torch", "torch.h")
     return root if os.path.exists(header) else None
 
@@ -100,14 +101,15 @@ def build_torch_module(verbose=False) -> str | None:
         if os.path.exists(target):   # of another torch
             os.remove(target)
         return None
-    import torch
+    abi = _run([sys.executable, "-c", "import torch; print(int(torch._C._GLIBCXX_USE_CXX11_ABI))"],
+               verbose).stdout.split()[-1]
     inc = [os.path.join(root, "include"),
            os.path.join(root, "include", "torch", "csrc", "api", "include"),
            os.path.join(os.path.dirname(os.path.dirname(HIPCC)) or "/opt/rocm", "include"),
            sysconfig.get_paths()["include"]]
     cmd = ["g++", "-std=c++17", "-O2", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1",
            "-DUSE_ROCM=1", "-DTORCH_EXTENSION_NAME=_gridtorch",
-           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           f"-D_GLIBCXX_USE_CXX11_ABI={abi}",
            *[x for i in inc for x in ("-isystem", i)], os.path.join(CSRC, "grid_torch.cpp"),
            "-L" + os.path.join(root, "lib"), "-Wl,-rpath," + os.path.join(root, "lib"), "-lc10",
            "-lc10_hip", "-ltorch_cpu", "-ltorch_hip", "-ltorch", "-ltorch_python", "-o",
@@ -240,16 +242,56 @@ def _precompile_mixed(k):
     return "+".join(r.name for r in robots)
 
 
-def precompile(verbose=False, workers=None):
-    """Compile every standard model's kernels and the mixed modules into the cache, several
-    at a time (one process each: a compile is single-threaded), the largest first."""
+def compiler_id() -> bytes:
+    """The version line of the HIP compiler, as the code objects it made carry it."""
+    text = subprocess.run([HIPCC, "--version"], capture_output=True, text=True).stdout
+    line = [x for x in text.splitlines() if "clang version" in x]
+    return line[0].strip().encode() if line else b""
+
+
+def drop_foreign_kernels(cache: str) -> None:
+    """Remove the code objects that another compiler made: the cache finds an object by its
+    source, whoever compiled it."""
+    mark = compiler_id()
+    if not mark or not os.path.isdir(cache):
+        return
+    for name in os.listdir(cache):
+        path = os.path.join(cache, name)
+        if name.endswith(".hsaco"):
+            with open(path, "rb") as f:
+                foreign = mark not in f.read()
+            if foreign:
+                os.remove(path)
+
+
+def precompile(verbose=False, names=None):
+    """Compile the standard models' kernels (or those of the robots in `names` alone) and the
+    mixed modules into the cache, in a process of its own: torch brings a hiprtc of another
+    release, and in a process that has imported it the library compiles with that one (clang 20
+    in place of 22: humanoid30's ID 6.2 us in place of 5.6, chain7 at 128 knots 1% slower)."""
+    drop_foreign_kernels(os.environ.get("GRID_KERNEL_CACHE") or os.path.join(HERE, "_kcache"))
+    r = subprocess.run([sys.executable, "-c",
+                        "import sys; from paper_2109_06976_amd import build\n"
+                        "build.compile_kernels(sys.argv[1] == '1', sys.argv[2:] or None)",
+                        str(int(verbose)), *(names or [])], cwd=ROOT)
+    if r.returncode != 0:
+        raise RuntimeError(f"compiling the kernels failed ({r.returncode})")
+
+
+def compile_kernels(verbose=False, names=None, workers=None):
+    """precompile's work: several kernels at a time (one process each: a compile is
+    single-threaded), the largest robots first."""
     import concurrent.futures
     import multiprocessing
+    assert "torch" not in sys.modules
     robots = sorted(standard_models(), key=lambda r: -r.n)
+    if names is not None:
+        robots = [r for r in robots if r.name in names]
     workers = workers or max(1, min(8, os.cpu_count() or 1))
     ctx = multiprocessing.get_context("fork")
     with concurrent.futures.ProcessPoolExecutor(workers, mp_context=ctx) as pool:
-        jobs = [pool.submit(_precompile_mixed, k) for k in range(len(mixed_sets()))]
+        jobs = [] if names is not None else [pool.submit(_precompile_mixed, k)
+                                             for k in range(len(mixed_sets()))]
         jobs += [pool.submit(_precompile_one, r) for r in robots]
         for job in jobs:
             name = job.result()
