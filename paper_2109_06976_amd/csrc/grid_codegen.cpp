@@ -369,8 +369,8 @@ static void emit_prelude(std::ostringstream& os, const std::vector<RobotSource>&
 }
 
 // The branches of one robot by shape, for the kernels with one lane per body: Group<g> holds
-// the NB branches of a shape with, per (branch, body), 24 floats (E_T, r, the second moment
-// P = tr(Ibar) / 2 - Ibar, h, m, the mass of the subtree, 1 for a prismatic joint) and 12 ints
+// the NB branches of a shape with, per (branch, body), 24 floats (E_T, r, Ibar, h, m, the mass
+// of the subtree, 1 for a prismatic joint) and 12 ints
 // (robot body, depth, rank among its siblings, children, the local ancestors from the parent
 // up as bytes); the robot row of each local body and the local column of each robot column
 // (-1: another branch's).
@@ -420,11 +420,7 @@ static void emit_groups(std::ostringstream& os, const Topology& t, const std::ve
             }
             for (int i = 0; i < B; ++i) {
                 const float* c = consts.data() + in.coff + (size_t)i * kConstStride;
-                tab.insert(tab.end(), c, c + 12);
-                const double tr = 0.5 * ((double)c[12] + c[13] + c[14]);
-                for (int e = 0; e < 6; ++e)
-                    tab.push_back((float)((e < 3 ? tr : 0.0) - c[12 + e]));
-                tab.insert(tab.end(), c + 18, c + 22);
+                tab.insert(tab.end(), c, c + 22);
                 tab.push_back((float)sub[i]);
                 tab.push_back((in.prism >> i) & 1ull ? 1.0f : 0.0f);
                 uint32_t words[8] = {};

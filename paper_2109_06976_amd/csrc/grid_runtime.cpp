@@ -280,13 +280,13 @@ int fused_variant_for(grid_model m, int32_t N)
 // unit, 7.4 and 7.2; of 6 at 8192, 3.2 per unit, 8.8 and 9.4, at 16384 11.1 and 9.9; of 7 at 8192,
 // 3.6 per unit, 10.2 and 12.1, at 16384 12.9 both; of 8 at 16384, 8 per unit, 14.7 and 18.6, at
 // 32768 27.8 and 19.9; quad12, branches of 3, at 4096 6.8 and 6.1; dID of a chain of 7 at 8192 7.6
-// and 8.4, at 16384 9.8 and 8.9)
+// and 8.4, at 16384 9.8 and 8.9). Up to five bodies the latter also rounds less (grid_axes.hip)
 static bool lane_per_body(grid_model m, int64_t N)
 {
     int longest = 0;
     for (const BranchShape& s : m->topo.shapes)
         longest = std::max(longest, s.B);
-    return longest > 8 || (longest > 4 && workgroups_team(m->topo, N) <=
+    return longest > 8 || (longest > 5 && workgroups_team(m->topo, N) <=
                                               2 * (int64_t)m->compute_units * (longest - 4));
 }
 

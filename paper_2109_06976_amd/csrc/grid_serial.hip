@@ -7,7 +7,7 @@
 // latency is one lane's whole chain). Per problem, float32 (Sec. IV-B), in the formulation of
 // grid_axes.hip:
 //   1. outward: axes, velocities, accelerations at qdd = 0, forces, inertias
-//   2. inward: M by the subtrees' inertias and the bias forces; M = L^T L along ancestor paths,
+//   2. inward: M by the subtrees' inertias and the bias forces; M = L^T D L along ancestor paths,
 //      qdd = M^-1 (tau - c), M^-1 by B solves
 //   3. outward: accelerations at qdd
 //   4. inward: the derivatives from the subtrees' inertias, momenta and forces, each column moved
@@ -299,8 +299,8 @@ constexpr int serial_floats()
     return SerialLds<I, OP>::floats;
 }
 
-// x <- (L^T L)^-1 x, entry k of x zero unless bit k of MASK is set (MASK holds the ancestors of
-// its bodies); entries up to LAST only
+// x <- M^-1 x, entry k of x zero unless bit k of MASK is set (MASK holds the ancestors of its
+// bodies); entries up to LAST only
 template <class S, unsigned long long MASK, int LAST>
 __device__ __forceinline__ void solve_masked(const float (&L)[S::B][S::B],
                                              const float (&dinv)[S::B], float (&x)[S::B])
@@ -309,7 +309,6 @@ __device__ __forceinline__ void solve_masked(const float (&L)[S::B][S::B],
     static_for<B>([&](auto kk) {
         constexpr int k = B - 1 - decltype(kk)::v;
         if constexpr ((MASK >> k) & 1ull) {
-            x[k] *= dinv[k];
 #pragma unroll
             for (int a = 0; a < k; ++a)
                 if ((S::anc[k] >> a) & 1ull)
@@ -318,12 +317,12 @@ __device__ __forceinline__ void solve_masked(const float (&L)[S::B][S::B],
     });
     static_for<LAST + 1>([&](auto kk) {
         constexpr int k = decltype(kk)::v;
-        float t = ((MASK >> k) & 1ull) ? x[k] : 0.0f;
+        float t = ((MASK >> k) & 1ull) ? x[k] * dinv[k] : 0.0f;
 #pragma unroll
         for (int a = 0; a < k; ++a)
             if ((S::anc[k] >> a) & 1ull)
                 t -= L[k][a] * x[a];
-        x[k] = t * dinv[k];
+        x[k] = t;
     });
 }
 
@@ -357,6 +356,7 @@ __device__ __forceinline__ void run_serial(const gridv::BatchArgs& A, int block,
     constexpr bool kBias = OP == kFdGrad || OP == kFdGradQ || OP == kFd;
     constexpr bool kDer = kIdDer || kFdDer || OP == kVjp;
     constexpr bool kPark = Y::kPark;
+    constexpr bool kFine = kFineBranch<B>;
     const int lane = (int)threadIdx.x;
     const int kraw = block * 64 + lane;
     const bool valid = kraw < A.nknots;
@@ -371,8 +371,9 @@ __device__ __forceinline__ void run_serial(const gridv::BatchArgs& A, int block,
 
     float qd[B], uu[B];
     V3 z[B], r[B], h[B];
-    Sym P[B];
+    Sym J[B];
     Six vl[B], psd[B], al[B];                           // vl, al: the parent's, at this origin
+    Six own[B];                                         // the body's own inertia on a revolute S_i
     const auto pri = [](int i) { return prismatic<I>(i); };
     const auto add_S = [&](int i, Six y, float s) {
         if (pri(i))
@@ -391,7 +392,7 @@ __device__ __forceinline__ void run_serial(const gridv::BatchArgs& A, int block,
     // the parents' accelerations (at qdd = 0 for dFD and FD, else at the given qdd), inertias
     Six F[B];
     {
-        Mat R[B];
+        MatD R[B];
         Six a[B], v[B];
         static_for<B>([&](auto ii) {
             constexpr int i = decltype(ii)::v;
@@ -401,26 +402,18 @@ __device__ __forceinline__ void run_serial(const gridv::BatchArgs& A, int block,
             const float qi = A.q[o];
             qd[i] = kVel ? A.qd[o] : 0.0f;
             uu[i] = kVel ? A.u[o] : 0.0f;
-            const V3 e0{c[0], c[1], c[2]}, e1{c[3], c[4], c[5]}, e2{c[6], c[7], c[8]};
-            float sn = 0.0f, co = 1.0f;
-            if (!pri(i)) {
-                const float rev = __builtin_amdgcn_fractf(qi * 0.159154943091895336f);
-                sn = __builtin_amdgcn_sinf(rev);
-                co = __builtin_amdgcn_cosf(rev);
-            }
-            const Mat X = pri(i) ? Mat{e0, e1, e2} : Mat{e0 * co + e1 * sn, e1 * co - e0 * sn, e2};
-            // second moment of the body: tr(Ibar) / 2 - Ibar
-            const double tr = 0.5 * ((double)c[12] + c[13] + c[14]);
-            const Sym PT{(float)(tr - c[12]), (float)(tr - c[13]), (float)(tr - c[14]),
-                         -c[15], -c[16], -c[17]};
-            const V3 hT{c[18], c[19], c[20]};
+            using AX = AxesOf<kFine>;                   // the type that turns a body's quantities
+            using VT = Vec<typename AX::T>;
+            const auto X = joint_axes(pri(i), qi, VT{c[0], c[1], c[2]}, VT{c[3], c[4], c[5]},
+                                      VT{c[6], c[7], c[8]});
+            const Sym JT{c[12], c[13], c[14], c[15], c[16], c[17]};   // Ibar
             if constexpr (p < 0) {
                 z[i] = V3{0.0f, 0.0f, 1.0f};
                 r[i] = zero3;
-                P[i] = PT;
-                h[i] = hT;
-                const V3 g{I::a0()[0], I::a0()[1], I::a0()[2]};
-                al[i] = Six{zero3, tmul(X, g)};
+                J[i] = JT;
+                h[i] = V3{c[18], c[19], c[20]};
+                own[i] = Six{{c[16], c[17], c[14]}, {-c[19], c[18], 0.0f}};
+                al[i] = Six{zero3, narrow(tmul(X, VT{I::a0()[0], I::a0()[1], I::a0()[2]}))};
                 vl[i] = Six{zero3, zero3};
                 psd[i] = vl[i];
                 v[i] = pri(i) ? Six{zero3, {0.0f, 0.0f, qd[i]}} : Six{{0.0f, 0.0f, qd[i]}, zero3};
@@ -432,19 +425,23 @@ __device__ __forceinline__ void run_serial(const gridv::BatchArgs& A, int block,
                         a[i].a.z = uu[i];
                 }
             } else {
-                const V3 rT{c[9], c[10], c[11]};
                 if constexpr (S::parent[p] < 0) {       // the first body's axes
-                    R[i] = X;
-                    r[i] = rT;
+                    R[i] = wide(X);
+                    r[i] = V3{c[9], c[10], c[11]};
                 } else {
-                    R[i] = Mat{mul(R[p], X.c0), mul(R[p], X.c1), mul(R[p], X.c2)};
-                    r[i] = mul(R[p], rT);
+                    const MatD Y = wide(X);
+                    R[i] = MatD{mul(R[p], Y.c0), mul(R[p], Y.c1), mul(R[p], Y.c2)};
+                    r[i] = narrow(mul(AX::of(R[p]), VT{c[9], c[10], c[11]}));
                 }
-                z[i] = R[i].c2;
+                const auto Ai = AX::of(R[i]);
+                z[i] = narrow(Ai.c2);
                 if (pri(i))
                     r[i] = r[i] + z[i] * qi;
-                P[i] = turn(R[i], PT);
-                h[i] = mul(R[i], hT);
+                J[i] = turn(Ai, JT);
+                h[i] = narrow(mul(Ai, VT{c[18], c[19], c[20]}));
+                if constexpr (kFine)
+                    own[i] = Six{narrow(mul(Ai, VT{c[16], c[17], c[14]})),
+                                 narrow(mul(Ai, VT{-c[19], c[18], 0.0f}))};
                 vl[i] = Six{v[p].a, v[p].l + cross(v[p].a, r[i])};
                 psd[i] = cross_S(i, vl[i]);
                 v[i] = add_S(i, vl[i], qd[i]);
@@ -453,16 +450,15 @@ __device__ __forceinline__ void run_serial(const gridv::BatchArgs& A, int block,
                 if constexpr (!kBias)
                     a[i] = add_S(i, a[i], uu[i]);
                 if constexpr (kPark) {
-                    park[64 * (4 * i - 4)] = float4{P[i].xx, P[i].yy, P[i].zz, P[i].xy};
-                    park[64 * (4 * i - 3)] = float4{P[i].xz, P[i].yz, h[i].x, h[i].y};
+                    park[64 * (4 * i - 4)] = float4{J[i].xx, J[i].yy, J[i].zz, J[i].xy};
+                    park[64 * (4 * i - 3)] = float4{J[i].xz, J[i].yz, h[i].x, h[i].y};
                     park[64 * (4 * i - 2)] = float4{h[i].z, psd[i].a.x, psd[i].a.y, psd[i].a.z};
                     park[64 * (4 * i - 1)] = float4{psd[i].l.x, psd[i].l.y, psd[i].l.z, qd[i]};
                 }
             }
             if constexpr (kBias || OP == kId) {         // f = I a + v x* (I v)
-                const Sym J = second_to_inertia(P[i]);
-                const Six Ia = inertia(mass_of(i), h[i], J, a[i]);
-                const Six Iv = inertia(mass_of(i), h[i], J, v[i]);
+                const Six Ia = inertia(mass_of(i), h[i], J[i], a[i]);
+                const Six Iv = inertia(mass_of(i), h[i], J[i], v[i]);
                 F[i] = Six{Ia.a + cross(v[i].a, Iv.a) + cross(v[i].l, Iv.l),
                            Ia.l + cross(v[i].a, Iv.l)};
             }
@@ -485,30 +481,39 @@ __device__ __forceinline__ void run_serial(const gridv::BatchArgs& A, int block,
     // inertias, the bias forces, the factor
     float Lf[B][B], dinv[B], x[B];
     if constexpr (kMass) {
-        Sym Pc[B];
+        Sym Jc[B];                                      // of the bodies below
         V3 hc[B];
-#pragma unroll
-        for (int i = 0; i < B; ++i) {
-            Pc[i] = P[i];
-            hc[i] = h[i];
-        }
         float mc[B];
 #pragma unroll
-        for (int i = 0; i < B; ++i)
+        for (int i = 0; i < B; ++i) {
+            Jc[i] = Sym{0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+            hc[i] = kFine ? zero3 : h[i];
             mc[i] = mass_of(i);
+        }
         static_for<B>([&](auto ii) {
             constexpr int i = B - 1 - decltype(ii)::v;
             constexpr int p = S::parent[i];
-            Six f = pri(i) ? Six{cross(hc[i], z[i]), z[i] * mc[i]}
-                           : Six{mul(second_to_inertia(Pc[i]), z[i]), cross(z[i], hc[i])};
-            Lf[i][i] = dot_S(i, f);
+            // the row of M in double; the body's own part of M_ii is a constant
+            const V3D zi = wide(z[i]), below = mul(Jc[i], zi);
+            Lf[i][i] = pri(i) ? mc[i] : (float)(C[i * kConstStride + 14] + dot(zi, below));
+            const V3 ht = kFine ? hc[i] + h[i] : hc[i];
+            V3D fa, fl;
+            if (pri(i)) {
+                fa = cross(wide(ht), zi);
+                fl = zi * mc[i];
+            } else {
+                fa = below + (kFine ? wide(own[i].a) : mul(J[i], zi));
+                fl = cross(zi, wide(hc[i]));
+                if constexpr (kFine)
+                    fl = fl + wide(own[i].l);
+            }
             static_for<i>([&](auto tt) {                // the ancestors, nearest first
                 constexpr int k = i - decltype(tt)::v;  // i, then each ancestor but the root
                 if constexpr (k == i || ((S::anc[i] >> k) & 1ull)) {
                     constexpr int q = S::parent[k];
                     if constexpr (q >= 0) {
-                        f.a = f.a + cross(r[k], f.l);
-                        Lf[i][q] = dot_S(q, f);
+                        fa = fa + cross(wide(r[k]), fl);
+                        Lf[i][q] = (float)dot(wide(z[q]), pri(q) ? fl : fa);
                     }
                 }
             });
@@ -518,9 +523,10 @@ __device__ __forceinline__ void run_serial(const gridv::BatchArgs& A, int block,
                     F[p] = Six{F[p].a + F[i].a + cross(r[i], F[i].l), F[p].l + F[i].l};
             }
             if constexpr (p >= 0) {
-                move_moments(Pc[i], hc[i], mc[i], r[i]);
-                Pc[p] = Sym{Pc[p].xx + Pc[i].xx, Pc[p].yy + Pc[i].yy, Pc[p].zz + Pc[i].zz,
-                            Pc[p].xy + Pc[i].xy, Pc[p].xz + Pc[i].xz, Pc[p].yz + Pc[i].yz};
+                Jc[i] = Jc[i] + J[i];
+                hc[i] = ht;
+                move_inertia(Jc[i], hc[i], mc[i], r[i]);
+                Jc[p] = Jc[p] + Jc[i];
                 hc[p] = hc[p] + hc[i];
                 mc[p] += mc[i];
             }
@@ -530,9 +536,9 @@ __device__ __forceinline__ void run_serial(const gridv::BatchArgs& A, int block,
             for (int i = 0; i < B; ++i)
                 x[i] = A.u2[vbase + I::body[i]];
         }
-        gridq::ltl_factor<S>(Lf, dinv);
+        ltdl_factor<S>(Lf, dinv);
         if constexpr (kBias || OP == kVjp) {
-            gridq::ltl_solve<S>(Lf, dinv, x);           // qdd, or taubar
+            ltdl_solve<S>(Lf, dinv, x);           // qdd, or taubar
             if (valid) {
                 float* out = OP == kVjp ? A.o2 : A.o0;
 #pragma unroll
@@ -598,18 +604,19 @@ __device__ __forceinline__ void run_serial(const gridv::BatchArgs& A, int block,
             if constexpr (kPark && i > 0) {
                 const float4 a = park[64 * (4 * i - 4)], b = park[64 * (4 * i - 3)],
                              c = park[64 * (4 * i - 2)], d = park[64 * (4 * i - 1)];
-                P[i] = Sym{a.x, a.y, a.z, a.w, b.x, b.y};
+                J[i] = Sym{a.x, a.y, a.z, a.w, b.x, b.y};
                 h[i] = V3{b.z, b.w, c.x};
                 psd[i] = Six{{c.y, c.z, c.w}, {d.x, d.y, d.z}};
                 qd[i] = d.w;
             }
             const float qdd = kFdDer ? (kBias ? x[i] : 0.0f) : uu[i];
             const Six v = add_S(i, vl[i], qd[i]);
-            const Sym J = second_to_inertia(P[i]);
-            K[i] = momentum_moment(v, h[i], P[i]);
+            const float* c = C + i * kConstStride;
+            const float half = (float)(0.5 * ((double)c[12] + c[13] + c[14]));
+            K[i] = momentum_moment(v, h[i], second_moment(J[i], half));
             l[i] = v.l * mass_of(i) + cross(v.a, h[i]);
             Six a = add_S(i, Six{al[i].a + psd[i].a * qd[i], al[i].l + psd[i].l * qd[i]}, qdd);
-            const Six Ia = inertia(mass_of(i), h[i], J, a), Bv = bmul(K[i], l[i], v.a);
+            const Six Ia = inertia(mass_of(i), h[i], J[i], a), Bv = bmul(K[i], l[i], v.a);
             F[i] = Six{Ia.a + Bv.a, Ia.l + Bv.l};
             const Six s = cross_S(i, al[i]);
             pdd[i] = S::parent[i] < 0 ? s
@@ -621,18 +628,17 @@ __device__ __forceinline__ void run_serial(const gridv::BatchArgs& A, int block,
         static_for<B>([&](auto jj) {
             constexpr int j = B - 1 - decltype(jj)::v;
             constexpr int p = S::parent[j];
-            const Sym J = second_to_inertia(P[j]);
             Six f, u, w;
             V3 b;
             if (pri(j)) {
                 f = Six{cross(h[j], z[j]), z[j] * mc[j]};
                 b = cross(l[j], z[j]);
             } else {
-                f = Six{mul(J, z[j]), cross(z[j], h[j])};
+                f = Six{mul(J[j], z[j]), cross(z[j], h[j])};
                 b = z[j] * (K[j].c0.x + K[j].c1.y + K[j].c2.z) - tmul(K[j], z[j]);
             }
             {
-                const Six Ip = inertia(mc[j], h[j], J, pdd[j]);
+                const Six Ip = inertia(mc[j], h[j], J[j], pdd[j]);
                 const Six Sf = pri(j) ? Six{cross(z[j], F[j].l), zero3}
                                       : Six{cross(z[j], F[j].a), cross(z[j], F[j].l)};
                 u = Six{Ip.a + Sf.a, Ip.l + Sf.l};
@@ -640,7 +646,7 @@ __device__ __forceinline__ void run_serial(const gridv::BatchArgs& A, int block,
                 if constexpr (p >= 0) {                 // psd of the first body is zero
                     const Six Bp = bmul(K[j], l[j], psd[j].a);
                     u = Six{Bp.a * 2.0f + u.a, Bp.l * 2.0f + u.l};
-                    w = inertia(mc[j], h[j], J, psd[j]);
+                    w = inertia(mc[j], h[j], J[j], psd[j]);
                 }
                 if (!pri(j)) {
                     const Six Bs = bmul(K[j], l[j], z[j]);
@@ -684,9 +690,8 @@ __device__ __forceinline__ void run_serial(const gridv::BatchArgs& A, int block,
                 K[p].c2 = K[p].c2 + K[j].c2 + l[j] * r[j].z;
                 l[p] = l[p] + l[j];
                 F[p] = Six{F[p].a + F[j].a + cross(r[j], F[j].l), F[p].l + F[j].l};
-                move_moments(P[j], h[j], mc[j], r[j]);
-                P[p] = Sym{P[p].xx + P[j].xx, P[p].yy + P[j].yy, P[p].zz + P[j].zz,
-                           P[p].xy + P[j].xy, P[p].xz + P[j].xz, P[p].yz + P[j].yz};
+                move_inertia(J[j], h[j], mc[j], r[j]);
+                J[p] = J[p] + J[j];
                 h[p] = h[p] + h[j];
                 mc[p] += mc[j];
             }

@@ -6,7 +6,7 @@
 // (Group<g>: NB branches of shape S). Each lane keeps its own body's quantities in registers
 // and meets the others through LDS; a workgroup is one wavefront, so no barrier is needed.
 //
-// The formulation is that of grid_axes.hip. M^-1 comes from M = L^T L (sparse along ancestor
+// The formulation is that of grid_axes.hip. M^-1 comes from M = L^T D L (sparse along ancestor
 // paths), which every lane of a problem factors for itself from the rows of M in LDS: 57 (7-body chain) to 324 (18-body tree) FMAs in
 // registers against one LDS round trip per level for a shared factor. Lane j then solves for
 // column j of M^-1, dqdd/dq and dqdd/dqd.
@@ -284,28 +284,20 @@ __device__ __forceinline__ void run_team(const BatchArgs& A, int block, float* p
     }
     const float4* tf = reinterpret_cast<const float4*>(G::table()) + (br * B + i) * 6;
     const float4 t0 = tf[0], t1 = tf[1], t2 = tf[2], t3 = tf[3], t4 = tf[4], t5 = tf[5];
-    const V3 e0{t0.x, t0.y, t0.z}, e1{t0.w, t1.x, t1.y}, e2{t1.z, t1.w, t2.x};   // rows of E_T
     const V3 rT{t2.y, t2.z, t2.w};
-    const Sym PT{t3.x, t3.y, t3.z, t3.w, t4.x, t4.y};
+    const Sym JT{t3.x, t3.y, t3.z, t3.w, t4.x, t4.y};
+    const float half = 0.5f * (JT.xx + JT.yy + JT.zz);   // for the second moment
     const V3 hT{t4.z, t4.w, t5.x};
     const float m = t5.y, mC = t5.z;
     const bool pr = kPrism && t5.w != 0.0f;
 
-    // body axes along the parent's: the rows of E = E_z(q) E_T, or E_T
-    float sn = 0.0f, co = 1.0f;
-    if (!pr) {
-        const float rev = __builtin_amdgcn_fractf(qi * 0.159154943091895336f);
-        sn = __builtin_amdgcn_sinf(rev);
-        co = __builtin_amdgcn_cosf(rev);
-    }
-    Mat R{e0 * co + e1 * sn, e1 * co - e0 * sn, e2};
+    Mat R = joint_axes(pr, qi, V3{t0.x, t0.y, t0.z}, V3{t0.w, t1.x, t1.y}, V3{t1.z, t1.w, t2.x});
     V3 rb = tmul(R, rT);                               // r in body axes
     if (kPrism && pr)
         rb.z += qi;
     V3 a0 = {0.0f, 0.0f, 0.0f};                        // -g along the first body's axes
     if constexpr (kVel) {
-        const V3 g{G::a0()[0], G::a0()[1], G::a0()[2]};
-        a0 = tmul(R, g);
+        a0 = tmul(R, V3{G::a0()[0], G::a0()[1], G::a0()[2]});
     }
     if (depth == 0)
         R = Mat{{1.0f, 0.0f, 0.0f}, {0.0f, 1.0f, 0.0f}, {0.0f, 0.0f, 1.0f}};
@@ -324,6 +316,15 @@ __device__ __forceinline__ void run_team(const BatchArgs& A, int block, float* p
             R = Mat{mul(Q, R.c0), mul(Q, R.c1), mul(Q, R.c2)};
         }
         wave_lds_sync();
+    }
+    {                                                  // orthonormal again
+        const auto unit = [](V3 v) {
+            const float d = __builtin_fmaf(v.x, v.x, __builtin_fmaf(v.y, v.y, __builtin_fmaf(v.z, v.z, -1.0f)));
+            return v * (1.0f - 0.5f * d);
+        };
+        R.c2 = unit(R.c2);
+        R.c0 = unit(R.c0 - R.c2 * dot(R.c0, R.c2));
+        R.c1 = cross(R.c2, R.c0);
     }
     const V3 z = R.c2;
     const V3 r = depth == 0 ? V3{0.0f, 0.0f, 0.0f} : mul(R, rb);
@@ -425,9 +426,10 @@ __device__ __forceinline__ void run_team(const BatchArgs& A, int block, float* p
     }
 
     // ------------------------------------------------------------ the body's own inertia
-    Sym P = turn(R, PT);
+    Sym J = turn(R, JT);
     V3 h = mul(R, hT);
-    const Sym P1 = P;                                  // the body alone (for the qdd increment)
+    const Six self{mul(R, V3{JT.xz, JT.yz, JT.zz}), mul(R, V3{-hT.y, hT.x, 0.0f})};
+    const Sym J1 = J;                                  // the body alone (for the qdd increment)
     const V3 h1 = h;
     Mat K{};
     V3 l{};
@@ -435,14 +437,14 @@ __device__ __forceinline__ void run_team(const BatchArgs& A, int block, float* p
     if constexpr (kVel) {
         const Six v = add_S(vl, qd);
         l = v.l * m + cross(v.a, h);
-        K = momentum_moment(v, h, P);
+        K = momentum_moment(v, h, second_moment(J, half));
     }
     if constexpr (kForce) {
         const Six v = add_S(vl, qd);
         Six a = Six{al.a + psd.a * qd, al.l + psd.l * qd};
         if constexpr (!kBias)
             a = add_S(a, ui);
-        const Six Ia = inertia(m, h, second_to_inertia(P), a), Bv = bmul(K, l, v.a);
+        const Six Ia = inertia(m, h, J, a), Bv = bmul(K, l, v.a);
         F = Six{Ia.a + Bv.a, Ia.l + Bv.l};
     }
 
@@ -503,13 +505,13 @@ __device__ __forceinline__ void run_team(const BatchArgs& A, int block, float* p
     };
     constexpr int NF = kDer ? (kForce ? 7 : 6) : (kForce ? 4 : 3);
     constexpr int KO = kForce ? 16 : 10;               // where K and l begin
-    float ms = m;                                      // the mass that P and h stand for
+    float ms = m;                                      // the mass that J and h stand for
     sum_up(
         grids::Int<NF>{},
         [&](float (&o)[4 * NF], V3 d) {
-            Sym Q = P;
+            Sym Q = J;
             V3 g = h;
-            move_moments(Q, g, ms, d);
+            move_inertia(Q, g, ms, d);
             const float f[10] = {Q.xx, Q.yy, Q.zz, Q.xy, Q.xz, Q.yz, g.x, g.y, g.z, ms};
 #pragma unroll
             for (int e = 0; e < 10; ++e)
@@ -534,7 +536,7 @@ __device__ __forceinline__ void run_team(const BatchArgs& A, int block, float* p
                 o[e] = 0.0f;
         },
         [&](const float (&o)[4 * NF]) {
-            P = Sym{P.xx + o[0], P.yy + o[1], P.zz + o[2], P.xy + o[3], P.xz + o[4], P.yz + o[5]};
+            J = J + Sym{o[0], o[1], o[2], o[3], o[4], o[5]};
             h = h + V3{o[6], o[7], o[8]};
             ms += o[9];
             if constexpr (kVel)
@@ -555,18 +557,24 @@ __device__ __forceinline__ void run_team(const BatchArgs& A, int block, float* p
     const auto dot_me = [&](Six f) { return kPrism && pr ? dot(z, f.l) : dot(z, f.a); };
 
     // F1 = I^c S and M's row of this body
-    const Sym J = second_to_inertia(P);
     const Six F1 = kPrism && pr ? Six{cross(h, z), z * mC} : Six{mul(J, z), cross(z, h)};
     float Lf[B][B], dinv[B];
     if constexpr (kMass) {
         float* row = sM + me * Y::RS;
-        row[0] = dot_me(F1);
-        V3 n = F1.a, s = r;
+        // in double; the body's own part of M_ii is a constant, of the others a turned one
+        const V3D zd = wide(z), below = mul(J - J1, zd);
+        V3D n = below + wide(self.a), fl = cross(zd, wide(h - h1)) + wide(self.l);
+        if (kPrism && pr) {
+            n = cross(wide(h), zd);
+            fl = zd * mC;
+        }
+        row[0] = kPrism && pr ? mC : (float)(JT.zz + dot(zd, below));
+        V3 s = r;
 #pragma unroll
         for (int t = 0; t < MD; ++t) {
-            n = n + cross(s, F1.l);
+            n = n + cross(wide(s), fl);
             const float4 zk = fZ[anc[t]], rk = fR[anc[t]];
-            const float x = dot_S(zk, rk, Six{n, F1.l});
+            const float x = (float)dot(V3D{zk.x, zk.y, zk.z}, kPrism && rk.w != 0.0f ? fl : n);
             if (t < depth)
                 row[1 + t] = x;
             s = V3{rk.x, rk.y, rk.z};
@@ -593,7 +601,7 @@ __device__ __forceinline__ void run_team(const BatchArgs& A, int block, float* p
             for (int t = 0; t < T::depth(k); ++t)
                 Lf[k][T::anc_at(k, t)] = rowk[1 + t];
         }
-        gridq::ltl_factor<S>(Lf, dinv);
+        ltdl_factor<S>(Lf, dinv);
     }
 
     // ------------------------------------------------------------ qdd, or taubar
@@ -612,7 +620,7 @@ __device__ __forceinline__ void run_team(const BatchArgs& A, int block, float* p
 #pragma unroll
         for (int k = 0; k < B; ++k)
             xs[k] = x[k];
-        gridq::ltl_solve<S>(Lf, dinv, xs);
+        ltdl_solve<S>(Lf, dinv, xs);
         wave_lds_sync();
         if (i == 0) {
 #pragma unroll
@@ -633,7 +641,7 @@ __device__ __forceinline__ void run_team(const BatchArgs& A, int block, float* p
         wave_lds_sync();
         const Six da = path_sum();
         al = Six{al.a + da.a, al.l + da.l};
-        Six f = inertia(m, h1, second_to_inertia(P1), add_S(da, xi));
+        Six f = inertia(m, h1, J1, add_S(da, xi));
         sum_up(
             grids::Int<2>{},
             [&](float (&o)[8], V3 d) {
@@ -809,7 +817,7 @@ __device__ __forceinline__ void run_team(const BatchArgs& A, int block, float* p
 #pragma unroll
         for (int k = 0; k < B; ++k)
             mc[k] = (k == i) ? 1.0f : 0.0f;
-        gridq::ltl_solve<S>(Lf, dinv, mc);
+        ltdl_solve<S>(Lf, dinv, mc);
         // entries (k, i), k <= i, to both mirrored positions: exactly symmetric
 #pragma unroll
         for (int k = 0; k < B; ++k) {
@@ -821,11 +829,11 @@ __device__ __forceinline__ void run_team(const BatchArgs& A, int block, float* p
         tile_done(0);
     }
     if constexpr (kFdDer && kQ) {
-        gridq::ltl_solve<S>(Lf, dinv, cq);
+        ltdl_solve<S>(Lf, dinv, cq);
         put_column(kV ? 1 : 0, cq, -1.0f);
     }
     if constexpr (kFdDer && kV) {
-        gridq::ltl_solve<S>(Lf, dinv, cqd);
+        ltdl_solve<S>(Lf, dinv, cqd);
         put_column(kQ ? 2 : 1, cqd, -1.0f);
     }
 }
