@@ -101,6 +101,13 @@ bool analyse_topology(const int32_t* parent, int32_t n, Topology* out, std::stri
         inst.coff = coff;
         coff += shape.B * kConstStride;
         t.insts.push_back(inst);
+        if (shape.B > t.longest.bodies) {
+            t.longest.bodies = shape.B;
+            t.longest.levels = 0;
+            for (uint64_t anc : shape.anc)
+                t.longest.levels = std::max(t.longest.levels, 1 + __builtin_popcountll(anc));
+        }
+        t.longest.count += shape.B > 8 ? 1 : 0;
     }
     *out = std::move(t);
     return true;
@@ -156,10 +163,13 @@ int64_t workgroups_serial(const Topology& t, int64_t nknots)
 // A branch of more than 8 bodies: a lane that holds a whole problem would spill most of it
 bool long_branch(const Topology& t)
 {
-    for (const BranchShape& sh : t.shapes)
-        if (sh.B > 8)
-            return true;
-    return false;
+    return t.longest.bodies > 8;
+}
+
+// whether FD, M^-1, dID and the VJP ever run in the quad layout (grid_runtime.cpp: quad_op_long)
+bool quad_ops(const Topology& t)
+{
+    return t.longest.bodies <= 16 || !t.longest.shallow();
 }
 
 // one lane per body: knots per wavefront of a group of nb branches of one shape, as in
@@ -562,6 +572,7 @@ std::string generate_source(const Topology& t, const std::vector<float>& consts,
     emit_dispatch(os, "Inst", t.insts.size(), "template <int ST>\n__device__ void grid_dispatch(const grid::Args& a, int block)",
              "64 / @::S::L", "grid::run_branch<@, ST>(a, b)");
     os << "#define GRID_LONG_BRANCH " << (long_branch(t) ? 1 : 0) << "\n";
+    os << "#define GRID_QUAD_OPS " << (quad_ops(t) ? 1 : 0) << "\n";
     os << "#line 1 \"grid_fused.hip\"\n";
     os << grid_fused_src;
     if (!long_branch(t)) {

@@ -66,12 +66,20 @@ struct BranchInst {
     uint64_t prism = 0;              // local bodies on prismatic joints
 };
 
+// the longest branch of a robot (the most bodies), and how many branches have more than 8
+struct LongBranch {
+    int bodies = 0, levels = 0;      // levels: bodies on its longest path from the base
+    int count = 0;
+    bool shallow() const { return bodies >= 2 * levels; }
+};
+
 struct Topology {
     int n = 0;
     std::vector<int> parent;
     std::vector<BranchShape> shapes;
     std::vector<BranchInst> insts;
     int waves = 1;                   // quad layout: wavefronts per workgroup (max W)
+    LongBranch longest;
 };
 
 // Staged pipeline workspace per knot (floats): c [n], the factors L of every branch
@@ -155,6 +163,7 @@ int fused_variant_for(grid_model m, int32_t N);
 int kernel_of(grid_model m, int variant, int32_t N);
 const char* kernel_name(grid_model m, int32_t N);
 bool long_branch(const Topology& t);
+bool quad_ops(const Topology& t);
 void load_tuning(grid_model m);
 std::string cache_dir();
 

@@ -279,9 +279,9 @@ extern "C" __global__ void __launch_bounds__(64) grid_op_id(gridq::OpArgs args)
     grid_dispatch_op<gridq::kOpId>(args, (int)blockIdx.x);
 }
 
-// a robot with a branch of more than 8 bodies runs the forms with one lane per body instead (its
-// columns of M would take several passes here)
-#if !GRID_LONG_BRANCH
+// (a robot whose longest branch has more than 16 bodies on few levels runs one lane per body at every
+// size: its columns of M would take two passes here)
+#if GRID_QUAD_OPS
 
 extern "C" __global__ void __launch_bounds__(64) grid_op_fd(gridq::OpArgs args)
 {
@@ -303,6 +303,6 @@ extern "C" __global__ void __launch_bounds__(64) grid_op_vjp(gridq::OpArgs args)
     grid_dispatch_op<gridq::kOpVjp>(args, (int)blockIdx.x);
 }
 
-#endif  // GRID_LONG_BRANCH
+#endif  // GRID_QUAD_OPS
 
 #endif  // GRID_PIPE_ONLY

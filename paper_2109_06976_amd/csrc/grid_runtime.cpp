@@ -242,10 +242,54 @@ const char* kernel_name(grid_model m, int32_t N)
     return kKernels[kernel_of(m, fused_variant_for(m, N), N)];
 }
 
-// The largest batch of a robot with a long branch that the three-role kernel runs as fast as one
-// lane per body in halves (humanoid30 at 1, 4, 16, 128 and 256 knots 11.4 / 11.5 / 11.7 / 12.0 / 16.2
-// us, and 11.3 up to 128 knots, 11.7 at 256: a quarter of the wavefronts)
-constexpr int kPipeLongKnots = 8;
+// A robot with a branch of more than 8 bodies: the three-role kernel while the wavefronts of such
+// branches fit one per SIMD, one lane per body beyond (chains of 9, 12, 16 and 17 at 256 knots, one per
+// SIMD: 5.7 / 7.6 / 10.5 / 14.9 us by the former, 8.7 / 10.9 / 14.4 / 15.7 by the latter; at 512 8.8 /
+// 13.8 / 19.7 / 28 and 9.1 / 11.2 / 14.9 / 16.7). Not at all for a branch of more than 16 bodies on few
+// levels: role C is missing and each column sweeps over all bodies, where one lane per body follows
+// the levels (18 bodies on 9 levels at 128 knots 12.0 and 11.5 us)
+static bool pipe_long(grid_model m, int64_t N)
+{
+    const LongBranch& b = m->topo.longest;
+    return !(b.bodies > 16 && b.shallow()) &&
+           N * b.count * pipe_waves(m->topo) <= 4 * (int64_t)m->compute_units;
+}
+
+// ID, FD, M^-1, dID and the VJP of such a robot in the quad layout? Each of its workgroups repeats the
+// sweeps over all bodies of one knot, so by the wavefronts of the long branches per compute unit (us,
+// quad layout and one lane per body):
+//   FD     chain of 9 at 1024 knots 6.2 and 6.1; of 12 at 256 and 512 6.5 / 7.6 and 7.8 / 7.7; of 16 at 256
+//          9.2 and 10.3; of 17 at 128 and 256 11.3 / 11.4 and 11.7 / 11.7; 16 bodies on 7 levels 7.2 and 6.5
+//   M^-1   chain of 9 at 2048 5.1 and 5.5, at 4096 7.8 and 6.0; of 12 at 1024 5.2 and 6.5, at 2048 7.6 and
+//          6.8; of 16 at 1024 7.2 and 8.5; of 17 at 128 9.3 and 9.7
+//   dID    chain of 9 at 256 5.4 and 7.5, at 512 7.9 and 7.5; of 12 and 16 at 512 7.8 / 9.9 and 8.7 / 10.3,
+//          at 1024 13.8 / 18.2 and 8.9 / 10.6; of 17 at 256 10.7 and 11.8; 12 bodies on 6 levels 7.4 and 7.0
+//   VJP    chain of 9 at 1024 7.4 and 8.6, at 2048 11.2 and 9.0; of 16 at 1024 14.2 and 14.3; of 17 at 256
+//          15.2 and 15.6; 12 bodies on 6 levels 8.2 and 7.9
+// 18 bodies on 9 levels run one lane per body at every size (FD at 16 knots 9.6 and 7.5). ID is shorter in
+// the quad layout at every size (humanoid30 at 4096 knots 5.9 and 7.1)
+static bool quad_op_long(grid_model m, int op, int64_t N)
+{
+    const LongBranch& b = m->topo.longest;
+    const int64_t cu = m->compute_units;
+    if (op == kOpId)
+        return true;
+    // few levels
+    if (b.bodies > 16 ? b.shallow()
+                      : (op == kOpFd ? b.bodies > 2 * b.levels : op != kOpMinv && b.shallow()))
+        return false;
+    const int64_t waves = N * b.count * (op == kOpIdGrad ? m->topo.waves : 1);
+    switch (op) {
+    case kOpFd:
+        return waves <= (b.bodies <= 10 ? 4 : b.bodies <= 16 ? 2 : 1) * cu;
+    case kOpMinv:
+        return waves <= (b.bodies <= 10 ? 8 : b.bodies <= 16 ? 4 : 1) * cu;
+    case kOpIdGrad:
+        return waves <= (b.bodies <= 11 ? 2 : 4) * cu;
+    default:
+        return waves <= 4 * cu;
+    }
+}
 
 int fused_variant_for(grid_model m, int32_t N)
 {
@@ -283,9 +327,7 @@ int fused_variant_for(grid_model m, int32_t N)
 // and 8.4, at 16384 9.8 and 8.9). Up to five bodies the latter also rounds less (grid_axes.hip)
 static bool lane_per_body(grid_model m, int64_t N)
 {
-    int longest = 0;
-    for (const BranchShape& s : m->topo.shapes)
-        longest = std::max(longest, s.B);
+    const int longest = m->topo.longest.bodies;
     return longest > 8 || (longest > 5 && workgroups_team(m->topo, N) <=
                                               2 * (int64_t)m->compute_units * (longest - 4));
 }
@@ -310,10 +352,9 @@ int kernel_of(grid_model m, int variant, int32_t N)
     const auto problems = [&] {
         return problems_in_halves(m, N) ? kVariantSerial2 : kVariantSerial;
     };
-    if (variant == kVariantPipe && (!long_branch(m->topo) || N <= kPipeLongKnots))
+    if (variant == kVariantPipe && (!long_branch(m->topo) || pipe_long(m, N)))
         return variant;
-    // a long branch: a lane does not hold it, and the three-role kernel gives it a workgroup
-    if (long_branch(m->topo))
+    if (long_branch(m->topo))              // a lane does not hold it
         return variant == kVariantTeam2 ? kVariantTeam : bodies();
     switch (variant) {
     case kVariantQuad:
@@ -655,7 +696,7 @@ grid_status grid_model_create(const grid_model_desc* desc, int32_t device, uint3
     static const char* const kOps[kNumOps] = {"grid_op_id", "grid_op_fd", "grid_op_minv",
                                               "grid_op_idgrad", "grid_op_vjp"};
     for (int k = 0; k < kNumOps && e == hipSuccess; ++k)
-        if (k == kOpId || !long_branch(m->topo))   // the others run one lane per body there
+        if (k == kOpId || quad_ops(m->topo))
             e = hipModuleGetFunction(&m->op[k], m->module, kOps[k]);
     static const char* const kTeamOps[kNumOps] = {nullptr, "grid_team_fd", "grid_team_minv",
                                                   "grid_team_idgrad", "grid_team_vjp"};
@@ -775,12 +816,10 @@ static grid_status launch_op(grid_model m, int op, int32_t N, const float* q, co
     // The quad layout's quads repeat the shared sweeps: beyond two wavefronts of it per SIMD the
     // batch forms take over. ID, FD and M^-1 then run one lane per problem (chain7 FD at 4096
     // knots, two per SIMD: 6.1 us, 5.4 in that form, M^-1 4.2 and 4.7, at 8192 6.0 and 4.8; ID
-    // beside its kernel), dID and the VJP one lane per body first. A long branch runs one lane per
-    // body at every size (humanoid30 at 16 knots: FD 9.6 us in the quad layout, 8.6), but for ID
-    // (at 512 and 4096 knots 5.7 and 5.9 us in the quad layout, 5.2 and 7.1).
+    // beside its kernel), dID and the VJP one lane per body first. Long branches: quad_op_long
     const bool longb = long_branch(m->topo);
-    if (blocks * waves > 8 * (int64_t)m->compute_units ? m->team_op[op] || m->serial_op[op]
-                                                       : longb && m->team_op[op]) {
+    const bool quad = longb ? quad_op_long(m, op, N) : blocks * waves <= 8 * (int64_t)m->compute_units;
+    if (!quad) {
         const bool body = longb || ((op == kOpIdGrad || op == kOpVjp) && lane_per_body(m, N));
         // (dID with one lane per body does not gain: humanoid30 at 128 knots 9.0 and 8.3 us, at 2048
         // 11.8 and 12.9)
