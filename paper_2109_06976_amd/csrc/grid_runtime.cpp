@@ -300,7 +300,8 @@ int fused_variant_for(grid_model m, int32_t N)
         return m->tuned.back().second;
     // untuned: the three-role kernel while its wavefronts fit one per SIMD of the device (the
     // lowest-latency form), then build 0 while its fit (it has fewer: chain7 at 1024 knots 6.6 us,
-    // build 4 6.8, build 1 7.5; quad12 at 512 4.3 / 4.4 / 5.1), the batch kernels beyond (indices
+    // build 4 6.8, build 1 7.5; quad12 at 512 4.3 / 4.4 / 5.1; a chain of 2 at 4096 3.3 / 3.4 / 3.05,
+    // of 1 at 8192 2.3 by build 0, 2.1 by build 1: not for such), the batch kernels beyond (indices
     // 1, 6 and 5: kernel_of says which). A robot with a long branch keeps the index of the
     // three-role build up to 4096 knots
     const int64_t simds = 4 * (int64_t)m->compute_units;
@@ -308,7 +309,7 @@ int fused_variant_for(grid_model m, int32_t N)
         return kVariantPipe;
     if (long_branch(m->topo))
         return N <= 4096 ? kVariantPipe : kVariantSerial4;
-    if (workgroups_quad(m->topo, N) * m->topo.waves <= simds)
+    if (m->topo.longest.bodies > 2 && workgroups_quad(m->topo, N) * m->topo.waves <= simds)
         return kVariantQuad;
     if (N >= 128 * (int64_t)m->compute_units)
         return kVariantSerial;
