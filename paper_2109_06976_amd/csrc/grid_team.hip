@@ -539,7 +539,7 @@ __device__ __forceinline__ void run_team(const BatchArgs& A, int block, float* p
             J = J + Sym{o[0], o[1], o[2], o[3], o[4], o[5]};
             h = h + V3{o[6], o[7], o[8]};
             ms += o[9];
-            if constexpr (kVel)
+            if constexpr (kForce)
                 F = Six{F.a + V3{o[10], o[11], o[12]}, F.l + V3{o[13], o[14], o[15]}};
             if constexpr (kDer) {
                 K.c0 = K.c0 + V3{o[KO], o[KO + 1], o[KO + 2]};
@@ -669,6 +669,7 @@ __device__ __forceinline__ void run_team(const BatchArgs& A, int block, float* p
             fQ1[me] = float4{pdd.l.y, pdd.l.z, 0.0f, 0.0f};
         }
         if constexpr (!T::chain()) {                   // entries off the ancestor paths
+            wave_lds_sync();                           // M's rows, in the same place, have been read
             for (int e = lane; e < Y::cols / 4; e += 64)
                 reinterpret_cast<float4*>(sT)[e] = float4{0.0f, 0.0f, 0.0f, 0.0f};
         }
