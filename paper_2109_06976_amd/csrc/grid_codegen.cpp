@@ -166,6 +166,12 @@ bool long_branch(const Topology& t)
     return t.longest.bodies > 8;
 }
 
+// whether dFD, dID and the VJP ever run one lane per body by the rule (grid_runtime.cpp: lane_per_body)
+bool may_run_by_bodies(const Topology& t)
+{
+    return t.longest.bodies > 5;
+}
+
 // whether FD, M^-1, dID and the VJP ever run in the quad layout (grid_runtime.cpp: quad_op_long)
 bool quad_ops(const Topology& t)
 {
@@ -548,6 +554,7 @@ static void emit_dispatch(std::ostringstream& os, const char* type, size_t count
 static void emit_team(std::ostringstream& os, const Topology& t, const std::vector<float>& consts)
 {
     emit_groups(os, t, consts);
+    os << "#define GRID_LANE_PER_BODY " << (may_run_by_bodies(t) ? 1 : 0) << "\n";
     os << "#line 1 \"grid_team.hip\"\n";
     os << grid_team_src;
     os << "\n// generated: workgroup -> (group of branches, knots), one lane per body\n";

@@ -164,6 +164,7 @@ int kernel_of(grid_model m, int variant, int32_t N);
 const char* kernel_name(grid_model m, int32_t N);
 bool long_branch(const Topology& t);
 bool quad_ops(const Topology& t);
+bool may_run_by_bodies(const Topology& t);
 void load_tuning(grid_model m);
 std::string cache_dir();
 

@@ -329,8 +329,9 @@ int fused_variant_for(grid_model m, int32_t N)
 static bool lane_per_body(grid_model m, int64_t N)
 {
     const int longest = m->topo.longest.bodies;
-    return longest > 8 || (longest > 5 && workgroups_team(m->topo, N) <=
-                                              2 * (int64_t)m->compute_units * (longest - 4));
+    return longest > 8 || (may_run_by_bodies(m->topo) &&
+                           workgroups_team(m->topo, N) <=
+                               2 * (int64_t)m->compute_units * (longest - 4));
 }
 
 // Two wavefronts with half of the outputs each: one lane per problem while there is a SIMD for
@@ -702,7 +703,8 @@ grid_status grid_model_create(const grid_model_desc* desc, int32_t device, uint3
     static const char* const kTeamOps[kNumOps] = {nullptr, "grid_team_fd", "grid_team_minv",
                                                   "grid_team_idgrad", "grid_team_vjp"};
     for (int k = 0; k < kNumOps && e == hipSuccess; ++k)
-        if (kTeamOps[k])
+        if (kTeamOps[k] && (k == kOpFd || k == kOpMinv ? long_branch(m->topo)
+                                                       : may_run_by_bodies(m->topo)))
             e = hipModuleGetFunction(&m->team_op[k], m->module, kTeamOps[k]);
     static const char* const kSerialOps[kNumOps] = {"grid_serial_id", "grid_serial_fd", "grid_serial_minv",
                                                     "grid_serial_idgrad", "grid_serial_vjp"};
@@ -719,7 +721,7 @@ grid_status grid_model_create(const grid_model_desc* desc, int32_t device, uint3
     if (e == hipSuccess)
         e = hipModuleLoadData(&m->pipe_module, pipe_code.data());
     for (int k : {kVariantPipe, kVariantTeam, kVariantTeam2})
-        if (e == hipSuccess)
+        if (e == hipSuccess && (k != kVariantTeam2 || may_run_by_bodies(m->topo)))
             e = hipModuleGetFunction(&m->fused_variant[k], m->pipe_module, kKernels[k]);
     if (e != hipSuccess) {
         grid_model_destroy(m);

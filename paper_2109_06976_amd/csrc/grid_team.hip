@@ -862,6 +862,7 @@ extern "C" __global__ void __launch_bounds__(64) grid_fdgrad_team(grid::Args arg
 // forces. humanoid30 at 128, 1024, 1536 and 2048 knots 14.1 / 16.0 / 16.6 / 17.5 us by one, 11.5 /
 // 13.7 / 15.1 / 17.4 by two, at 4096 24.1 and 30.0; chain7 at 1024, 4096 and 8192 8.4 / 9.1 / 10.0
 // and 7.5 / 8.5 / 9.7, at 16384 12.7 and 18.4
+#if GRID_LANE_PER_BODY
 extern "C" __global__ void __launch_bounds__(64) grid_fdgrad_team_halves(grid::Args args)
 {
     const gridv::BatchArgs a{args.nknots, args.q, args.qd, args.tau, nullptr,
@@ -872,8 +873,12 @@ extern "C" __global__ void __launch_bounds__(64) grid_fdgrad_team_halves(grid::A
     else
         grid_dispatch_t<gridv::kFdGradV>(a, b - half);
 }
+#endif
 
 #else
+
+// (reached by robots with a branch of more than 8 bodies)
+#if GRID_LONG_BRANCH
 
 extern "C" __global__ void __launch_bounds__(64) grid_team_fd(gridq::OpArgs x)
 {
@@ -887,6 +892,9 @@ extern "C" __global__ void __launch_bounds__(64) grid_team_minv(gridq::OpArgs x)
     grid_dispatch_t<gridt::kMinv>(a, (int)blockIdx.x);
 }
 
+#endif  // GRID_LONG_BRANCH
+#if GRID_LANE_PER_BODY
+
 extern "C" __global__ void __launch_bounds__(64) grid_team_idgrad(gridq::OpArgs x)
 {
     const gridv::BatchArgs a{x.nknots, x.q, x.qd, x.u, nullptr, x.out0, x.out1, nullptr, nullptr};
@@ -898,5 +906,7 @@ extern "C" __global__ void __launch_bounds__(64) grid_team_vjp(gridq::OpArgs x)
     const gridv::BatchArgs a{x.nknots, x.q, x.qd, x.u, x.u2, x.out0, x.out1, x.out2, nullptr};
     grid_dispatch_t<gridt::kVjp>(a, (int)blockIdx.x);
 }
+
+#endif  // GRID_LANE_PER_BODY
 
 #endif  // GRID_PIPE_ONLY
