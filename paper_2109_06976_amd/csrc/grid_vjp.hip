@@ -73,7 +73,7 @@ grid_dt_kernel(int nknots, int n, int kpb, unsigned magic_n, unsigned magic_2n, 
         const float eye = i == j ? 1.0f : 0.0f;
         float* a = A0 + k * 2 * nn + e;                        // knot k's A starts at 4 k n^2
         a[0] = (left ? eye : dt * eye) + dt2 * d;
-        a[2 * nn] = (left ? 0.0f : eye) + dt * d;
+        a[2 * nn] = left ? dt * d : eye + dt * d;
     }
     for (unsigned e = threadIdx.x; e < knots * nn; e += 256) {
         const unsigned k = div_small(div_small(e, n, magic_n), n, magic_n);
