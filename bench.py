@@ -4,9 +4,11 @@
 One step = one batched call of the whole path (transforms, RNEA, M and its factor,
 M^-1, qdd, RNEA at qdd, dRNEA forward and backward, -M^-1 dtau) over 128 knot points, as
 one fused kernel launch, with inputs and outputs resident in device memory. Prints one
-JSON line.
+JSON line: the contract's fields and a short form of what follows (the line stays under 6000
+characters, so that whoever keeps only the end of the output keeps all of it); the whole record
+goes to the file that --details names.
 
-Also reported (extra fields of the same line):
+Also reported:
   plain         the staged pipeline (five launches, intermediates in device memory) on
                 the same batch, and fused_vs_plain = plain step time / fused step time;
   roofline      the fused kernel's algorithmic FLOP rate against the FP32 vector peak,
@@ -115,6 +117,8 @@ def parse():
     ap.add_argument("--build", type=int, default=-1,
                     help="pin one build of the fused kernel (skips the per-build timings and "
                          "the autotuner; used for profiling one kernel)")
+    ap.add_argument("--details", default=os.path.join(ROOT, "bench_details.json"),
+                    help="file for the whole record ('' for none)")
     ap.add_argument("--copy-calibration-mb", type=float, default=0.0,
                     help="also run a plain device copy of this size (for counter scaling)")
     return ap.parse_args()
@@ -577,6 +581,44 @@ def cpu_baseline(args, robot, kn, synth):
         "timer": "CLOCK_MONOTONIC (time.monotonic) around each batch call; mean and median"}
 
 
+# fields of the record that the printed line repeats as they are, beside the contract's
+LINE_FIELDS = ("fused_vs_plain", "tuned", "autograd")
+
+
+def headline(record):
+    """The printed line: the contract's fields whole, the rest by its main figures."""
+    keep = ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step",
+            "higher_is_better", "scaling", "vs_baseline", "dtype", "data", "config", "roofline")
+    out = {k: record[k] for k in keep + LINE_FIELDS if k in record}
+    if "plain" in record:
+        out["plain"] = {k: record["plain"][k] for k in ("value", "unit", "ms_per_step")}
+    if "builds" in record:
+        out["builds_us"] = {k: v["kernel_avg_us"] for k, v in record["builds"].items()}
+    if "sweep" in record:
+        out["sweep_us"] = {k: round(v["ms_per_step"] * 1e3, 2) for k, v in record["sweep"].items()}
+    if "io_inclusive" in record:
+        io = record["io_inclusive"]
+        out["io_inclusive_us"] = {"pinned": round(io["wall_ms_per_call"] * 1e3, 2),
+                                  "pageable": round(io["pageable"]["wall_ms_per_call"] * 1e3, 2),
+                                  **{k: round(v["wall_ms_per_call"] * 1e3, 2)
+                                     for k, v in io["mapped"].items()}}
+    if "served" in record:      # p50 and p99 by mode and request rate
+        out["served_us"] = {
+            mode: {rate: [round(r["p50_us"], 1), round(r["p99_us"], 1)]
+                   for rate, r in rates.items() if isinstance(r, dict) and "p50_us" in r}
+            for mode, rates in record["served"].items()
+            if isinstance(rates, dict) and any(isinstance(r, dict) and "p50_us" in r
+                                               for r in rates.values())}
+    if "mixed" in record:
+        out["mixed_us"] = {plan: {mode: r["us_per_step"] for mode, r in modes.items()
+                                  if isinstance(r, dict) and "us_per_step" in r}
+                           for plan, modes in record["mixed"].items() if isinstance(modes, dict)}
+    if "cpu_baseline" in record:
+        out["cpu_baseline"] = {k: v for k, v in record["cpu_baseline"].items()
+                               if k in ("value", "unit", "cores", "kind", "sample")}
+    return out
+
+
 def main():
     args = parse()
     world = int(os.environ.get("WORLD_SIZE", "1"))
@@ -624,6 +666,8 @@ def main():
         for b in range(len(grid.BUILD_KERNELS)):
             grid.tune_apply(model, {1 << 22: b})
             name = grid.kernel_for(model, N)
+            if name in builds:      # another index of the same kernel
+                continue
             st, ks = time_steps(torch, launch, max(200, args.steps // 10), 50)
             builds[name] = {"us_per_step": round(st * 1e6, 3),
                             "kernel_avg_us": round(ks * 1e6, 3)}
@@ -797,7 +841,10 @@ def main():
         progress("cpu baseline done")
 
     model.close()
-    print(json.dumps(result), flush=True)
+    if args.details:
+        with open(args.details, "w") as f:
+            json.dump(result, f)
+    print(json.dumps(headline(result)), flush=True)
 
 
 if __name__ == "__main__":
