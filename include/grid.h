@@ -445,7 +445,7 @@ grid_status grid_minv(grid_model m, int32_t N, const float* q, float* Minv, void
 /* M(q)^-1 by a chosen route, to compare the paper's direct inverse with the factorisation
  * the fused kernels use (Sec. IV-B lists the direct inverse of Carpentier and Mansard):
  *   GRID_MINV_QUAD         grid_minv itself (columns of M, L^T L, solves: quad layout; one lane
- *                          per problem for large batches, per body for long branches);
+ *                          per problem for large batches, per body for those of long branches);
  *   GRID_MINV_LANE_LTL     one lane per knot and branch: M by composite rigid bodies,
  *                          M = L^T L along ancestor paths, B triangular solve pairs;
  *   GRID_MINV_LANE_DIRECT  one lane per knot and branch: the direct articulated-body
@@ -486,15 +486,16 @@ grid_status grid_fd_vjp_adjoint(grid_model m, int32_t N, const float* q, const f
  * dtau/dq; M^-1), the shortest dependency chain. Build 5 gives each (knot, branch) problem one
  * lane (no repeated work: the fewest instructions per knot, the longest latency). Build 1 gives
  * each body of a problem one lane, so that a wavefront holds several problems, up to a batch
- * size that depends on the longest branch (none for branches of up to 4 bodies), and one
+ * size that depends on the longest branch (none for branches of up to 5 bodies), and one
  * lane per problem beyond. Either runs as two wavefronts with half of the outputs each while the
  * device holds them side by side. Builds 3 and 6 are the same as build 1 (indices that tables may
  * hold); build 2 is one lane per body and build 7 one lane per problem, never in halves.
- * A robot with a base branch of more than 8 bodies runs one lane per body as every build but 4,
- * and as build 4 for batches of more than 8 knots (its long branch does not fit one lane, and the
- * three-role kernel gives it a workgroup per knot).
+ * A robot with a base branch of more than 8 bodies runs one lane per body as every build but 4
+ * (its long branch does not fit one lane), and as build 4 once the wavefronts of such branches
+ * exceed one per SIMD of the device, or from 9 knots on if its longest branch has more than 16 bodies
+ * and at least two per level of the tree.
  * Untuned, a batch runs build 4 while its wavefronts fit one per SIMD of the device, build 0
- * while its fit, build 1 beyond, build 6 from 64 knots per compute unit and build 5 from 128,
+ * while its fit (not for branches of one or two bodies), build 1 beyond, build 6 from 64 knots per compute unit and build 5 from 128,
  * except for a robot with a base branch of more than 8 bodies: build 4 up to 4096 knots, build 6
  * beyond.
  * grid_tune times each build on the model's

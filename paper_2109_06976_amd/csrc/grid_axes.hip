@@ -15,7 +15,8 @@
 // the inertia I^c_j, the force f^c_j and B^c_j with B v = v x* I v, and with
 //   F1_j = I^c_j S_j,  b_j = B^c_j^T S_j,
 //   u_j = 2 B^c_j psd_j + I^c_j pdd_j + S_j x* f^c_j,   w_j = 2 (B^c_j S_j + I^c_j psd_j)
-// they are, for i = j or i an ancestor of j,
+// they are, for i = j or i an ancestor of j (the analytical derivatives by spatial vector algebra of
+// Singh, Russell and Wensing, RA-L 2022; the particle form of B below is this library's),
 //   M_ij = S_i . F1_j,   dtau_i/dq_j = S_i . u_j,   dtau_i/dqd_j = S_i . w_j,
 //   dtau_j/dq_i = 2 b_j . psd_i + F1_j . pdd_i,
 //   dtau_j/dqd_i = 2 (b_j . S_i + F1_j . psd_i)         (i an ancestor of j),

@@ -245,14 +245,16 @@ const char* kernel_name(grid_model m, int32_t N)
 // A robot with a branch of more than 8 bodies: the three-role kernel while the wavefronts of such
 // branches fit one per SIMD, one lane per body beyond (chains of 9, 12, 16 and 17 at 256 knots, one per
 // SIMD: 5.7 / 7.6 / 10.5 / 14.9 us by the former, 8.7 / 10.9 / 14.4 / 15.7 by the latter; at 512 8.8 /
-// 13.8 / 19.7 / 28 and 9.1 / 11.2 / 14.9 / 16.7). Not at all for a branch of more than 16 bodies on few
-// levels: role C is missing and each column sweeps over all bodies, where one lane per body follows
-// the levels (18 bodies on 9 levels at 128 knots 12.0 and 11.5 us)
+// 13.8 / 19.7 / 28 and 9.1 / 11.2 / 14.9 / 16.7). For a branch of more than 16 bodies on few levels up
+// to 8 knots only, where both take the same (18 bodies on 9 levels 11.4 to 11.7 and 11.6 us; at 128 knots
+// 12.0 and 11.5): role C is missing and each column sweeps over all bodies, where one lane per body
+// follows the levels. Those few keep build 4 bit for bit what a launch over several robots gives
 static bool pipe_long(grid_model m, int64_t N)
 {
     const LongBranch& b = m->topo.longest;
-    return !(b.bodies > 16 && b.shallow()) &&
-           N * b.count * pipe_waves(m->topo) <= 4 * (int64_t)m->compute_units;
+        if (b.bodies > 16 && b.shallow())
+        return N <= 8;
+    return N * b.count * pipe_waves(m->topo) <= 4 * (int64_t)m->compute_units;
 }
 
 // ID, FD, M^-1, dID and the VJP of such a robot in the quad layout? Each of its workgroups repeats the

@@ -829,7 +829,7 @@ JOINT_REVOLUTE, JOINT_PRISMATIC, JOINT_FIXED = 0, 1, 2
 # each build's kernel. Builds 1, 3 and 6 leave one lane per body for one lane per problem as
 # batches grow; up to a batch size either runs as its _halves kernel (two wavefronts with half of
 # the outputs each), except as builds 2 and 7. A robot with a base branch of more than 8 bodies runs
-# grid_fdgrad_team as all of them but build 4, and as build 4 beyond 8 knots
+# grid_fdgrad_team as all of them but build 4, and as build 4 beyond one wavefront per SIMD
 BUILD_KERNELS = ("grid_fdgrad_quad", "grid_fdgrad_team", "grid_fdgrad_team", "grid_fdgrad_team",
                  "grid_fdgrad_pipe", "grid_fdgrad_serial", "grid_fdgrad_team",
                  "grid_fdgrad_serial")

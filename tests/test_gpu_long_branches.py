@@ -47,11 +47,12 @@ def test_gradient_on_both_sides_of_the_three_role_kernels_line(orc, name):
         m.close()
 
 
-def test_shallow_long_branch_runs_one_lane_per_body():
+def test_shallow_long_branch_runs_one_lane_per_body_beyond_a_few_knots():
     import torch  # noqa: F401
     m = grid.Model(synth.humanoid30())
     try:
-        assert {grid.kernel_for(m, N) for N in (1, 8, 128)} == {"grid_fdgrad_team_halves"}
+        assert {grid.kernel_for(m, N) for N in (1, 8)} == {"grid_fdgrad_pipe"}
+        assert {grid.kernel_for(m, N) for N in (9, 128)} == {"grid_fdgrad_team_halves"}
     finally:
         m.close()
 
