@@ -486,7 +486,7 @@ grid_status grid_fd_vjp_adjoint(grid_model m, int32_t N, const float* q, const f
  * dtau/dq; M^-1), the shortest dependency chain. Build 5 gives each (knot, branch) problem one
  * lane (no repeated work: the fewest instructions per knot, the longest latency). Build 1 gives
  * each body of a problem one lane, so that a wavefront holds several problems, up to a batch
- * size that depends on the longest branch (none for branches of up to 5 bodies), and one
+ * size that depends on the longest branch (none for branches of up to 4 bodies), and one
  * lane per problem beyond. Either runs as two wavefronts with half of the outputs each while the
  * device holds them side by side. Builds 3 and 6 are the same as build 1 (indices that tables may
  * hold); build 2 is one lane per body and build 7 one lane per problem, never in halves.

@@ -38,7 +38,7 @@
 // and here: M^-1 of quad12 0.80 and 0.78, chain7 7.8 and 5.9, humanoid30 6.1 and 4.9; qdd 0.98 and
 // 0.90, 9.4 and 7.2, 7.7 and 6.3; dqdd/dq 3.1 and 2.95, 26 and 19.5, 21 and 17.7 (without these: M^-1
 // 2.25, 8.2 and 7.8). It costs 3 to 5% of a launch: humanoid30 at 4096 knots 23.5 and 24.2 us, chain7 at
-// 65536 20.2 and 21.0.
+// 65536 20.2 and 21.0. Short branches turned in float: quad12 dqdd/dq 3.16, a launch 2 to 4% shorter.
 
 namespace gridv {
 

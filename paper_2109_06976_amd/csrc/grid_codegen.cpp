@@ -169,7 +169,7 @@ bool long_branch(const Topology& t)
 // whether dFD, dID and the VJP ever run one lane per body by the rule (grid_runtime.cpp: lane_per_body)
 bool may_run_by_bodies(const Topology& t)
 {
-    return t.longest.bodies > 5;
+        return t.longest.bodies > 4;
 }
 
 // whether FD, M^-1, dID and the VJP ever run in the quad layout (grid_runtime.cpp: quad_op_long)

@@ -322,12 +322,13 @@ int fused_variant_for(grid_model m, int32_t N)
 
 // One lane per body, or one per problem? The latter issues a third of the instructions but takes
 // the same time for 64 knots as for 16384, longer the longer the branch: the former while its
-// wavefronts are at most two per compute unit for each body of the longest branch beyond four
-// (dFD, by body and by problem: chain of 4 at 1024 knots 5.8 and 5.4 us; of 5 at 4096, 1.3 per
-// unit, 7.4 and 7.2; of 6 at 8192, 3.2 per unit, 8.8 and 9.4, at 16384 11.1 and 9.9; of 7 at 8192,
-// 3.6 per unit, 10.2 and 12.1, at 16384 12.9 both; of 8 at 16384, 8 per unit, 14.7 and 18.6, at
-// 32768 27.8 and 19.9; quad12, branches of 3, at 4096 6.8 and 6.1; dID of a chain of 7 at 8192 7.6
-// and 8.4, at 16384 9.8 and 8.9). Up to five bodies the latter also rounds less (grid_axes.hip)
+// wavefronts are at most two per compute unit for each body of the longest branch beyond four (dFD, us,
+// best by body and best by problem: chain of 3 at 4096 knots 5.5 and 4.7; of 5 at 4096, 1.3 per unit,
+// 6.9 and 7.9, at 16384 10.0 and 9.1; of 6 at 8192, 3.2 per unit, 9.2 and 10.4, at 16384 12.0 and 11.0; of 7
+// at 8192, 3.6 per unit, 10.4 and 13.2, at 16384 13.7 and 13.9; of 8 at 16384, 8 per unit, 15.6 and 18.2,
+// at 32768 27.4 and 19.8; dID of a chain of 7 at 8192 7.9 and 8.4, at 16384 9.8 and 8.9). Four bodies would gain
+// up to 8192 knots (at 4096 5.6 and 6.3), but one lane per problem, which turns short branches in
+// double, rounds less there (dqdd/dq 6.4e-7 and 5.6e-7)
 static bool lane_per_body(grid_model m, int64_t N)
 {
     const int longest = m->topo.longest.bodies;

@@ -13,12 +13,11 @@
 //   4. inward: the derivatives from the subtrees' inertias, momenta and forces, each column moved
 //      up its ancestor path; dqdd/du_j = -M^-1 dtau/du_j by the two triangular solves
 //
-// 65536 knots of chain7 are one wavefront per SIMD: bound by issue (7,150 VALU instructions, 11.9
-// us) and by its stores, which do not overlap with it, since all wavefronts run in step (9 us at
-// the rate of a copy). 37.1 us per launch with a derivative sweep per column (15,452
-// instructions), 20.0 here; quad12 44.7 and 29.7 (writes at 4.3 TB/s), at 16384 knots 19.7 and
-// 10.2. FD / M^-1 / dID / VJP of chain7 at 32768 knots 13 / 11 / 19 / 19 us with one lane per body,
-// 5.6 / 5.5 / 12.0 / 14.3 here.
+// 65536 knots of chain7 are one wavefront per SIMD: bound by issue and by its stores, which do not
+// overlap with it, since all wavefronts run in step (9 us at the rate of a copy). 37.1 us per launch
+// with a derivative sweep per column, 21.0 here with half the instructions; quad12 44.7 and 32 (writes
+// at 4.0 TB/s), at 16384 knots 19.7 and 10.5. FD / M^-1 / dID / VJP of chain7 at 32768 knots 13 / 11 /
+// 19 / 19 us with one lane per body, 6.2 / 6.2 / 10.3 / 15.3 here.
 
 namespace grids {
 
@@ -281,9 +280,10 @@ __device__ __forceinline__ void flush_blocks(float* d0, float* d1, const float* 
 // LDS: the tiles of one matrix, or of two at a time where they are small (the addresses are then
 // computed once), and what a lane parks while it factors M and writes M^-1: 16 floats for every
 // body but the first. Without parking a branch of 7 bodies holds 330 floats there, which move
-// through the accumulation registers and scratch memory (65536 knots 21.4 us, 20.2 with it); one
-// of 3 bodies has room (7.0 us at 128 knots, 7.7 with it), and so have the halves of dFD (7 bodies
-// at 32768 knots 14.3, 22.8 with it: the LDS then leaves room for too few wavefronts)
+// through the accumulation registers and scratch memory (65536 knots 21.4 us, 20.2 with it, the rows
+// of M in float32 then); one of 3 bodies has room (7.0 us at 128 knots, 7.7 with it), and so have
+// the halves of dFD (7 bodies at 32768 knots 14.3, 22.8 with it: the LDS then leaves room for too few
+// wavefronts)
 template <class I, int OP>
 struct SerialLds {
     static constexpr int B = I::S::B;

@@ -13,10 +13,13 @@
 //
 // Bound by the latency of its chain of LDS exchanges up to a few wavefronts per SIMD, by VALU
 // issue beyond. humanoid30: 236 us per launch at 4096 knots and 648 at 16384 on the kernels it
-// took the place of, 23.5 and 69 here; chain7 at 4096 knots 11.4 and 8.8, quad12 7.8 and 6.8.
+// took the place of, 24.2 and 69.0 here (74.6 and 83.6 at 16384 where a run's outputs do not stay
+// in the caches); chain7 at 4096 knots 11.4 and 9.0, quad12 7.8 and 6.6.
 // FD / M^-1 / dID / VJP against the quad layout's (grid_ops.hip): humanoid30 at 4096 knots 46 /
-// 31 / 192 / 68 and 11 / 11 / 15 / 16 us, at 128 9.8 / 9.7 / 11.3 / 14.1 and 7.4 / 6.8 / 9.1 /
-// 10.4; chain7 at 32768 29 / 16 / 77 / 53 and 12 / 10 / 17 / 17.
+// 31 / 192 / 68 and 10.3 / 10.8 / 15.6 / 16.1 us, at 128 9.8 / 9.7 / 11.3 / 14.1 and 7.4 / 6.9 / 9.2 /
+// 10.5; chain7 dID at 8192 8.4 and 7.9. (Where a comment below gives figures of an alternative, both
+// sides are of this kernel with the rows of M in float32, 3 to 5% faster.)
+
 
 namespace gridt {
 
@@ -859,9 +862,10 @@ extern "C" __global__ void __launch_bounds__(64) grid_fdgrad_team(grid::Args arg
 }
 
 // dFD by two wavefronts: qdd and dqdd/dq; M^-1 and dqdd/dqd, which needs neither accelerations nor
-// forces. humanoid30 at 128, 1024, 1536 and 2048 knots 14.1 / 16.0 / 16.6 / 17.5 us by one, 11.5 /
-// 13.7 / 15.1 / 17.4 by two, at 4096 24.1 and 30.0; chain7 at 1024, 4096 and 8192 8.4 / 9.1 / 10.0
-// and 7.5 / 8.5 / 9.7, at 16384 12.7 and 18.4
+// forces. humanoid30 at 128, 1024, 1536 and 2048 knots 14.5 / 16.4 / 17.0 / 18.0 us by one, 11.8 /
+// 14.2 / 16.1 / 18.1 by two; chain7 at 1024 and 4096 8.9 / 9.5 and 7.85 / 9.0, at 8192 and 16384
+// 10.4 / 13.7 and 10.7 / 14.0
+
 #if GRID_LANE_PER_BODY
 extern "C" __global__ void __launch_bounds__(64) grid_fdgrad_team_halves(grid::Args args)
 {
