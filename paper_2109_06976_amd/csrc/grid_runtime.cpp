@@ -252,7 +252,7 @@ const char* kernel_name(grid_model m, int32_t N)
 static bool pipe_long(grid_model m, int64_t N)
 {
     const LongBranch& b = m->topo.longest;
-        if (b.bodies > 16 && b.shallow())
+    if (b.bodies > 16 && b.shallow())
         return N <= 8;
     return N * b.count * pipe_waves(m->topo) <= 4 * (int64_t)m->compute_units;
 }
